@@ -83,7 +83,7 @@ typedef enum {
   ARBOR_KERNEL_SCORE_ATTN = 0,    /* the two-pass score kernel of arbor_score      */
   ARBOR_KERNEL_SELECT = 1,        /* the selection kernel of arbor_select          */
   ARBOR_KERNEL_COMPACT_MOVE = 2,  /* the row-move kernel of arbor_compact          */
-  ARBOR_KERNEL_DECODE_ATTN = 3,   /* the attention kernels of arbor_tree_decode_attn */
+  ARBOR_KERNEL_DECODE_ATTN = 3,   /* the attention kernel of arbor_tree_decode_attn */
   ARBOR_KERNEL_DECODE_CREDIT = 4, /* the merge-and-credit kernel of
                                      arbor_tree_decode_attn_scored                 */
   ARBOR_KERNEL_COUNT = 5
@@ -91,9 +91,7 @@ typedef enum {
 
 /* (host) A timing request that belongs to one call: when a call launches
  * `kernel`, it records `start` on the launch stream right before that launch
- * and `stop` right after it (for ARBOR_KERNEL_DECODE_ATTN around the up to
- * three attention launches of the call, which run back to back), so
- * hipEventElapsedTime(start, stop) after the stream has synchronised is the
+ * and `stop` right after it, so hipEventElapsedTime(start, stop) after the stream has synchronised is the
  * kernel's own duration.  The caller owns the events (created with timing on
  * the device of the call) and the struct; the library keeps no reference
  * after the call returns.  Calls that do not launch `kernel` record nothing. */
@@ -391,8 +389,8 @@ typedef struct {
   int64_t *rows_seen;           /* device, int64 [V], in/out                         */
 } arbor_decode_credit_t;
 
-/* The attention units keep the logits of the distinct slice layers (fp32,
- * CHUNK = 256 per unit row and kv head) in the workspace; the launch that
+/* The attention units keep the logits of the distinct slice layers (fp32, a
+ * multiple of 64 per unit row and kv head) in the workspace; the launch that
  * merges the partials also turns them into the credited weights, its credit
  * workgroups forming each row's log-sum-exp from the chain's partials
  * themselves.  The workspace must be sized with arbor_sizes_t.n_slice >=

@@ -3,8 +3,10 @@
 // step depends only on the ancestor chain).
 //
 // Tree-aware split-K: a work unit is (chain node a, chunk of a's slots, layer,
-// kv head).  Its rows are the G query heads of every active leaf below a, so a
-// shared ancestor is streamed from HBM once for all leaves that need it.  A
+// kv head, up to 16 of the node's query rows).  The node's rows are the G query
+// heads of every active leaf below a, so a shared ancestor is streamed from HBM
+// once for all leaves that need it: the units of one chunk that differ only in
+// their rows are neighbouring waves, whose loads meet in the caches.  A
 // wave computes S = K Q^T with bf16 MFMA (keys along M, so each lane owns one
 // query row), an online softmax per fragment of keys, and O += P V.  For
 // bf16 pools P is split into a bf16 high part and a bf16 remainder, both
@@ -24,10 +26,47 @@ namespace {
 
 constexpr int MAXD = ARBOR_MAX_DEPTH + 1;
 static_assert(MAXD == kWave, "one wave covers a chain");
-constexpr int CHUNK = 256;        // slots per work unit
-constexpr int kPlanLds = 4096;    // trees up to this many nodes are planned from LDS
+// Slots of a chain node that one work unit takes: the plan picks the largest
+// of kChunks that still gives kMinUnits units, so that a call over few keys
+// (one layer of a model's own loop) is cut finely enough to fill the chip and
+// one over many keys writes and merges few partials.  Measured: one layer of a
+// 341-block tree under 16 leaves takes 35 us at 64 slots, 91 at the former 256
+// (with one launch per class of 16, 32 or 64 rows); 20 layers of the 70B shape
+// 355 us at up to 1,024, 373 at 512, 402 at 256; 32 layers of the 8B shape 122
+// us with at least 4,096 units (two for every wave the chip holds), 131 with
+// 2,048 and 135 with 8,192.
+constexpr int kChunks[] = {1024, 512, 256, 128, 64};
+constexpr int kNChunks = 5;
+constexpr int kMinChunk = 64, kMaxChunk = 1024;
+constexpr int kMinUnits = 4096;
+constexpr int kPlanLds = 4096;    // trees up to this many nodes are walked from LDS
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+
+// One chunk of a chain node and one block of 16 of its rows (for every layer
+// and kv head): all a wave needs besides the page ids and its query rows.
+struct __attribute__((aligned(16))) Unit {
+  int32_t po;        // first page-table entry of the node
+  int32_t s_begin;   // first slot
+  int32_t n_slots;
+  int32_t rowbase;   // partial row of the chunk's row 0
+  int32_t R;         // rows of the node: G per leaf below it
+  int32_t loff;      // its leaves in leaf_list
+  int32_t first;     // unit of the chunk's row block 0
+  int32_t zbase;     // its kept logits, [R][slots rounded up to 64]: first block of 64
+  int32_t node;
+  int32_t pad[3];
+};
+static_assert(sizeof(Unit) == 48, "three 16-byte loads");
+
+struct Meta {
+  int32_t n_units, rows, chunk, z_total;
+  int32_t max_np, pad;
+  int64_t parts;     // float offsets from `rest`: leaf_part entries, max_np per leaf,
+  int64_t ml;        //   (max, sum) of the partial rows,
+  int64_t part;      //   their unnormalised outputs,
+  int64_t z;         //   kept logits
+};
 
 struct DecArgs {
   Tree t;
@@ -38,29 +77,23 @@ struct DecArgs {
   const void *q;
   float sl2;
   // plan outputs
-  const int32_t *meta;        // [0..2] items per class, [3] total rows
-  const int32_t *cls_items;   // [3][max_items]
-  int max_items;
-  const int32_t *item_node;   // [items]
-  const int32_t *item_chunk;
-  const int32_t *item_rowbase;
-  const int32_t *node_nl;     // leaves below a node (0 off the path)
-  const int32_t *node_leaf_off;
-  const int32_t *leaf_list;   // leaves below each node, in leaf order
-  const int32_t *node_item0;  // first item of each path node
-  const int32_t *node_rowbase;
-  const int32_t *lanc;        // [n_leaves][MAXD]
-  const int32_t *ldepth;
-  const int32_t *lrank;       // [n_leaves][MAXD]
-  const int32_t *leaf_np;     // partials of each leaf's chain
-  const int32_t *leaf_part;   // [n_leaves][max_parts]: first partial row of the leaf's heads
-  int max_parts;
-  float *part;
-  int64_t part_cap;
-  int zS;                     // credit calls: distinct slice layers whose logits the units keep
-  int zlr[8];                 //   (relative to l0); zS = 0 otherwise
+  Meta *meta;
+  int32_t *leaf_list;   // leaves below each chain node, in leaf order
+  int32_t *lanc;        // [n_leaves][MAXD] chain of each leaf, root first
+  int32_t *ldepth;
+  int32_t *leaf_np;     // partials of each leaf's chain
+  // units, leaf_part (first partial row of the leaf's heads, per partial), the
+  // partials and the kept logits follow one another here
+  float *rest;
+  int64_t rest_cap;     // floats
+  int zS;               // credit calls: distinct slice layers whose logits the units keep
+  int zlr[8];           //   (relative to l0); zS = 0 otherwise
   int32_t *status;
 };
+
+__device__ __forceinline__ const Unit *units_of(const DecArgs &a) {
+  return reinterpret_cast<const Unit *>(a.rest);
+}
 
 // The decode-time credit of accumulated attention: slice layers relative to
 // the call's first layer, the crediting mode and the caller's A / rows_seen.
@@ -74,208 +107,283 @@ struct CreditArgs {
   int64_t *rows_seen;
 };
 
-// Plan of one call, in one workgroup: each active leaf's chain (root first),
-// the leaves below every node (in leaf order), the work units (chunks of the
-// chain nodes' slots, per class of row count), each unit's partial rows and
-// each leaf's list of partials, root first.  The per-node and per-leaf state
-// sits in LDS for trees of up to kPlanLds nodes and up to kPlanLeaves leaves,
-// so the chain walks, ranks and scans wait on global memory only for the
-// tree's arrays.  SMALL / FEW are template arguments, so that every access
-// compiles to an LDS or a global instruction rather than a flat one.
+// Plan of one call, in one workgroup.  Every (leaf, depth) entry of the active
+// chains finds the other leaves below its node: the first of them stands for
+// the node (its entry's rank is 0) and brings the node's units, the others
+// only their place in its leaf list.  The work is O(leaves depth), not O(V):
+// only the parent links are read for the whole tree (into LDS, for trees of up
+// to kPlanLds nodes, so that the chain walks do not wait on global memory).
+// There the leaves below a node are one 64-bit mask, set during the walks (up
+// to kPlanLeaves leaves); otherwise an entry compares its node with the other
+// leaves' nodes of its depth.  The units are written by all threads, each
+// finding its unit's entry by a binary search.  SMALL / FEW are template
+// arguments, so that every access compiles to an LDS or a global instruction
+// rather than a flat one.
+// Bound by latency: 16 leaves of a 341-block tree take 8.2 us; with a
+// comparison against every leaf and each node's thread writing its units
+// 14.8, and 9.7 for the former plan, which scanned all V nodes.
 constexpr int kPlanLeaves = 64;
+
+// per-entry state, [n_leaves][MAXD] each (workspace for many leaves); entry
+// e = leaf * ds + depth for chains of at most ds blocks
+struct PlanEnt {
+  int32_t *up;       // [n_leaves][MAXD]: the chain, leaf first
+  int32_t *kept, *rbase, *loff, *np, *u0, *z0;
+  uint64_t *place;   // rank | first << 21 | leaves below << 42
+};
+constexpr int kPlanEnts = 7;
+
+struct Place {
+  int rank, first, nl;
+};
+
 template <bool SMALL, bool FEW>
-__global__ __launch_bounds__(1024) void decode_plan(DecArgs a, int32_t *meta, int32_t *cls_items,
-                                                    int32_t *item_node, int32_t *item_chunk,
-                                                    int32_t *item_rowbase, int32_t *node_nl,
-                                                    int32_t *node_leaf_off, int32_t *leaf_list,
-                                                    int32_t *node_item0, int32_t *node_rowbase,
-                                                    int32_t *lanc, int32_t *ldepth,
-                                                    int32_t *lrank, int32_t *leaf_np,
-                                                    int32_t *leaf_part) {
-  __shared__ int64_t sm[6 * 16];
-  __shared__ int s_err;
-  __shared__ int32_t s_par[kPlanLds], s_nl[kPlanLds], s_kept[kPlanLds], s_loff[kPlanLds],
-      s_rbase[kPlanLds], s_item0[kPlanLds];
-  __shared__ int32_t s_lanc[kPlanLeaves * MAXD], s_lrank[kPlanLeaves * MAXD], s_ldep[kPlanLeaves];
+__global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
+  constexpr bool MASKS = SMALL && FEW;
+  constexpr int kEnt = FEW ? kPlanLeaves * MAXD : 1;
+  __shared__ int64_t sm[3 * 16];
+  __shared__ int s_cu[kNChunks * 16];
+  __shared__ int s_err, s_maxd, s_maxnp;
+  // the parent links are not needed once the chains are known: u0 takes their place
+  static_assert(kPlanLds >= kPlanLeaves * MAXD, "u0 fits");
+  __shared__ int32_t s_par[SMALL ? kPlanLds : kEnt];
+  __shared__ uint64_t s_mask[MASKS ? kPlanLds : kEnt];   // or the entries' places
+  __shared__ int32_t s_ent[kPlanEnts - 1][kEnt];
+  __shared__ int32_t s_ldep[FEW ? kPlanLeaves : 1];
   const Tree &t = a.t;
-  const int V = t.V;
-  const int G = a.pl.G;
-  const int nt = blockDim.x;
-  const int tid = threadIdx.x;
+  const int V = t.V, G = a.pl.G, nb = a.n_leaves;
+  const int nt = blockDim.x, tid = threadIdx.x;
   // each thread's first node and leaf are loaded together with the status word
-  const int par0 = tid < V ? t.parent[tid] : 0, kept0 = tid < V ? t.n_kept[tid] : 0;
-  const int leaf0 = tid < a.n_leaves ? a.leaves[tid] : 0;
+  const int par0 = SMALL && tid < V ? t.parent[tid] : 0;
+  const int leaf0 = tid < nb ? a.leaves[tid] : 0;
   if (status_failed(a.status)) {
-    if (threadIdx.x == 0) meta[0] = meta[1] = meta[2] = 0;
+    if (tid == 0) a.meta->n_units = 0;
     return;
   }
-  constexpr bool small = SMALL;
-  constexpr bool few = FEW;
-  const int32_t *par = small ? s_par : t.parent;
-  const int32_t *kept = small ? s_kept : t.n_kept;
-  int32_t *nlp = small ? s_nl : node_nl;
-  int32_t *loffp = small ? s_loff : node_leaf_off;
-  int32_t *rbasep = small ? s_rbase : node_rowbase;
-  int32_t *item0p = small ? s_item0 : node_item0;
-  int32_t *lancp = few ? s_lanc : lanc;
-  int32_t *lrankp = few ? s_lrank : lrank;
-  int32_t *ldepp = few ? s_ldep : ldepth;
-  if (tid == 0) s_err = 0;
-  for (int i = tid; i < V; i += nt) {
-    nlp[i] = 0;
-    if (small) {
+  PlanEnt en;
+  if constexpr (FEW)
+    en = PlanEnt{s_ent[0], s_ent[1], s_ent[2], s_ent[3], s_ent[4], s_par, s_ent[5], s_mask};
+  else
+    en = gent;
+  int32_t *ldepp = FEW ? s_ldep : a.ldepth;
+  if (tid == 0) s_err = s_maxd = s_maxnp = 0;
+  if constexpr (SMALL)
+    for (int i = tid; i < V; i += nt) {
       s_par[i] = i == tid ? par0 : t.parent[i];
-      s_kept[i] = i == tid ? kept0 : t.n_kept[i];
+      if (MASKS) s_mask[i] = 0;
     }
-  }
+  const int32_t *par = SMALL ? s_par : t.parent;
   __syncthreads();
-  for (int b = tid; b < a.n_leaves; b += nt) {
+  for (int b = tid; b < nb; b += nt) {
     const int l = b == tid ? leaf0 : a.leaves[b];
-    if (l < 0 || l >= V) {
-      atomicOr(&s_err, 1);
-      ldepp[b] = -1;
-      continue;
-    }
-    // validate and measure the chain, then write it root first (two walks up
-    // the parent links keep the chain out of per-lane scratch memory)
-    int d = 0, bad = 0;
-    for (int x = l; x >= 0; x = par[x]) {
-      if ((x > 0 && (par[x] < 0 || par[x] >= x)) || (x == 0 && par[x] != -1)) {
-        bad = 1;
-        break;
-      }
-      if (++d > MAXD) {
-        bad = 2;
-        break;
-      }
+    int d = 0, bad = l < 0 || l >= V ? 1 : 0;
+    // validate the chain and keep it, leaf first
+    for (int x = l; x >= 0 && !bad;) {
+      const int px = par[x];
+      if (px >= x || px < (x > 0 ? 0 : -1)) bad = 1;
+      else if (d == MAXD) bad = 2;
+      else en.up[b * MAXD + d++] = x;
+      if (MASKS)
+        atomicOr(reinterpret_cast<unsigned long long *>(&s_mask[x]), 1ull << (b & 63));
+      x = px;
     }
     if (bad) {
       atomicOr(&s_err, bad);
-      ldepp[b] = -1;
-      continue;
+      d = 0;
     }
     ldepp[b] = d - 1;
-    int e = d - 1;
-    for (int x = l; x >= 0; x = par[x], --e) {
-      lancp[(int64_t)b * MAXD + e] = x;
-      atomicAdd(&nlp[x], 1);
-    }
+    if (FEW) a.ldepth[b] = d - 1;
+    atomicMax(&s_maxd, d - 1);
   }
   __syncthreads();
   if (s_err) {
     if (tid == 0) {
       status_error(a.status, (s_err & 1) ? ARBOR_EINVAL : ARBOR_EUNSUPPORTED);
-      meta[0] = meta[1] = meta[2] = 0;
+      a.meta->n_units = 0;
     }
     return;
   }
-  // rank of each leaf among the leaves below each of its chain nodes
-  for (int e = tid; e < a.n_leaves * MAXD; e += nt) {
-    const int b = e / MAXD, d = e % MAXD;
-    if (d > ldepp[b]) continue;
-    const int x = lancp[(int64_t)b * MAXD + d];
-    int r = 0;
-    for (int b2 = 0; b2 < b; ++b2)
-      if (ldepp[b2] >= d && lancp[(int64_t)b2 * MAXD + d] == x) ++r;
-    lrankp[(int64_t)b * MAXD + d] = r;
-  }
-  // per-node offsets: leaf lists, items, partial rows; and class lists
-  int64_t run_leaf = 0, run_item = 0, run_rows = 0, run_cls[3] = {0, 0, 0};
-  for (int base = 0; base < V; base += nt) {
-    const int i = base + tid;
-    const int nl = i < V ? nlp[i] : 0;
-    if (small && i < V) node_nl[i] = nl;
-    const int c = (i < V && nl > 0) ? kept[i] : 0;
-    const int chunks = (c + CHUNK - 1) / CHUNK;
-    const int rows = nl * G;
-    const int nbr = (rows + 15) / 16;
-    const int cls = nbr <= 1 ? 0 : (nbr <= 2 ? 1 : 2);
-    const int64_t sv[6] = {nl, chunks, (int64_t)chunks * rows, cls == 0 ? chunks : 0,
-                           cls == 1 ? chunks : 0, cls == 2 ? chunks : 0};
-    int64_t sx[6], stot[6];
-    block_exclusive_scan_n<6>(sv, sx, stot, sm);
-    if (i < V) {
-      const int lo = (int32_t)(run_leaf + sx[0]);
-      const int it0 = (int32_t)(run_item + sx[1]);
-      const int rb = (int32_t)(run_rows + sx[2]);
-      loffp[i] = lo;
-      item0p[i] = it0;
-      rbasep[i] = rb;
-      if (small) {
-        node_leaf_off[i] = lo;
-        node_item0[i] = it0;
-        node_rowbase[i] = rb;
+  const int ds = s_maxd + 1;
+  const int n_e = nb * ds;
+  // the leaves below the node of entry e (node x of leaf b at depth d)
+  auto place = [&](int e, int b, int x) __attribute__((always_inline)) -> Place {
+    const uint64_t m = en.place[MASKS ? x : e];
+    if constexpr (MASKS)
+      return Place{popc(m & ((1ull << b) - 1)), (int)__builtin_ctzll(m), popc(m)};
+    constexpr uint64_t k = (1ull << 21) - 1;
+    return Place{(int)(m & k), (int)((m >> 21) & k), (int)(m >> 42)};
+  };
+  int64_t cu[kNChunks];
+#pragma unroll
+  for (int k = 0; k < kNChunks; ++k) cu[k] = 0;
+  for (int e = tid; e < n_e; e += nt) {
+    const int b = e / ds, d = e - b * ds;
+    const int dl = ldepp[b];
+    if (d > dl) continue;
+    const int x = en.up[b * MAXD + dl - d];
+    const int c = t.n_kept[x];
+    if constexpr (!MASKS) {
+      int r = 0, cnt = 0, first = b;
+#pragma unroll 4
+      for (int b2 = 0; b2 < nb; ++b2) {
+        const int d2 = ldepp[b2];
+        const bool same = d2 >= d && en.up[b2 * MAXD + (d2 >= d ? d2 - d : 0)] == x;
+        cnt += same ? 1 : 0;
+        r += same && b2 < b ? 1 : 0;
+        first = same && b2 < first ? b2 : first;
       }
-      const int64_t ce = cls == 0 ? run_cls[0] + sx[3]
-                                  : (cls == 1 ? run_cls[1] + sx[4] : run_cls[2] + sx[5]);
-      for (int q = 0; q < chunks; ++q) {
-        const int64_t it = it0 + q;
-        item_node[it] = i;
-        item_chunk[it] = q;
-        item_rowbase[it] = (int32_t)(rb + (int64_t)q * rows);
-        cls_items[(int64_t)cls * a.max_items + ce + q] = (int32_t)it;
+      en.place[e] = (uint64_t)r | ((uint64_t)first << 21) | ((uint64_t)cnt << 42);
+    }
+    const Place pc = place(e, b, x);
+    a.lanc[b * MAXD + d] = x;
+    en.kept[e] = c;
+    if (pc.rank == 0) {
+      const int nbr = (pc.nl * G + 15) / 16;
+#pragma unroll
+      for (int k = 0; k < kNChunks; ++k)
+        cu[k] += (int64_t)((c + kChunks[k] - 1) / kChunks[k]) * nbr;
+    }
+  }
+  // the chunk size (counts of units, saturated: only their order against
+  // kMinUnits matters)
+  int C = kMinChunk;
+  {
+    const int planes = a.Lr * a.pl.Hkv;
+    const int nw = nt >> 6;
+    if ((tid & ~(kWave - 1)) < n_e) {
+      int v[kNChunks];
+#pragma unroll
+      for (int k = 0; k < kNChunks - 1; ++k)
+        v[k] = wave_sum((int)(cu[k] * planes < kMinUnits ? cu[k] * planes : kMinUnits));
+      if (lane_id() == 0)
+#pragma unroll
+        for (int k = 0; k < kNChunks - 1; ++k) s_cu[k * 16 + (tid >> 6)] = v[k];
+    } else if (lane_id() < kNChunks - 1) {
+      s_cu[lane_id() * 16 + (tid >> 6)] = 0;
+    }
+    __syncthreads();
+    // lane (k, w) holds wave w's count for size k
+    static_assert((kNChunks - 1) * 16 == kWave, "one row of 16 lanes per chunk size");
+    int s = (lane_id() & 15) < nw ? s_cu[lane_id()] : 0;
+    s += dpp_move<dpp::kQuadXor1>(s);
+    s += dpp_move<dpp::kQuadXor2>(s);
+    s += dpp_move<dpp::kRowHalfMirror>(s);
+    s += dpp_move<dpp::kRowMirror>(s);
+    const uint64_t m = ballot(s >= kMinUnits);
+#pragma unroll
+    for (int k = kNChunks - 2; k >= 0; --k) C = (m >> (16 * k)) & 1 ? kChunks[k] : C;
+  }
+  const int lc = 31 - __builtin_clz(C);      // chunks of c slots: (c + C - 1) >> lc
+  // units, partial rows, leaf-list places and logit slots of every node, in
+  // the order of its first leaf's chain; v[0] carries units (high half) and
+  // leaf-list entries (low half)
+  int64_t run[3] = {0, 0, 0};
+  for (int base = 0; base < n_e; base += nt) {
+    const int e = base + tid;
+    const int b = e / ds, d = e - b * ds;
+    int64_t v[3] = {0, 0, 0};
+    if (e < n_e && d <= ldepp[b]) {
+      const int c = en.kept[e];
+      const int chunks = (c + C - 1) >> lc;
+      // the entry's place among its leaf's partials: the chunks above it
+      int np = 0;
+      for (int d2 = 0; d2 < d; ++d2) np += (en.kept[e - d + d2] + C - 1) >> lc;
+      en.np[e] = np;
+      if (d == ldepp[b]) {
+        a.leaf_np[b] = np + chunks;
+        atomicMax(&s_maxnp, np + chunks);
+      }
+      const Place pc = place(e, b, en.up[b * MAXD + ldepp[b] - d]);
+      if (pc.rank == 0) {
+        const int R = pc.nl * G;
+        v[0] = ((int64_t)chunks * ((R + 15) / 16) << 32) | pc.nl;
+        v[1] = (int64_t)chunks * R;
+        v[2] = (int64_t)R * ((c + 63) / 64);
       }
     }
-    run_leaf += stot[0];
-    run_item += stot[1];
-    run_rows += stot[2];
-    run_cls[0] += stot[3];
-    run_cls[1] += stot[4];
-    run_cls[2] += stot[5];
+    int64_t ex[3], tot[3];
+    block_exclusive_scan_n<3>(v, ex, tot, sm, n_e - base);
+    if (e < n_e) {
+      en.u0[e] = (int)((run[0] + ex[0]) >> 32);
+      en.loff[e] = (int)(uint32_t)(run[0] + ex[0]);
+      en.rbase[e] = (int)(run[1] + ex[1]);
+      en.z0[e] = (int)(run[2] + ex[2]);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) run[k] += tot[k];
   }
   __syncthreads();
-  for (int e = tid; e < a.n_leaves * MAXD; e += nt) {
-    const int b = e / MAXD, d = e % MAXD;
-    if (d > ldepp[b]) continue;
-    const int x = lancp[(int64_t)b * MAXD + d];
-    leaf_list[loffp[x] + lrankp[(int64_t)b * MAXD + d]] = b;
-    if (few) lanc[(int64_t)b * MAXD + d] = x;
-  }
-  if (few)
-    for (int b = tid; b < a.n_leaves; b += nt) ldepth[b] = s_ldep[b];
-  // each leaf's partials, root first, so the merge needs no chain walk: one
-  // thread per (leaf, chain depth); the offsets come from a per-leaf scan of
-  // the chunk counts along the chain (at most MAXD entries)
-  for (int b0 = 0; b0 < a.n_leaves; b0 += nt / MAXD) {
-    const int b = b0 + tid / MAXD;
-    const int d = tid % MAXD;
-    const bool live = b < a.n_leaves && d <= ldepp[b];
-    int x = 0, nch = 0;
-    if (live) {
-      x = lancp[(int64_t)b * MAXD + d];
-      nch = (kept[x] + CHUNK - 1) / CHUNK;
-    }
-    // inclusive scan over the MAXD threads of this leaf (MAXD = kWave)
-    const int incl = wave_inclusive_scan<int>(nch);
-    const int np = incl - nch;
-    if (live) {
-      const int r = lrankp[(int64_t)b * MAXD + d] * G;
-      const int rows = nlp[x] * G;
-      if (incl > a.max_parts) {
-        atomicOr(&s_err, 4);  // more resident tokens than the workspace was sized for
-      } else {
-        for (int q = 0; q < nch; ++q)
-          leaf_part[(int64_t)b * a.max_parts + np + q] = rbasep[x] + q * rows + r;
-      }
-      if (d == ldepp[b]) leaf_np[b] = min(incl, a.max_parts);
-    }
-  }
-  __syncthreads();
+  const int64_t n_units = run[0] >> 32;
+  const int max_np = s_maxnp;
+  const int64_t parts = n_units * (int64_t)(sizeof(Unit) / 4);
   if (tid == 0) {
-    // the partials, then (credit calls) the slice-layer logits of every unit
-    // row and slot: [slice][kv head][row][CHUNK]
-    const int64_t need_p = (run_rows * a.Lr * a.pl.Hkv * (int64_t)(a.pl.D + 2) + 3) & ~(int64_t)3;
-    const int64_t need = need_p + (int64_t)a.zS * a.pl.Hkv * run_rows * CHUNK;
-    if (run_item > a.max_items || need > a.part_cap || need_p > INT32_MAX || s_err) {
+    // the units and the partial lists, the partials, then (credit calls) the
+    // slice-layer logits of every node's rows and slots, in blocks
+    // of 64 floats: [slice][kv head][z_total]
+    Meta m;
+    const int64_t planes = (int64_t)a.Lr * a.pl.Hkv;
+    m.n_units = (int32_t)n_units;
+    m.rows = (int32_t)run[1];
+    m.chunk = C;
+    m.z_total = (int32_t)run[2];
+    m.max_np = max_np;
+    m.pad = 0;
+    m.parts = parts;
+    m.ml = (parts + (int64_t)nb * max_np + 3) & ~(int64_t)3;
+    m.part = (m.ml + run[1] * planes * 2 + 3) & ~(int64_t)3;
+    m.z = m.part + run[1] * planes * a.pl.D;
+    const int64_t need = m.z + (int64_t)a.zS * a.pl.Hkv * run[2] * 64;
+    if (need > a.rest_cap || run[1] > INT32_MAX || run[2] > INT32_MAX) {
       status_error(a.status, ARBOR_EWORKSPACE);
-      meta[0] = meta[1] = meta[2] = 0;
-      return;
+      m.n_units = 0;
     }
-    meta[0] = (int32_t)run_cls[0];
-    meta[1] = (int32_t)run_cls[1];
-    meta[2] = (int32_t)run_cls[2];
-    meta[3] = (int32_t)run_rows;
-    meta[4] = (int32_t)need_p;
+    *a.meta = m;
+  }
+  // the units
+  Unit *units = reinterpret_cast<Unit *>(a.rest);
+  const int64_t unit_cap = a.rest_cap / (int64_t)(sizeof(Unit) / 4);
+  for (int64_t i = tid; i < n_units && i < unit_cap; i += nt) {
+    int lo = 0, hi = n_e - 1;                 // the last entry with u0 <= i
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (en.u0[mid] <= (int)i) lo = mid;
+      else hi = mid - 1;
+    }
+    const int b = lo / ds, d = lo - b * ds;
+    const int x = en.up[b * MAXD + ldepp[b] - d];
+    const int po = (int)t.page_off[x];
+    const int c = en.kept[lo];
+    const int R = place(lo, b, x).nl * G;
+    const int nbr = (R + 15) / 16;
+    const int q = ((int)i - en.u0[lo]) / nbr;
+    Unit u;
+    u.po = po;
+    u.s_begin = q << lc;
+    u.n_slots = min(C, c - (q << lc));
+    u.rowbase = en.rbase[lo] + q * R;
+    u.R = R;
+    u.loff = en.loff[lo];
+    u.first = en.u0[lo] + q * nbr;
+    u.zbase = en.z0[lo] + R * (q << (lc - 6));
+    u.node = x;
+    u.pad[0] = u.pad[1] = u.pad[2] = 0;
+    units[i] = u;
+  }
+  // the leaves below each node, and each leaf's partials, root first (so the
+  // merge needs no chain walk)
+  int32_t *leaf_part = reinterpret_cast<int32_t *>(a.rest) + parts;
+  const int64_t parts_cap = a.rest_cap - parts;
+  for (int e = tid; e < n_e; e += nt) {
+    const int b = e / ds, d = e - b * ds;
+    if (d > ldepp[b]) continue;
+    const Place pc = place(e, b, en.up[b * MAXD + ldepp[b] - d]);
+    const int f = pc.first * ds + d;
+    a.leaf_list[en.loff[f] + pc.rank] = b;
+    const int nch = (en.kept[e] + C - 1) >> lc;
+    const int rb = en.rbase[f] + pc.rank * G, rows = pc.nl * G;
+    const int64_t o = (int64_t)b * max_np + en.np[e];
+    for (int q = 0; q < nch; ++q)
+      if (o + q < parts_cap) leaf_part[o + q] = rb + q * rows;
   }
 }
 
@@ -336,73 +444,57 @@ __device__ __forceinline__ KVFrag<T, D, GSP> fetch_kv(const UnitAddr &ua, int pg
 // rescaled only when some row's running max moved.
 // zs (when keep_z) receives the fragment's masked logits in log2 units, the
 // weights the decode-time credit normalises later; the caller stores them.
-template <class T, int D, int NB, int GSP>
+template <class T, int D, int GSP>
 __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
-                                       const typename Op<T>::reg (&q)[NB][KVFrag<T, D, GSP>::KS],
-                                       float sl2, int g4, float (&m_run)[NB], float (&l_run)[NB],
-                                       f32x4 (&o)[NB][D / 16], bool keep_z,
-                                       float (&zs)[GSP][NB][4]) {
+                                       const typename Op<T>::reg (&q)[KVFrag<T, D, GSP>::KS],
+                                       float sl2, int g4, float &m_run, float &l_run,
+                                       f32x4 (&o)[D / 16], f32x4 (&ot)[D / 16], bool keep_z,
+                                       float (&zs)[GSP][4]) {
   typedef KVFrag<T, D, GSP> F;
   constexpr int NC = F::NC;
-  float sv[GSP][NB][4];
-  float gmax[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) gmax[nb] = -__builtin_inff();
+  float sv[GSP][4];
+  float gmax = -__builtin_inff();
 #pragma unroll
   for (int sp = 0; sp < GSP; ++sp) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < F::KS; ++ks) acc = Op<T>::mma(f.k[sp][ks], q[ks], acc);
 #pragma unroll
-      for (int ks = 0; ks < F::KS; ++ks) acc = Op<T>::mma(f.k[sp][ks], q[nb][ks], acc);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sv[sp][nb][e] = acc[e] * sl2;
-    }
+    for (int e = 0; e < 4; ++e) sv[sp][e] = acc[e] * sl2;
     if (f.nval[sp] < 16) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          sv[sp][nb][e] = 4 * g4 + e < f.nval[sp] ? sv[sp][nb][e] : -__builtin_inff();
+      for (int e = 0; e < 4; ++e)
+        sv[sp][e] = 4 * g4 + e < f.nval[sp] ? sv[sp][e] : -__builtin_inff();
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int cc = 0; cc < NC; ++cc)
           f.v[sp][e][cc] = 4 * g4 + e < f.nval[sp] ? f.v[sp][e][cc] : (typename F::VT)0.f;
     }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      gmax[nb] = fmaxf(gmax[nb], fmaxf(fmaxf(sv[sp][nb][0], sv[sp][nb][1]),
-                                       fmaxf(sv[sp][nb][2], sv[sp][nb][3])));
+    gmax = fmaxf(gmax, fmaxf(fmaxf(sv[sp][0], sv[sp][1]), fmaxf(sv[sp][2], sv[sp][3])));
     if (keep_z) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) zs[sp][nb][e] = sv[sp][nb][e];
+      for (int e = 0; e < 4; ++e) zs[sp][e] = sv[sp][e];
     }
   }
-  bool moved = false;
-  float alpha[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    gmax[nb] = across_rows(gmax[nb], [](float x, float y) { return fmaxf(x, y); });
-    const float mn = fmaxf(m_run[nb], gmax[nb]);
-    moved |= mn != m_run[nb];
-    alpha[nb] = (m_run[nb] > -__builtin_inff()) ? __builtin_amdgcn_exp2f(m_run[nb] - mn) : 0.f;
-    m_run[nb] = mn;
-  }
+  gmax = across_rows(gmax, [](float x, float y) { return fmaxf(x, y); });
+  const float mn = fmaxf(m_run, gmax);
+  const bool moved = mn != m_run;
+  const float alpha = m_run > -__builtin_inff() ? __builtin_amdgcn_exp2f(m_run - mn) : 0.f;
+  m_run = mn;
   if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+    l_run *= alpha;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      l_run[nb] *= alpha[nb];
+    for (int e = 0; e < 4; ++e) {
+      const float fe = __shfl(alpha, 4 * g4 + e, kWave);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float fe = __shfl(alpha[nb], 4 * g4 + e, kWave);
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) o[nb][cc][e] *= fe;
+      for (int cc = 0; cc < NC; ++cc) {
+        o[cc][e] *= fe;
+        ot[cc][e] *= fe;
       }
     }
   }
+  const float nm = m_run > -__builtin_inff() ? -m_run : 0.f;
   if constexpr (sizeof(T) == 2) {
     // bf16 values: O += P V as bf16 MFMAs (16x16x32), one per 16 output
     // columns and pair of sub-pages sp0, sp0 + 1 of the fragment, element t =
@@ -413,25 +505,18 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
     // quarter of the fp32 MFMA's issue time.
 #pragma unroll
     for (int sp0 = 0; sp0 < GSP; sp0 += 2) {
-      bf16x8 ph[NB], pl[NB];
+      bf16x8 ph, pl;
+      float p[8];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float nm = m_run[nb] > -__builtin_inff() ? -m_run[nb] : 0.f;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int sp = sp0 + t / 4, e = t % 4;
-          if (sp < GSP) {
-            const float p = __builtin_amdgcn_exp2f(sv[sp][nb][e] + nm);
-            l_run[nb] += p;
-            const __bf16 hi = (__bf16)p;
-            ph[nb][t] = hi;
-            pl[nb][t] = (__bf16)(p - (float)hi);
-          } else {
-            ph[nb][t] = (__bf16)0.f;
-            pl[nb][t] = (__bf16)0.f;
-          }
-        }
+      for (int t = 0; t < 8; ++t) {
+        const int sp = sp0 + t / 4, e = t % 4;
+        p[t] = sp < GSP ? __builtin_amdgcn_exp2f(sv[sp < GSP ? sp : 0][e] + nm) : 0.f;
+        const __bf16 hi = (__bf16)p[t];
+        ph[t] = hi;
+        pl[t] = (__bf16)(p[t] - (float)hi);
       }
+      // (pairwise: the running sum of a 1,024-slot chunk takes 32 terms, not 256)
+      l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
         bf16x8 vv;
@@ -440,57 +525,48 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
           const int sp = sp0 + t / 4;
           vv[t] = sp < GSP ? (__bf16)f.v[sp < GSP ? sp : 0][t % 4][cc] : (__bf16)0.f;
         }
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          o[nb][cc] = Op<__bf16>::mma(ph[nb], vv, o[nb][cc]);
-          o[nb][cc] = Op<__bf16>::mma(pl[nb], vv, o[nb][cc]);
-        }
+        o[cc] = Op<__bf16>::mma(ph, vv, o[cc]);
+        o[cc] = Op<__bf16>::mma(pl, vv, o[cc]);
       }
     }
   } else {
 #pragma unroll
     for (int sp = 0; sp < GSP; ++sp) {
+      float p[4];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        float p[4];
-        const float nm = m_run[nb] > -__builtin_inff() ? -m_run[nb] : 0.f;
+      for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(sv[sp][e] + nm);
+      l_run += (p[0] + p[1]) + (p[2] + p[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          p[e] = __builtin_amdgcn_exp2f(sv[sp][nb][e] + nm);
-          l_run[nb] += p[e];
-        }
+      for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-          for (int cc = 0; cc < NC; ++cc)
-            o[nb][cc] = mma_f32(p[ks], (float)f.v[sp][ks][cc], o[nb][cc]);
-      }
+        for (int cc = 0; cc < NC; ++cc) o[cc] = mma_f32(p[ks], (float)f.v[sp][ks][cc], o[cc]);
     }
   }
 }
 
 // Sub-pages a wave loads at once: 16 KB of K and V in flight per wave, one
 // fragment at a time.  Measured on the llama8b and dpts trees: with a single
-// buffer the 16-row waves fit three to a SIMD, whose loads overlap one
-// another's work; double-buffered fragments, or larger ones, leave one or
-// two waves per SIMD and stream HBM more slowly.
-template <class T, int D, int NB>
+// buffer the waves fit three to a SIMD, whose loads overlap one another's
+// work; double-buffered fragments, or larger ones, leave one or two waves per
+// SIMD and stream HBM more slowly.
+template <class T, int D>
 constexpr int sub_pages_per_fetch() {
   constexpr int per = 32 * D * (int)sizeof(T);   // K and V of one 16-slot sub-page
   return (16 << 10) / per < 1 ? 1 : (16 << 10) / per;
 }
 
-// One wave: one work unit (a CHUNK of a chain node's slots, one layer, one kv
-// head), rows [rbase, rbase + 16 NB).  The unit's sub-pages are taken GSP at
+// One wave: one unit (a chunk of a chain node's slots, one layer, one kv
+// head), rows [rbase, rbase + 16).  The unit's sub-pages are taken GSP at
 // a time (the last fragment of a unit re-reads its last sub-page in the
 // unused places, which the cache serves); other waves of the SIMD attend
 // while one waits for its fragment.
 // KZ: the call credits (some slice layers keep their logits); a plain call
 // compiles without that path and its registers.
-template <class T, int D, int NB, bool KZ>
-__device__ void decode_unit(const DecArgs &a, int item, int lr, int g, int rbase) {
+template <class T, int D, bool KZ>
+__device__ __forceinline__ void decode_unit(const DecArgs &a, const Meta &mt, const Unit &un,
+                                            int lr, int g, int rbase) {
   using O = Op<T>;
-  constexpr int GSP = sub_pages_per_fetch<T, D, NB>();
+  constexpr int GSP = sub_pages_per_fetch<T, D>();
   typedef KVFrag<T, D, GSP> F;
   constexpr int KS = F::KS;
   constexpr int NC = F::NC;
@@ -500,43 +576,28 @@ __device__ void decode_unit(const DecArgs &a, int item, int lr, int g, int rbase
   const int rr = lane & 15;
   const int g4 = lane >> 4;
   const int G = pl.G;
-  const int node = a.item_node[item];
-  const int chunk = a.item_chunk[item];
-  const int nl = a.node_nl[node];
-  const int R = nl * G;
-  const int c = t.n_kept[node];
-  const int s_begin = chunk * CHUNK;
-  const int s_end = min(c, s_begin + CHUNK);
+  const int R = un.R;
+  const int s_begin = un.s_begin, s_end = un.s_begin + un.n_slots;
   const int layer = a.l0 + lr;
   const int Hq = pl.Hkv * G;
-  const int64_t po = t.page_off[node];
-  const int loff = a.node_leaf_off[node];
-  const int n_sub = (s_end - s_begin + 15) / 16;
+  const int n_sub = (un.n_slots + 15) / 16;
   const int n_grp = (n_sub + GSP - 1) / GSP;
   // page ids of all sub-pages up front: a dependent load inside the pipeline
   // would make every wait cover the fragment still in flight
-  static_assert(CHUNK / 16 <= kWave, "one lane per sub-page");
-  const int pg = lane < n_sub ? t.page_table[po + (s_begin + 16 * lane) / pl.P] : 0;
+  static_assert(kMaxChunk / 16 <= kWave, "one lane per sub-page");
+  const int pg = lane < n_sub ? t.page_table[un.po + (s_begin + 16 * lane) / pl.P] : 0;
 
-  int qleaf[NB];
+  const int r = rbase + rr;
+  typename O::reg q[KS];
+  if (r < R) {
+    const int b = a.leaf_list[un.loff + r / G];
+    const int h = g * G + r % G;
+    const T *qp = static_cast<const T *>(a.q) + (((int64_t)b * a.Lr + lr) * Hq + h) * D;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int r = rbase + nb * 16 + rr;
-    qleaf[nb] = r < R ? a.leaf_list[loff + r / G] : -1;
-  }
-  typename O::reg q[NB][KS];
+    for (int ks = 0; ks < KS; ++ks) q[ks] = O::load(qp + frag_col<T>(ks, g4));
+  } else {
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int r = rbase + nb * 16 + rr;
-    if (qleaf[nb] >= 0) {
-      const int h = g * G + r % G;
-      const T *qp = static_cast<const T *>(a.q) + (((int64_t)qleaf[nb] * a.Lr + lr) * Hq + h) * D;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) q[nb][ks] = O::load(qp + frag_col<T>(ks, g4));
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) q[nb][ks] = O::zero();
-    }
+    for (int ks = 0; ks < KS; ++ks) q[ks] = O::zero();
   }
   UnitAddr ua;
   {
@@ -551,88 +612,92 @@ __device__ void decode_unit(const DecArgs &a, int item, int lr, int g, int rbase
   }
   // a credited slice layer keeps its logits: [slice][kv head][unit row][slot]
   float *zrow = nullptr;
+  const int zstride = (un.n_slots + 63) & ~63;
   for (int z = 0; KZ && z < a.zS; ++z)
     if (a.zlr[z] == lr) {
-      zrow = a.part + a.meta[4] +
-             (((int64_t)z * pl.Hkv + g) * a.meta[3] + a.item_rowbase[item]) * CHUNK;
+      zrow = a.rest + mt.z + (((int64_t)z * pl.Hkv + g) * mt.z_total + un.zbase) * 64 +
+             (int64_t)r * zstride;
       break;
     }
   F cur = fetch_kv<T, D, GSP>(ua, pg, s_begin, s_end, n_sub, 0, pl.P);
-  float m_run[NB], l_run[NB];
-  f32x4 o[NB][NC];
+  float m_run = -__builtin_inff(), l_run = 0.f;
+  // o holds the sums of up to kFlush slots, ot those before: a chunk of 1,024
+  // slots is summed to the accuracy of one of 256 (one level: 4.9e-7 from the
+  // 64-bit outputs on the 70B shape, against 4.1e-7)
+  constexpr int kFlush = 256 / (16 * GSP);
+  f32x4 o[NC], ot[NC];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    m_run[nb] = -__builtin_inff();
-    l_run[nb] = 0.f;
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) o[nb][cc] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int cc = 0; cc < NC; ++cc) o[cc] = ot[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
   // the logits of fragment gi are stored after fragment gi + 1's loads are
   // issued: a wave's loads and stores share one counter, so a wait for loads
   // issued after the stores would wait for the stores as well
-  float zs[GSP][NB][4];
+  float zs[GSP][4];
   auto store_z = [&](int gz) __attribute__((always_inline)) {
-    // lane (rr, g4) holds keys 4 g4 .. 4 g4 + 3 of each sub-page for row rr:
-    // zrow + r * CHUNK + 16 sub + key for query row r < R of the unit
+    // lane (rr, g4) holds keys 4 g4 .. 4 g4 + 3 of each sub-page for row rr
 #pragma unroll
-    for (int sp = 0; sp < GSP; ++sp) {
-      if (gz * GSP + sp >= n_sub) continue;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int r = rbase + nb * 16 + rr;
-        if (r < R)
-          *reinterpret_cast<float4 *>(zrow + (int64_t)r * CHUNK + 16 * (gz * GSP + sp) + 4 * g4) =
-              make_float4(zs[sp][nb][0], zs[sp][nb][1], zs[sp][nb][2], zs[sp][nb][3]);
-      }
-    }
+    for (int sp = 0; sp < GSP; ++sp)
+      if (gz * GSP + sp < n_sub && r < R)
+        *reinterpret_cast<float4 *>(zrow + 16 * (gz * GSP + sp) + 4 * g4) =
+            make_float4(zs[sp][0], zs[sp][1], zs[sp][2], zs[sp][3]);
   };
   for (int gi = 0; gi < n_grp; ++gi) {
     if (gi > 0) {
       cur = fetch_kv<T, D, GSP>(ua, pg, s_begin, s_end, n_sub, gi * GSP, pl.P);
       if (KZ && zrow) store_z(gi - 1);
     }
-    attend<T, D, NB, GSP>(cur, q, a.sl2, g4, m_run, l_run, o, KZ && zrow != nullptr, zs);
-  }
-  if (KZ && zrow && n_grp > 0) store_z(n_grp - 1);
-  // partial rows [m, l, o(0..D-1)] of this unit
-  const int64_t stride = D + 2;
-  const int64_t slab = ((int64_t)lr * pl.Hkv + g) * a.meta[3];
-  float *outp = a.part + (slab + a.item_rowbase[item]) * stride;
+    attend<T, D, GSP>(cur, q, a.sl2, g4, m_run, l_run, o, ot, KZ && zrow != nullptr, zs);
+    if (gi % kFlush == kFlush - 1) {
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const float l = across_rows(l_run[nb], [](float x, float y) { return x + y; });
-    const int row = rbase + nb * 16 + rr;
-    if (g4 == 0 && row < R) {
-      outp[row * stride] = m_run[nb];
-      outp[row * stride + 1] = l;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int orow = rbase + nb * 16 + 4 * g4 + e;
-      if (orow < R) {
-        float *op = outp + orow * stride + 2 + NC * rr;
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) op[cc] = o[nb][cc][e];
+      for (int cc = 0; cc < NC; ++cc) {
+        ot[cc] += o[cc];
+        o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
+    }
+  }
+#pragma unroll
+  for (int cc = 0; cc < NC; ++cc) o[cc] += ot[cc];
+  if (KZ && zrow && n_grp > 0) store_z(n_grp - 1);
+  // partial rows of this unit: (max, sum) pairs and outputs
+  const int64_t prow = ((int64_t)lr * pl.Hkv + g) * mt.rows + un.rowbase;
+  const float l = across_rows(l_run, [](float x, float y) { return x + y; });
+  if (g4 == 0 && r < R)
+    reinterpret_cast<float2 *>(a.rest + mt.ml)[prow + r] = make_float2(m_run, l);
+  float *outp = a.rest + mt.part + prow * D + NC * rr;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int orow = rbase + 4 * g4 + e;
+    if (orow < R) {
+#pragma unroll
+      for (int cc = 0; cc < NC; cc += 4)
+        *reinterpret_cast<float4 *>(outp + (int64_t)orow * D + cc) =
+            make_float4(o[cc][e], o[cc + 1][e], o[cc + 2][e], o[cc + 3][e]);
     }
   }
 }
 
-template <class T, int D, int NB, bool KZ>
-__global__ __launch_bounds__(256) void decode_attn(DecArgs a, int cls) {
-  if (status_failed(a.status)) return;
-  const int n_items = a.meta[cls];
+// Waves take (unit, layer, kv head) in turn: chunk by chunk, over its planes
+// (whose rows of a page lie side by side), the chunk's row blocks innermost.
+// Every other workgroup takes them from the end: the shared blocks near the
+// root (many rows, so bound by the matrix cores) come first in the plan's
+// order, and run beside the leaves' (bound by HBM).
+template <class T, int D, bool KZ>
+__global__ __launch_bounds__(256) void decode_attn(DecArgs a) {
   const int planes = a.Lr * a.pl.Hkv;
-  const int64_t total = (int64_t)n_items * planes;
   // the wave index is wave-uniform: keep the unit's bookkeeping scalar
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int64_t w = (int64_t)blockIdx.x * 4 + wave; w < total; w += (int64_t)gridDim.x * 4) {
-    const int item = a.cls_items[(int64_t)cls * a.max_items + w / planes];
-    const int rem = (int)(w % planes);
-    const int lr = rem / a.pl.Hkv;
-    const int g = rem % a.pl.Hkv;
-    const int R = a.node_nl[a.item_node[item]] * a.pl.G;
-    for (int rbase = 0; rbase < R; rbase += 16 * NB) decode_unit<T, D, NB, KZ>(a, item, lr, g, rbase);
+  // (loaded together with the status word)
+  const Meta mt = *a.meta;
+  if (status_failed(a.status)) return;
+  const int64_t total = (int64_t)mt.n_units * planes;
+  const int64_t nblk = (total + 3) / 4;
+  for (int64_t vb = blockIdx.x; vb < nblk; vb += gridDim.x) {
+    const int64_t w = ((vb & 1) ? nblk - 1 - vb / 2 : vb / 2) * 4 + wave;
+    if (w >= total) continue;
+    const Unit un = units_of(a)[w / planes];
+    const int p = (int)(w - (int64_t)un.first * planes);
+    const int nbr = (un.R + 15) / 16;
+    const int plane = p / nbr;
+    decode_unit<T, D, KZ>(a, mt, un, plane / a.pl.Hkv, plane % a.pl.Hkv, 16 * (p % nbr));
   }
 }
 
@@ -642,17 +707,16 @@ __global__ __launch_bounds__(256) void decode_attn(DecArgs a, int cls) {
 // so the result does not depend on scheduling.  Workgroups blk of nblk take
 // the rows in turn.
 template <int D>
-__device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_dtype,
-                                           float *lse_out, int blk, int nblk) {
+__device__ __forceinline__ void merge_rows(const DecArgs &a, const Meta &mt, void *out,
+                                           int out_dtype, float *lse_out, int blk, int nblk) {
   constexpr int EPL = D / 64;  // output columns per lane
-  constexpr int U = 4;         // partial rows loaded together
+  constexpr int U = 8;         // partial rows loaded together
   constexpr int kPreO = 8;     // partial rows read ahead of the max
   const Pool &pl = a.pl;
   const int lane = lane_id();
   const int G = pl.G;
   const int Hq = pl.Hkv * G;
   const int64_t total = (int64_t)a.n_leaves * a.Lr * Hq;
-  const int64_t stride = D + 2;
   const int wpb = blockDim.x / kWave;
   for (int64_t w = (int64_t)blk * wpb + threadIdx.x / kWave; w < total;
        w += (int64_t)nblk * wpb) {
@@ -662,32 +726,51 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_
     const int h = rem % Hq;
     const int g = h / G;
     const int hl = h % G;
-    const float *base = a.part + (((int64_t)lr * pl.Hkv + g) * a.meta[3] + hl) * stride;
-    const int32_t *lp = a.leaf_part + (int64_t)b * a.max_parts;
+    const int64_t row0 = ((int64_t)lr * pl.Hkv + g) * mt.rows + hl;
+    const float2 *ml = reinterpret_cast<const float2 *>(a.rest + mt.ml) + row0;
+    const float *base = a.rest + mt.part + row0 * D + EPL * lane;
     const int np = a.leaf_np[b];
+    const int32_t *lp = reinterpret_cast<const int32_t *>(a.rest) + mt.parts +
+                        (int64_t)b * mt.max_np;
     // global max over the chain's partials; the first kWave partials'
-    // offsets, maxima and sums stay in registers for the second pass (longer
+    // rows, maxima and sums stay in registers for the second pass (longer
     // chains reload the rest there)
-    int64_t off0 = 0;
+    int off0 = 0;
     float m0 = -__builtin_inff(), l0 = 0.f;
     if (lane < np) {
-      off0 = (int64_t)lp[lane] * stride;
-      m0 = base[off0];
-      l0 = base[off0 + 1];
+      off0 = lp[lane];
+      const float2 v = ml[off0];
+      m0 = v.x;
+      l0 = v.y;
     }
     // the output rows of the first kPreO partials are read together with
     // their (max, sum), before the max is known
     float xv0[kPreO][EPL];
+    auto load_row = [&](float (&x)[EPL], int row) __attribute__((always_inline)) {
+      const float *p = base + (int64_t)row * D;
+      if constexpr (EPL == 2) {
+        const float2 v = *reinterpret_cast<const float2 *>(p);
+        x[0] = v.x;
+        x[1] = v.y;
+      } else {
+        x[0] = p[0];
+      }
+    };
+    static_assert(EPL == 1 || EPL == 2, "head_dim 64 or 128");
 #pragma unroll
     for (int u = 0; u < kPreO; ++u) {
-      const int64_t oj = lane_value(off0, u < np ? u : 0);
+      const int oj = lane_value(off0, u < np ? u : 0);
+      if (u < np) {
+        load_row(xv0[u], oj);
+      } else {
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) xv0[u][e] = u < np ? base[oj + 2 + 64 * e + lane] : 0.f;
+        for (int e = 0; e < EPL; ++e) xv0[u][e] = 0.f;
+      }
     }
     float M = m0;
     for (int k0 = kWave; k0 < np; k0 += kWave) {
       const int k = k0 + lane;
-      const float m = k < np ? base[(int64_t)lp[k] * stride] : -__builtin_inff();
+      const float m = k < np ? ml[lp[k]].x : -__builtin_inff();
       M = fmaxf(M, m);
     }
     M = wave_allreduce(M, [](float x, float y) { return fmaxf(x, y); });
@@ -697,16 +780,17 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_
     if (M > -__builtin_inff()) {
       for (int k0 = 0; k0 < np; k0 += kWave) {
         const int k = k0 + lane;
-        int64_t off = 0;
+        int off = 0;
         float f = 0.f, lk = 0.f;
         if (k < np) {
           float m = m0;
           off = off0;
           lk = l0;
           if (k0 > 0) {
-            off = (int64_t)lp[k] * stride;
-            m = base[off];
-            lk = base[off + 1];
+            off = lp[k];
+            const float2 v = ml[off];
+            m = v.x;
+            lk = v.y;
           }
           f = m > -__builtin_inff() ? __builtin_amdgcn_exp2f(m - M) : 0.f;
         }
@@ -727,10 +811,8 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const int j = min(j0 + u, nk - 1);
-            const int64_t oj = lane_value(off, j);
             fj[u] = j0 + u < nk ? lane_value(f, j) : 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) xv[u][e] = base[oj + 2 + 64 * e + lane];
+            load_row(xv[u], lane_value(off, j));
           }
 #pragma unroll
           for (int u = 0; u < U; ++u)
@@ -739,16 +821,16 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_
         }
       }
     }
-    const int64_t oi = (((int64_t)b * a.Lr + lr) * Hq + h) * D;
+    const int64_t oi = (((int64_t)b * a.Lr + lr) * Hq + h) * D + EPL * lane;
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     if (out_dtype == ARBOR_BF16) {
       __bf16 *op = static_cast<__bf16 *>(out) + oi;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) op[64 * e + lane] = (__bf16)(ov[e] * inv);
+      for (int e = 0; e < EPL; ++e) op[e] = (__bf16)(ov[e] * inv);
     } else {
       float *op = static_cast<float *>(out) + oi;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) op[64 * e + lane] = ov[e] * inv;
+      for (int e = 0; e < EPL; ++e) op[e] = ov[e] * inv;
     }
     if (lane == 0) {
       const float l2 = L > 0.f ? M + __log2f(L) : -__builtin_inff();
@@ -768,103 +850,113 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, void *out, int out_
 // log2(sum_k l_k exp2(m_k - M)) over the (max m_k, sum l_k) of the partials of
 // its leaf's chain, is formed here from those partials, so the credit does not
 // wait for the merge and runs beside it in the same launch.
-// One workgroup of kCreditWaves waves per quarter (64 slots) of a unit, one
-// lane per slot.  The unit's (row, distinct slice layer, kv head) triples, in
-// the order (r * U + z) * Hkv + g, are staged in LDS up to kCreditTile at a
-// time (one thread per triple): each triple's lse2 and its weight, the layer's
-// multiplicity, negated when the row is the node's own leaf's.  Wave v takes
+// One workgroup of kCreditWaves waves per 64 slots of a chunk, one lane per
+// slot.  The unit's (row, distinct slice layer, kv head) triples, in
+// the order (z * Hkv + g) * R + r, are staged in LDS up to kCreditTile at a
+// time: each triple's lse2 and its weight, the layer's multiplicity, in one of
+// two tables, for the rows of other leaves and for the node's own.  Rows are
+// innermost because the (max, sum) pairs of a partial's rows lie side by side,
+// so that the lanes of a load share cache lines (with the kv heads innermost
+// each lane read a line of its own: 16.8 us for the launch against 13.3, one
+// layer under 16 leaves).  Several threads share a triple's partials where there are fewer
+// triples than threads.  Wave v takes
 // the triples v, v + kCreditWaves, ... in order, kCreditBatch logit loads at a
 // time, the next batch in flight while one is summed; the first batch is
-// issued before the tables are built (a triple's logit row, (z * Hkv + g) *
-// rows + r, is known without them), and for up to kCreditWaves * kCreditBatch
-// triples it is the only one.  The rows of other leaves and the node's own
-// rows are kept in two sums; the waves' sums are added in wave order, so each
-// token's sum has one owner and a fixed order.  Workgroup 0 also adds the row
-// counts to rows_seen (integer atomics: order-free).
+// issued before the tables are built, and for up to kCreditWaves *
+// kCreditBatch triples it is the only one.  A batch's table entries come with
+// one LDS read per table (lane u holds entry u).  The two
+// sums of a wave are added in wave order, so each token's sum has one owner
+// and a fixed order.  Workgroup 0 also adds the row counts to rows_seen
+// (integer atomics: order-free).
 constexpr int kCreditWaves = 16;
 constexpr int kCreditThreads = kCreditWaves * kWave;
 constexpr int kCreditTile = 1024;
 constexpr int kCreditBatch = 16;
-constexpr int kQuarters = CHUNK / kWave;
-constexpr int kLsePar = 8;            // partials of a chain loaded together
-static_assert(CHUNK % kWave == 0, "a unit is a whole number of 64-slot quarters");
+constexpr int kLsePar = 12;           // partials of a chain that a thread loads together
+constexpr int kLseThreads = 32;       // most threads of one triple's LSE
+static_assert(kMinChunk % kWave == 0, "a chunk is a whole number of 64-slot pieces");
 static_assert(kCreditTile % (kCreditWaves * kCreditBatch) == 0, "batches do not straddle tiles");
+static_assert(kCreditTile == kCreditThreads, "one thread per triple of a full tile");
 
-// a triple as (row r, zg = z * Hkv + g), stepped without divisions
+// a triple as (row r, zg = z * Hkv + g); dr, dzg: the step of kCreditWaves
 struct Triple {
-  int r, zg;
-  __device__ __forceinline__ void step(int k, int per) {
-    zg += k;
-    while (zg >= per) {
-      zg -= per;
-      ++r;
+  int r, zg, dr, dzg;
+  __device__ __forceinline__ Triple(int e, int R)
+      : r(e % R), zg(e / R), dr(kCreditWaves % R), dzg(kCreditWaves / R) {}
+  __device__ __forceinline__ void step(int R) {
+    r += dr;
+    zg += dzg;
+    if (r >= R) {
+      r -= R;
+      ++zg;
     }
   }
 };
 
 // logits of the batch of triples it, it + kCreditWaves, ... (it is left at
 // the next batch's first triple): zb points at the unit's first logit row and
-// the lane's slot; triples past the unit's R rows are not read
+// the lane's slot; triples past the last one are not read
 __device__ __forceinline__ void credit_load(float (&zv)[kCreditBatch], const float *zb, Triple &it,
-                                            int R, int per, int64_t rows_total) {
+                                            int R, int per, int64_t z_slab, int zstride) {
 #pragma unroll
   for (int u = 0; u < kCreditBatch; ++u) {
-    zv[u] = it.r < R ? zb[((int64_t)it.zg * rows_total + it.r) * CHUNK] : 0.f;
-    it.step(kCreditWaves, per);
+    zv[u] = it.zg < per ? zb[it.zg * z_slab + (int64_t)it.r * zstride] : 0.f;
+    it.step(R);
   }
 }
 
-// log2 LSE of query row (leaf b, layer lr, head g * G + hl) over the partials
-// of b's chain, with the maximum taken kLsePar partials at a time
-template <int D>
-__device__ __forceinline__ float chain_lse2(const DecArgs &a, int b, int lr, int g, int hl) {
-  const int64_t stride = D + 2;
-  const float *base = a.part + (((int64_t)lr * a.pl.Hkv + g) * a.meta[3] + hl) * stride;
-  const int32_t *lp = a.leaf_part + (int64_t)b * a.max_parts;
+// (max, sum) of two sets of partials
+__device__ __forceinline__ float2 ml_merge(float2 x, float2 y) {
+  const float m = fmaxf(x.x, y.x);
+  if (m == -__builtin_inff()) return make_float2(m, 0.f);
+  const float sx = x.x > -__builtin_inff() ? x.y * __builtin_amdgcn_exp2f(x.x - m) : 0.f;
+  const float sy = y.x > -__builtin_inff() ? y.y * __builtin_amdgcn_exp2f(y.x - m) : 0.f;
+  return make_float2(m, sx + sy);
+}
+
+// (max, sum) of query row (leaf b, layer lr, head g * G + hl) over the partials
+// j, j + tpt, ... of b's chain, kLsePar of them loaded together
+__device__ __forceinline__ float2 chain_ml(const DecArgs &a, const Meta &mt, int b, int lr, int g,
+                                           int hl, int j, int tpt) {
+  const float2 *ml = reinterpret_cast<const float2 *>(a.rest + mt.ml) +
+                     ((int64_t)lr * a.pl.Hkv + g) * mt.rows + hl;
   const int np = a.leaf_np[b];
-  float M = -__builtin_inff(), L = 0.f;
-  for (int k0 = 0; k0 < np; k0 += kLsePar) {
-    float m[kLsePar], l[kLsePar];
+  const int32_t *lp = reinterpret_cast<const int32_t *>(a.rest) + mt.parts +
+                      (int64_t)b * mt.max_np;
+  float2 r = make_float2(-__builtin_inff(), 0.f);
+  for (int k0 = j; k0 < np; k0 += kLsePar * tpt) {
+    int row[kLsePar];
+    float2 v[kLsePar];
 #pragma unroll
-    for (int u = 0; u < kLsePar; ++u) {
-      const int64_t off = k0 + u < np ? (int64_t)lp[k0 + u] * stride : 0;
-      m[u] = k0 + u < np ? base[off] : -__builtin_inff();
-      l[u] = k0 + u < np ? base[off + 1] : 0.f;
-    }
-    float Mn = M;
-#pragma unroll
-    for (int u = 0; u < kLsePar; ++u) Mn = fmaxf(Mn, m[u]);
-    if (Mn == -__builtin_inff()) continue;
-    L = M > -__builtin_inff() ? L * __builtin_amdgcn_exp2f(M - Mn) : 0.f;
+    for (int u = 0; u < kLsePar; ++u) row[u] = k0 + u * tpt < np ? lp[k0 + u * tpt] : -1;
 #pragma unroll
     for (int u = 0; u < kLsePar; ++u)
-      L += m[u] > -__builtin_inff() ? l[u] * __builtin_amdgcn_exp2f(m[u] - Mn) : 0.f;
-    M = Mn;
+      v[u] = row[u] >= 0 ? ml[row[u]] : make_float2(-__builtin_inff(), 0.f);
+    float m = r.x;
+#pragma unroll
+    for (int u = 0; u < kLsePar; ++u) m = fmaxf(m, v[u].x);
+    if (m == -__builtin_inff()) continue;
+    float s = r.x > -__builtin_inff() ? r.y * __builtin_amdgcn_exp2f(r.x - m) : 0.f;
+#pragma unroll
+    for (int u = 0; u < kLsePar; ++u)
+      s += v[u].x > -__builtin_inff() ? v[u].y * __builtin_amdgcn_exp2f(v[u].x - m) : 0.f;
+    r = make_float2(m, s);
   }
-  return L > 0.f ? M + __log2f(L) : -__builtin_inff();
+  return r;
 }
 
-// the credit of the quarters blk, blk + nblk, ... of the plan's units
-template <int D>
-__device__ __forceinline__ void credit_quarters(const DecArgs &a, const CreditArgs &cr, int blk,
-                                                int nblk) {
+// the credit of the 64-slot pieces blk, blk + nblk, ... of the plan's chunks
+__device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
+                                              const CreditArgs &cr, int blk, int nblk) {
   __shared__ float s_oth[kCreditWaves][kWave], s_own[kCreditWaves][kWave];
-  __shared__ float s_l2[kCreditTile], s_w[kCreditTile];
+  __shared__ float s_l2[kCreditTile], s_wo[kCreditTile], s_wn[kCreditTile];
+  __shared__ float2 s_ml[kCreditThreads];
   const Tree &t = a.t;
   const Pool &pl = a.pl;
   const int G = pl.G, Hkv = pl.Hkv;
   const int Hq = Hkv * G;
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // the launch covers at most max_items units, so the first unit's fields can
-  // be read before the plan's unit count is known
-  const int n_items = a.meta[0] + a.meta[1] + a.meta[2];
-  const int64_t rows_total = a.meta[3];
-  const int item0 = blk / kQuarters;
-  const int node0 = a.item_node[item0];
-  const int chunk0 = a.item_chunk[item0];
-  const int rb0 = a.item_rowbase[item0];
-  if (status_failed(a.status)) return;
   if (blk == 0) {
     const unsigned long long per = (unsigned long long)cr.S * Hq;
     for (int e = threadIdx.x; e < a.n_leaves * MAXD; e += blockDim.x) {
@@ -876,34 +968,39 @@ __device__ __forceinline__ void credit_quarters(const DecArgs &a, const CreditAr
                   per);
     }
   }
-  const float *z0 = a.part + a.meta[4];
+  const float *z0 = a.rest + mt.z;
+  const int64_t z_slab = (int64_t)mt.z_total * 64;
   const int per = cr.U * Hkv;
+  const int pieces = mt.chunk / kWave;
   constexpr int kLast = kCreditWaves - 1;
-  for (int w = blk; w < n_items * kQuarters; w += nblk) {
-    const int item = w / kQuarters;
-    const bool first = w == blk;
-    const int node = first ? node0 : a.item_node[item];
-    const int k0 = (first ? chunk0 : a.item_chunk[item]) * CHUNK;
-    const int rb = first ? rb0 : a.item_rowbase[item];
-    const int c = t.n_kept[node];
-    const int s0 = k0 + (w % kQuarters) * kWave;
-    if (s0 >= c) continue;                    // uniform over the workgroup
-    const int slot = s0 + lane;
-    const bool key_ok = slot < c;
-    const int R = a.node_nl[node] * G;
-    const int loff = a.node_leaf_off[node];
+  for (int64_t w = blk; w < (int64_t)mt.n_units * pieces; w += nblk) {
+    const int u = (int)(w / pieces);
+    const Unit un = units_of(a)[u];
+    const int piece = (int)(w - (int64_t)u * pieces) * kWave;
+    // (uniform over the workgroup) a chunk is credited once, by its first unit
+    if (un.first != u || piece >= un.n_slots) continue;
+    const int node = un.node;
+    const int slot = un.s_begin + piece + lane;
+    const bool key_ok = piece + lane < un.n_slots;
+    const int R = un.R;
+    const int loff = un.loff;
     const int n = R * per;
+    const int zstride = (un.n_slots + 63) & ~63;
+    // threads per triple: as many as there are for the unit's triples, but no
+    // more than the longest list of partials
+    int tpt = 1;
+    while (2 * tpt <= kLseThreads && 2 * tpt * n <= kCreditThreads && tpt < mt.max_np) tpt *= 2;
+    const int tri = min(n, kCreditTile);
+    const int tj = (int)threadIdx.x / tri, ti = (int)threadIdx.x - tj * tri;
     // the leaf of this thread's first table entry, read before the logits so
     // that waiting for it does not wait for them
-    const int b_first = (int)threadIdx.x < min(n, kCreditTile)
-                            ? a.leaf_list[loff + (int)threadIdx.x / per / G] : 0;
-    // logit rows hold CHUNK slots each, so the lane's slot is in bounds for
+    const int b_first = tj < tpt ? a.leaf_list[loff + ti % R / G] : 0;
+    // logit rows hold whole 64-slot pieces, so the lane's slot is in bounds for
     // every lane; lanes past the node's count are masked after the load
-    const float *zb = z0 + (int64_t)rb * CHUNK + (slot - k0);
+    const float *zb = z0 + (int64_t)un.zbase * 64 + piece + lane;
     float cur[kCreditBatch];
-    Triple it{0, 0};
-    it.step(wv, per);
-    credit_load(cur, zb, it, R, per, rows_total);
+    Triple it(wv, R);
+    credit_load(cur, zb, it, R, per, z_slab, zstride);
     // the last wave fetches the lane's token and its A entry meanwhile; each
     // token has one owner, so A is read before the sums
     int64_t tok = 0;
@@ -922,29 +1019,40 @@ __device__ __forceinline__ void credit_quarters(const DecArgs &a, const CreditAr
     int e0 = wv;
     for (int t0 = 0; t0 < n; t0 += kCreditTile) {
       const int nt = min(kCreditTile, n - t0);
-      for (int i = threadIdx.x; i < nt; i += blockDim.x) {
-        const int e = t0 + i;
-        const int r = e / per, zg = e % per;
-        const int z = zg / Hkv, g = zg % Hkv;
-        const int b = t0 == 0 && i == (int)threadIdx.x ? b_first : a.leaf_list[loff + r / G];
-        s_l2[i] = chain_lse2<D>(a, b, cr.slice[z], g, r % G);
+      const int e = t0 + ti;
+      const int r = e % R, zg = e / R;
+      const int z = zg / Hkv, g = zg - z * Hkv;
+      const bool mine = tj < tpt && ti < nt;
+      int b = 0;
+      if (mine) {
+        b = t0 == 0 ? b_first : a.leaf_list[loff + r / G];
+        s_ml[tj * tri + ti] = chain_ml(a, mt, b, cr.slice[z], g, r % G, tj, tpt);
+      }
+      __syncthreads();
+      if (mine && tj == 0) {
+        float2 v = s_ml[ti];
+        for (int j = 1; j < tpt; ++j) v = ml_merge(v, s_ml[j * tri + ti]);
         const float m = (float)cr.mult[z];
-        s_w[i] = a.leaves[b] == node ? -m : m;
+        const bool own_row = a.leaves[b] == node;
+        s_l2[ti] = v.y > 0.f ? v.x + __log2f(v.y) : -__builtin_inff();
+        s_wo[ti] = own_row ? 0.f : m;
+        s_wn[ti] = own_row ? m : 0.f;
+      } else if ((int)threadIdx.x >= nt) {
+        s_l2[threadIdx.x] = s_wo[threadIdx.x] = s_wn[threadIdx.x] = 0.f;
       }
       __syncthreads();
       for (; e0 < t0 + nt; e0 += kCreditWaves * kCreditBatch) {
         float nxt[kCreditBatch];
         const bool more = e0 + kCreditWaves * kCreditBatch < n;
-        if (more) credit_load(nxt, zb, it, R, per, rows_total);
+        if (more) credit_load(nxt, zb, it, R, per, z_slab, zstride);
+        static_assert(kCreditBatch == 16, "one row of lanes per batch");
+        const int i = e0 - t0 + kCreditWaves * (lane & (kCreditBatch - 1));
+        const float l2 = s_l2[i], wo = s_wo[i], wn = s_wn[i];
 #pragma unroll
         for (int u = 0; u < kCreditBatch; ++u) {
-          const int i = e0 + kCreditWaves * u - t0;
-          if (i < nt) {
-            const float p = key_ok ? __builtin_amdgcn_exp2f(cur[u] - s_l2[i]) : 0.f;
-            const float wt = s_w[i];
-            if (wt < 0.f) own += -wt * p;
-            else oth += wt * p;
-          }
+          const float p = key_ok ? __builtin_amdgcn_exp2f(cur[u] - lane_value(l2, u)) : 0.f;
+          oth = __builtin_fmaf(lane_value(wo, u), p, oth);
+          own = __builtin_fmaf(lane_value(wn, u), p, own);
         }
         if (more) {
 #pragma unroll
@@ -966,15 +1074,17 @@ __device__ __forceinline__ void credit_quarters(const DecArgs &a, const CreditAr
       }
       cr.A[tok] = a_old + tot;
     }
-    __syncthreads();                          // the sums are reused by the next quarter
+    __syncthreads();                          // the sums are reused by the next piece
   }
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge(DecArgs a, void *out, int out_dtype,
                                                     float *lse_out) {
+  // (loaded together with the status word)
+  const Meta mt = *a.meta;
   if (status_failed(a.status)) return;
-  merge_rows<D>(a, out, out_dtype, lse_out, blockIdx.x, gridDim.x);
+  merge_rows<D>(a, mt, out, out_dtype, lse_out, blockIdx.x, gridDim.x);
 }
 
 // scored calls: the first credit_blocks workgroups credit (their chain of
@@ -984,12 +1094,14 @@ __global__ __launch_bounds__(kCreditThreads) void decode_merge_credit(DecArgs a,
                                                                       void *out, int out_dtype,
                                                                       float *lse_out,
                                                                       int credit_blocks) {
+  // (loaded together with the status word)
+  const Meta mt = *a.meta;
+  if (status_failed(a.status)) return;
   if ((int)blockIdx.x < credit_blocks) {
-    credit_quarters<D>(a, cr, blockIdx.x, credit_blocks);
+    credit_pieces(a, mt, cr, blockIdx.x, credit_blocks);
     return;
   }
-  if (status_failed(a.status)) return;
-  merge_rows<D>(a, out, out_dtype, lse_out, blockIdx.x - credit_blocks,
+  merge_rows<D>(a, mt, out, out_dtype, lse_out, blockIdx.x - credit_blocks,
                 gridDim.x - credit_blocks);
 }
 
@@ -997,23 +1109,11 @@ template <class T, int D>
 void launch_decode_kernels(const arbor_geom_t *geom, const DecArgs &a, void *out, int out_dtype,
                            float *lse_out, const CreditArgs *cr, hipStream_t stream) {
   const int grid = 2048;
-  // rows of a work unit are at most n_leaves * G: only the row classes that
-  // can occur are launched
-  const int max_rows = a.n_leaves * a.pl.G;
   timing_begin(geom, ARBOR_KERNEL_DECODE_ATTN, stream);
-  if (cr) {
-    hipLaunchKernelGGL((decode_attn<T, D, 1, true>), dim3(grid), dim3(256), 0, stream, a, 0);
-    if (max_rows > 16)
-      hipLaunchKernelGGL((decode_attn<T, D, 2, true>), dim3(grid / 2), dim3(256), 0, stream, a, 1);
-    if (max_rows > 32)
-      hipLaunchKernelGGL((decode_attn<T, D, 4, true>), dim3(grid / 4), dim3(256), 0, stream, a, 2);
-  } else {
-    hipLaunchKernelGGL((decode_attn<T, D, 1, false>), dim3(grid), dim3(256), 0, stream, a, 0);
-    if (max_rows > 16)
-      hipLaunchKernelGGL((decode_attn<T, D, 2, false>), dim3(grid / 2), dim3(256), 0, stream, a, 1);
-    if (max_rows > 32)
-      hipLaunchKernelGGL((decode_attn<T, D, 4, false>), dim3(grid / 4), dim3(256), 0, stream, a, 2);
-  }
+  if (cr)
+    hipLaunchKernelGGL((decode_attn<T, D, true>), dim3(grid), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_attn<T, D, false>), dim3(grid), dim3(256), 0, stream, a);
   timing_end(geom, ARBOR_KERNEL_DECODE_ATTN, stream);
   const int64_t mw = (int64_t)a.n_leaves * a.Lr * a.pl.Hkv * a.pl.G;
   if (!cr) {
@@ -1022,10 +1122,10 @@ void launch_decode_kernels(const arbor_geom_t *geom, const DecArgs &a, void *out
                        lse_out);
     return;
   }
-  // credit workgroups stride over the quarters of the plan's units (at most
-  // half the chip's wave slots, so that the merge workgroups start beside
+  // credit workgroups stride over the 64-slot pieces of the plan's chunks (at
+  // most half the chip's wave slots, so that the merge workgroups start beside
   // them); merge workgroups hold kCreditWaves rows each
-  const int cgrid = std::min(a.max_items * kQuarters, 256);
+  const int cgrid = 256;
   const int64_t mb = (mw + kCreditWaves - 1) / kCreditWaves;
   const int mgrid = (int)(mb < 2048 ? mb : 2048);
   timing_begin(geom, ARBOR_KERNEL_DECODE_CREDIT, stream);
@@ -1036,27 +1136,27 @@ void launch_decode_kernels(const arbor_geom_t *geom, const DecArgs &a, void *out
 
 }  // namespace
 
-static size_t decode_max_items(const arbor_sizes_t *sz) {
-  return (size_t)sz->num_nodes + (size_t)(sz->num_tokens / CHUNK) + 1;
-}
-
-// partials along one chain: at most one ragged chunk per chain node
-static size_t decode_max_parts(const arbor_sizes_t *sz) {
-  return (size_t)(sz->num_tokens / CHUNK) + MAXD + 1;
-}
-
 size_t decode_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
-  const size_t V = (size_t)sz->num_nodes;
   const size_t nl = (size_t)(sz->max_leaves > 0 ? sz->max_leaves : 1);
-  const size_t items = decode_max_items(sz);
-  const size_t per_leaf = (size_t)(sz->max_context / CHUNK) + MAXD + 1;
-  const size_t rows = nl * per_leaf * g->q_per_kv;
-  size_t b = 19 * 256;
-  b += 3 * items * 4 + 3 * items * 4 + V * 4 * 4 + nl * MAXD * 4 * 3 + nl * 4 + nl * MAXD * 4;
-  b += nl * 4 + nl * decode_max_parts(sz) * 4;
-  b += rows * (size_t)sz->max_layers * g->num_kv_heads * (g->head_dim + 2) * 4;
+  const size_t planes = (size_t)sz->max_layers * g->num_kv_heads;
+  const size_t ctx = (size_t)sz->max_context, G = (size_t)g->q_per_kv;
+  // chunks along one chain (at most one ragged chunk per chain node), at the
+  // smallest chunk size; rows and units over all leaves
+  const size_t per_leaf = ctx / kMinChunk + MAXD + 1;
+  const size_t rows = nl * per_leaf * G;
+  size_t b = 16 * 256;
+  b += nl * (MAXD * (4 * (2 + kPlanEnts) + 8) + 12);
+  b += (nl * per_leaf + rows / 16 + nl) * sizeof(Unit) + nl * per_leaf * 4;
+  // partial rows over all planes: a chunk size below the largest is taken only
+  // while the next larger one gives fewer than kMinUnits units (16 rows at
+  // most each, and at most two chunks for one)
+  const size_t least = nl * (ctx / kMaxChunk + MAXD + 1) * G * planes;
+  const size_t most = std::min(rows * planes, (size_t)kMinUnits * 32);
+  b += std::max(least, most) * (g->head_dim + 2) * 4;
   // logits of the credited slice layers (scored decode)
-  b += rows * (size_t)(sz->n_slice > 0 ? sz->n_slice : 0) * g->num_kv_heads * CHUNK * 4 + 16;
+  b += nl * G * (ctx + 64 * (MAXD + 1)) * (size_t)(sz->n_slice > 0 ? sz->n_slice : 0) *
+           g->num_kv_heads * 4 +
+       64;
   return b;
 }
 
@@ -1068,12 +1168,6 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   Tree t = make_tree(tree);
   Pool pl = make_pool(geom, pool);
   if (t.V <= 0 || n_leaves <= 0 || layer_end <= layer_begin) return ARBOR_OK;
-  arbor_sizes_t sz{};
-  sz.num_nodes = t.V;
-  sz.num_tokens = t.N;
-  sz.max_context = t.N;
-  sz.max_leaves = n_leaves;
-  const int max_items = (int)decode_max_items(&sz);
   DecArgs a;
   a.t = t;
   a.pl = pl;
@@ -1084,25 +1178,21 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   a.q = q;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)geom->head_dim);
   a.sl2 = scale * kLog2e;
-  a.max_items = max_items;
   a.status = status;
+  const bool small = t.V <= kPlanLds, few = n_leaves <= kPlanLeaves;
+  const size_t ne = (size_t)n_leaves * MAXD;
   Carve cv(workspace, workspace_bytes);
-  int32_t *meta = cv.take<int32_t>(8);
-  int32_t *cls_items = cv.take<int32_t>((size_t)3 * max_items);
-  int32_t *item_node = cv.take<int32_t>(max_items);
-  int32_t *item_chunk = cv.take<int32_t>(max_items);
-  int32_t *item_rowbase = cv.take<int32_t>(max_items);
-  int32_t *node_nl = cv.take<int32_t>(t.V);
-  int32_t *node_leaf_off = cv.take<int32_t>(t.V);
-  int32_t *node_item0 = cv.take<int32_t>(t.V);
-  int32_t *node_rowbase = cv.take<int32_t>(t.V);
-  int32_t *leaf_list = cv.take<int32_t>((size_t)n_leaves * MAXD);
-  int32_t *lanc = cv.take<int32_t>((size_t)n_leaves * MAXD);
-  int32_t *ldepth = cv.take<int32_t>(n_leaves);
-  int32_t *lrank = cv.take<int32_t>((size_t)n_leaves * MAXD);
-  const int max_parts = (int)decode_max_parts(&sz);
-  int32_t *leaf_np = cv.take<int32_t>(n_leaves);
-  int32_t *leaf_part = cv.take<int32_t>((size_t)n_leaves * max_parts);
+  a.meta = cv.take<Meta>(1);
+  a.leaf_list = cv.take<int32_t>(ne);
+  a.lanc = cv.take<int32_t>(ne);
+  a.ldepth = cv.take<int32_t>(n_leaves);
+  a.leaf_np = cv.take<int32_t>(n_leaves);
+  PlanEnt ent{};
+  if (!few) {
+    int32_t **f[kPlanEnts] = {&ent.up, &ent.kept, &ent.rbase, &ent.loff, &ent.np, &ent.u0, &ent.z0};
+    for (int e = 0; e < kPlanEnts; ++e) *f[e] = cv.take<int32_t>(ne);
+    ent.place = cv.take<uint64_t>(ne);
+  }
   if (!cv.ok) return ARBOR_EWORKSPACE;
   CreditArgs cr{};
   if (credit) {
@@ -1120,33 +1210,14 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   }
   a.zS = credit ? cr.U : 0;
   for (int e = 0; e < 8; ++e) a.zlr[e] = credit && e < cr.U ? cr.slice[e] : -1;
-  a.meta = meta;
-  a.cls_items = cls_items;
-  a.item_node = item_node;
-  a.item_chunk = item_chunk;
-  a.item_rowbase = item_rowbase;
-  a.node_nl = node_nl;
-  a.node_leaf_off = node_leaf_off;
-  a.leaf_list = leaf_list;
-  a.node_item0 = node_item0;
-  a.node_rowbase = node_rowbase;
-  a.lanc = lanc;
-  a.ldepth = ldepth;
-  a.lrank = lrank;
-  a.leaf_np = leaf_np;
-  a.leaf_part = leaf_part;
-  a.max_parts = max_parts;
-  a.part = reinterpret_cast<float *>(cv.rest());
-  a.part_cap = (int64_t)(cv.remaining() / 4);
-  // one thread per node, and one wave per leaf for the per-leaf scans: a
+  a.rest = reinterpret_cast<float *>(cv.rest());
+  a.rest_cap = (int64_t)(cv.remaining() / 4);
+  // one thread per node (whose parent links go to LDS) and per chain entry: a
   // small tree takes a smaller workgroup, whose barriers are cheaper
-  const int64_t plan_need = std::max<int64_t>(t.V, (int64_t)n_leaves * MAXD);
+  const int64_t plan_need = std::max<int64_t>(small ? t.V : 0, (int64_t)n_leaves * 8);
   const int plan_threads = (int)std::min<int64_t>(1024, (plan_need + kWave - 1) / kWave * kWave);
-#define ARBOR_PLAN_LAUNCH(S, F)                                                                \
-  hipLaunchKernelGGL((decode_plan<S, F>), dim3(1), dim3(plan_threads), 0, stream, a, meta,       \
-                     cls_items, item_node, item_chunk, item_rowbase, node_nl, node_leaf_off,      \
-                     leaf_list, node_item0, node_rowbase, lanc, ldepth, lrank, leaf_np, leaf_part)
-  const bool small = t.V <= kPlanLds, few = n_leaves <= kPlanLeaves;
+#define ARBOR_PLAN_LAUNCH(S, F) \
+  hipLaunchKernelGGL((decode_plan<S, F>), dim3(1), dim3(plan_threads), 0, stream, a, ent)
   if (small && few) ARBOR_PLAN_LAUNCH(true, true);
   else if (small) ARBOR_PLAN_LAUNCH(true, false);
   else if (few) ARBOR_PLAN_LAUNCH(false, true);

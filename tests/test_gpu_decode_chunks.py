@@ -1,0 +1,74 @@
+"""GPU parity of the tree decode over its chunk sizes and row blocks: the plan
+cuts a chain node's slots into chunks of 64 to 1,024 by the number of units,
+and its rows (leaves below it times G) into blocks of 16.  |g - o| <= 2e-3 for
+fp32 outputs and 1e-4 relative for A, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import arbor_oracle as O
+from paper_2605_22106_amd import _lib as L
+from paper_2605_22106_amd import synth
+from tests.gpu_helpers import check_rc, status, to_gpu, workspace
+from tests.helpers import oracle_state
+
+pytestmark = pytest.mark.gpu
+
+
+def _tree(root, nodes):
+    """root -> three children -> two leaves each, with the given token counts."""
+    parent = [-1, 0, 0, 0, 1, 1, 2, 2, 3, 3]
+    return parent, [root] + nodes
+
+
+# (layers, root tokens, leaves, G, dtype): one plane set of 8 kv heads per
+# layer, so that 1 layer gives few units (64-slot chunks), 8 layers under many
+# rows a middle size, and 64 layers at least 4,096 units of 1,024 slots
+CASES = [(1, 1, [4], 4, "bf16"), (1, 63, [4, 9], 8, "bf16"), (1, 1100, [4, 5, 6, 9], 4, "bf16"),
+         (1, 64, [1, 4, 8], 1, "f32"), (8, 1025, [4, 5, 6, 7, 8, 9] * 3, 8, "bf16"),
+         (8, 700, [4], 1, "f32"), (64, 2049, [4, 5, 6, 9, 9], 8, "bf16"),
+         (64, 1024, [7], 4, "bf16"), (2, 300, [4, 5, 6, 7, 8, 9, 1, 0] * 9, 2, "bf16")]
+
+
+@pytest.mark.parametrize("layers,root,leaves,G,dtype", CASES)
+def test_decode_chunks(layers, root, leaves, G, dtype):
+    nodes = [70, 128, 1, 65, 16, 257, 33, 640, 15]
+    parent, n_full = _tree(root, nodes)
+    d = 64 if layers > 1 else 128
+    st = synth.build_state(parent, n_full, layers=layers, kv_heads=8, q_per_kv=G, head_dim=d,
+                           dtype=dtype, seed=root + layers, shuffle_pages=True, heavy_frac=0.05,
+                           active=leaves, host_store=False)
+    kv = to_gpu(st)
+    Hq, nb = 8 * G, len(leaves)
+    q = st["q_dec"].cuda().contiguous()
+    lt = torch.tensor(leaves, dtype=torch.int32, device="cuda")
+    ws = workspace(kv, max_leaves=nb, max_layers=layers, n_slice=1)
+    outs = []
+    for scored in (False, True):
+        out = torch.full((nb, layers, Hq, d), 7.0, device="cuda")
+        lse = torch.full((nb, layers, Hq), 7.0, device="cuda")
+        A = torch.zeros(kv.num_tokens, device="cuda")
+        rows = torch.zeros(kv.num_nodes, dtype=torch.int64, device="cuda")
+        stt = status()
+        if scored:
+            check_rc(L.arbor_tree_decode_attn_scored(kv, lt, 0, layers, q, out, lse, 0.0,
+                                                     [layers - 1], 1, A, rows, stt, ws))
+        else:
+            check_rc(L.arbor_tree_decode_attn(kv, lt, 0, layers, q, out, lse, 0.0, stt, ws))
+        torch.cuda.synchronize()
+        assert int(stt) == L.OK
+        outs.append((out, lse))
+    # the plain and the scored call agree bitwise, at every layer
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    # the last and the first layer against the oracle on that layer
+    for lr in {0, layers - 1}:
+        one = oracle_state(dict(st, k=st["k"][lr:lr + 1], v=st["v"][lr:lr + 1]))
+        ql = q[:, lr:lr + 1].float().cpu().numpy()
+        o, ls = O.tree_decode_attn(one, leaves, 0, 1, ql, G)
+        assert np.max(np.abs(outs[0][0][:, lr].cpu().numpy() - o[:, 0])) <= 2e-3
+        assert np.max(np.abs(outs[0][1][:, lr].cpu().numpy() - ls[:, 0])) <= 2e-3
+        if lr == layers - 1:
+            Ao, ro = O.decode_credit(one, leaves, 0, ql, G, [0], np.zeros(kv.num_tokens, np.float32),
+                                     np.zeros(kv.num_nodes, np.int64), self_window=1)
+            assert np.allclose(A.cpu().numpy(), Ao, rtol=1e-4, atol=1e-30)
+            assert np.array_equal(rows.cpu().numpy(), ro)
