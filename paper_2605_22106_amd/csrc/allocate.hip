@@ -14,15 +14,16 @@
 // Finding the (E+1)-th smallest price without listing every token: the prices
 // of block i are j / W_i for consecutive j, so the number of prices up to x is
 // floor(x W_i) - F_i (clamped), exact up to rounding at the two ends.  A
-// search over x with that count brackets the order statistic between two
-// values whose exact counts lie on either side of E; only the few prices in
-// the bracket are listed, and an MSB-first radix select over their fp64 bit
-// patterns (positive doubles order like their bits) picks the exact one.
+// search over x on exact counts brackets the order statistic between two
+// values whose counts lie on either side of E; only the few prices left in
+// the bracket are listed and ranked (positive doubles order like their bits).
 //
-// Everything runs in one 1024-thread workgroup: the work is O(V) per search
-// step and latency bound.  Per-node state sits in LDS when the tree is small
-// enough, else in the workspace.  fp64, no contraction, so the prices are the
-// same IEEE quotients any fp64 implementation computes.
+// Small trees (kLdsNodes) run in one 1024-thread workgroup with all per-node
+// state in LDS.  Larger ones take two launches: alloc_nodes, one thread per
+// block over the whole chip (geometry, floors, weights, eligible prices and
+// their totals per workgroup), then alloc_cut, one workgroup (the search and
+// the counts, or the Pressure drain).  fp64, no contraction, so the prices
+// are the same IEEE quotients any fp64 implementation computes.
 #include "arbor_internal.h"
 
 #pragma clang fp contract(off)
@@ -33,12 +34,14 @@ namespace {
 
 constexpr int AT = 1024;
 constexpr int kLdsNodes = 512;    // per-node state in LDS up to this many nodes
-constexpr int kGeoNodes = 10240;  // parent, depth and down links in LDS up to this many
-constexpr int kCandLds = 1536;    // listed prices selected in LDS up to this many
+constexpr int kGeoNodes = 16384;  // parent and down links in LDS up to this many
+constexpr int kCandLds = 1536;    // listed prices
 constexpr int kNodeBytes = 2 * 8 + 8 * 4 + 1;
-constexpr int kSearchWaves = AT / kWave / 2;   // waves per bracket end
-constexpr int kPtsPerWave = 4;                  // test points of each wave
-constexpr int kSearchPts = kSearchWaves * kPtsPerWave;   // test points per end
+constexpr int kNodeThreads = 256; // blocks of a workgroup of alloc_nodes
+constexpr int kCutThreads = 512;  // threads of alloc_cut
+constexpr int kRegNodes = 20;     // blocks of a thread of alloc_cut held in registers
+constexpr int kCutPts = 3;        // test points of a search round
+constexpr int kSnapFrom = 10, kSnapEvery = 6;   // search rounds that look for ties
 constexpr int kDecay = 128;                    // tabulated depths and distances
 
 // The decay factors exp(-lambda_d d) and exp(-lambda_Delta Delta) for small
@@ -73,13 +76,26 @@ struct Nodes {
   uint8_t *path;
 };
 
+// Totals of one workgroup of alloc_nodes.
+struct NodeSums {
+  int64_t path_tok, sum_F, sum_red, total;
+  int64_t kmin, kmax;    // price keys of the eligible prices
+  int64_t flags;         // malformed | NaN s << 21 | s outside [0, 1] << 42 (at most one
+                         //   of each per workgroup)
+};
+
+// A block as alloc_cut reads it, in one 16-byte load.
+struct __attribute__((aligned(16))) NodeRec {
+  int32_t F, cnt;                  // F: -1 on pinned Path* blocks
+  double W;                        // 1 on blocks without eligible prices
+};
+
 struct AllocWs {
-  int32_t *depth, *down, *F, *cnt, *cap;
-  double *W, *w;
-  uint64_t *buf0, *buf1;
-  int64_t buf_cap;
-  int32_t *eF, *eC;     // the blocks with eligible prices: F, count
-  double *eW;            // and W, side by side (trees beyond LDS mode)
+  int32_t *down;
+  NodeRec *rec;
+  double *w;
+  NodeSums *sums;                  // per workgroup of alloc_nodes
+  int32_t *gated;                  // 1: a Pressure event that does not fire
 };
 
 __device__ __forceinline__ double price(int j, double W) {
@@ -117,7 +133,9 @@ __device__ int last_le(double x, int F, int cnt, double W) {
   const bool up_ok = m == F + cnt || (double)(m + 1) > yr * (1.0 + 0x1p-50);
   const bool down_ok = m == F || (double)m < yr * (1.0 - 0x1p-50);
   if (up_ok && down_ok && yr < __builtin_inf()) return m;
+#pragma unroll 1
   while (m < F + cnt && price(m + 1, W) <= x) ++m;
+#pragma unroll 1
   while (m > F && price(m, W) > x) --m;
   return m;
 }
@@ -131,9 +149,21 @@ __device__ int last_lt(double x, int F, int cnt, double W) {
   const bool up_ok = m == F + cnt || (double)(m + 1) > yr * (1.0 + 0x1p-50);
   const bool down_ok = m == F || (double)m < yr * (1.0 - 0x1p-50);
   if (up_ok && down_ok && yr < __builtin_inf()) return m;
+#pragma unroll 1
   while (m < F + cnt && price(m + 1, W) < x) ++m;
+#pragma unroll 1
   while (m > F && !(price(m, W) < x)) --m;
   return m;
+}
+
+// last_le and last_lt where they agree and need no division: floor(x W),
+// clamped, unless x W lies within 2^-50 of an integer (or is no number), which
+// sets *near.
+// (lo = F, hi = F + cnt)
+__device__ __forceinline__ int last_fast(double x, double lo, double hi, double W, bool &near) {
+  const double yr = x * W;
+  near |= !(__builtin_fabs(yr - __builtin_rint(yr)) > yr * 0x1p-50) && !(yr >= hi + 1.0);
+  return (int)__builtin_fmin(__builtin_fmax(__builtin_floor(yr), lo), hi);
 }
 
 // Eligible prices of a block: those in (F, cap] that are finite and at most
@@ -144,12 +174,6 @@ __device__ int eligible(int F, int cap, double W, double amax) {
   if (last <= amax && last < __builtin_inf()) return cap - F;
   if (last < __builtin_inf()) return last_le(amax, F, cap - F, W) - F;
   return count_prefix(F, cap, W, [amax](double x) { return x <= amax && x < __builtin_inf(); });
-}
-
-// Rounded count of prices <= x of one node (exact up to one price at each end).
-__device__ __forceinline__ double approx_le(double x, int F, int cnt, double W) {
-  double y = __builtin_floor(x * W) - (double)F;
-  return y < 0.0 ? 0.0 : (y > (double)cnt ? (double)cnt : y);
 }
 
 // three block-wide sums in one exchange; sm holds 48 values
@@ -324,32 +348,555 @@ __device__ __forceinline__ double key_value(uint64_t k) {
   return __longlong_as_double((long long)k);
 }
 
-// test point q (0-based) of N splitting (lo, lo + span) into N + 1 parts
-template <int N>
-__device__ __forceinline__ uint64_t split_point(uint64_t lo, uint64_t span, int q) {
-  const uint64_t m = (uint64_t)(q + 1);
-  return lo + (span / (N + 1)) * m + ((span % (N + 1)) * m) / (N + 1);
+// What one block brings to the allocation: floor, cap, weights and its eligible
+// prices.  di: depth, best: distance to the nearest active leaf, on: Path*
+// (not pinned); flags a bad score in err (2: NaN, 4: outside [0, 1]).
+struct NodeTerms {
+  int F, cap, cnt;
+  double W, w;
+  uint64_t lo, hi;   // keys of its first and last eligible price (cnt > 0)
+};
+__device__ __forceinline__ NodeTerms node_terms(const AllocParams &p, const double *dexp,
+                                                const double *texp, bool on, int n, int c,
+                                                float sf, int di, int best, int &err) {
+  NodeTerms r;
+  r.cap = on && p.rehydrate ? n : c;
+  // s_i = clip(sigmoid(.), 0, 1) lies in [0, 1]
+  if (!(sf == sf)) err |= 2;
+  else if (!(sf >= 0.f && sf <= 1.f)) err |= 4;
+  const double s = (double)sf;
+  // Eq. 3 at the ratio floor r_min, capped; a Path* block under floor
+  // protection keeps at least k_protect
+  int f = max(p.k_min, min(p.l_tail, n));
+  f = max(f, (int)floor(p.r_min * (double)n));
+  f = min(r.cap, min(n, f));
+  if (on) f = max(f, min(r.cap, p.k_protect));
+  r.F = f;
+  // the Eq. 2 weight without alpha, in the same operation order as
+  // ((eta^[off path] * s^gamma) * e^{-lambda_d d}) * e^{-lambda_Delta Delta}
+  double w = (on ? 1.0 : p.eta) * pow_gamma(s, p.gamma);
+  w = w * (di < kDecay ? dexp[di] : exp(-p.lambda_d * (double)di));
+  w = w * (best < kDecay ? texp[best] : exp(-p.lambda_delta * (double)best));
+  // -0 (s = -0 with an odd gamma) as +0: the Pressure order compares bit
+  // patterns, in which -0 would rank above every positive weight
+  r.w = w == 0.0 ? 0.0 : w;
+  r.W = r.w * (double)n;
+  r.cnt = eligible(f, r.cap, r.W, p.alpha_max);
+  r.lo = r.hi = 0;
+  if (r.cnt > 0) {
+    r.lo = (uint64_t)__double_as_longlong(price(f + 1, r.W));
+    r.hi = (uint64_t)__double_as_longlong(price(f + r.cnt, r.W));
+  }
+  return r;
 }
 
-// MODE 1: all per-node state in LDS; 2: the geometry (parent, depth, down)
-// in LDS, the rest in the workspace; 0: everything in the workspace.  The
-// mode is a template argument so that every access compiles to an LDS or a
-// global instruction rather than a flat one.
-template <int MODE>
+// Pressure (Alg. 2): the floors exceed the budget by `excess`; the blocks of
+// lowest priority are drained to min(K_min, c).  Called by the whole workgroup.
+template <class Floor>
+__device__ void pressure_drain(const AllocParams &p, int V, const uint8_t *path, Floor &&F,
+                               const double *w, const int32_t *n_kept, int64_t sum_red,
+                               int64_t excess, int32_t *__restrict__ k_out, int32_t *status,
+                               int64_t *sm) {
+  __shared__ unsigned long long hist64[256];
+  const int tid = threadIdx.x;
+  if (sum_red < excess) {
+    for (int i = tid; i < V; i += (int)blockDim.x) {
+      if (!path[i]) k_out[i] = min(p.k_min, n_kept[i]);
+      else if (p.k_protect > 0) k_out[i] = F(i);   // Path* keeps its floor
+    }
+    if (tid == 0) status_warn(status, ARBOR_OVER_BUDGET);
+    return;
+  }
+  // smallest priority value W* whose cumulative reducible count reaches excess
+  uint64_t prefix = 0, pmask = 0;
+  int64_t need = excess;
+  for (int shift = 56; shift >= 0; shift -= 8) {
+    for (int b = tid; b < 256; b += (int)blockDim.x) hist64[b] = 0;
+    __syncthreads();
+    for (int i = tid; i < V; i += (int)blockDim.x) {
+      if (path[i]) continue;
+      const uint64_t key = (uint64_t)__double_as_longlong(w[i]);
+      if ((key & pmask) != prefix) continue;
+      const int red = F(i) - min(p.k_min, n_kept[i]);
+      if (red > 0) atomicAdd(&hist64[(key >> shift) & 255ull], (unsigned long long)red);
+    }
+    __syncthreads();
+    int chosen = 255;
+    int64_t acc = 0;
+    for (int b = 0; b < 256; ++b) {
+      const int64_t h = (int64_t)hist64[b];
+      if (acc + h >= need) {
+        chosen = b;
+        break;
+      }
+      acc += h;
+    }
+    need -= acc;
+    prefix |= (uint64_t)chosen << shift;
+    pmask |= 255ull << shift;
+    __syncthreads();
+  }
+  // nodes below W* drain fully; nodes at W* drain in id order until `need`
+  int64_t run = 0;
+  for (int base = 0; base < V; base += (int)blockDim.x) {
+    const int i = base + tid;
+    int64_t red = 0;
+    uint64_t key = 0;
+    const bool off = i < V && !path[i];
+    if (off) {
+      red = F(i) - min(p.k_min, n_kept[i]);
+      key = (uint64_t)__double_as_longlong(w[i]);
+    }
+    const bool tie = off && key == prefix;
+    int64_t tot;
+    const int64_t ex = block_exclusive_scan<int64_t>(tie ? red : 0, sm, &tot);
+    if (off) {
+      int kk = F(i);
+      if (key < prefix) {
+        kk -= (int)red;
+      } else if (tie) {
+        const int64_t before = run + ex;
+        if (before < need) kk -= (int)min<int64_t>(red, need - before);
+      }
+      k_out[i] = kk;
+    } else if (i < V && p.k_protect > 0) {
+      k_out[i] = F(i);                                // Path* keeps its floor
+    }
+    run += tot;
+  }
+}
+
+// Larger trees, first launch for trees beyond kGeoNodes blocks: the distance of
+// each Path* block down to its nearest active leaf, in the workspace (one
+// workgroup; alloc_nodes forms it in LDS for smaller ones).
+__global__ __launch_bounds__(AT) void alloc_path(Tree t, const int32_t *__restrict__ active,
+                                                 int n_active, int32_t *status, AllocWs ws) {
+  if (status_failed(status)) return;
+  for (int i = threadIdx.x; i < t.V; i += AT) ws.down[i] = INT32_MAX;
+  __syncthreads();
+  for (int j = threadIdx.x; j < n_active; j += AT) {
+    const int l = active[j];
+    if (l < 0 || l >= t.V) continue;
+    int k = 0;
+    for (int a = l;; ++k) {
+      atomicMin(&ws.down[a], k);
+      const int pa = a > 0 ? t.parent[a] : -1;
+      if (pa < 0 || pa >= a) break;
+      a = pa;
+    }
+  }
+}
+
+// Larger trees: geometry, floors, weights and eligible prices, one thread per
+// block.  Every workgroup copies the parent links to LDS and marks the active
+// chains itself (a chain is short, and a copy of the links costs less than
+// the launch that would share the marks), so nothing waits on another
+// workgroup.  One workgroup for all blocks took 35 us of its 41 here on the
+// 9,841-block tree; this kernel takes @NODES@.
+template <bool IN_LDS>
+__global__ __launch_bounds__(kNodeThreads) void alloc_nodes(
+    Tree t, const int32_t *__restrict__ active, int n_active, int64_t budget,
+    const float *__restrict__ s_in, AllocParams p, int32_t *__restrict__ k_out,
+    int32_t *__restrict__ delta_out, uint8_t *__restrict__ on_path, int32_t *status, AllocWs ws,
+    int gate) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ int64_t sm[6 * 16];
+  __shared__ double s_dexp[kDecay], s_texp[kDecay];
+  __shared__ int s_err;
+  constexpr int NT = kNodeThreads;
+  const int tid = threadIdx.x, V = t.V;
+  const int i = blockIdx.x * NT + tid;
+  const bool live = i < V;
+  // the thread's block, its score and the decay tables: loads issued
+  // together, ahead of the status check, so they cost one round trip
+  int par0 = 0, n = 0, c = 0;
+  float s0 = 0.f;
+  if (live) {
+    par0 = t.parent[i];
+    n = t.n_full[i];
+    c = t.n_kept[i];
+    s0 = s_in[i];
+  }
+  const int leaf0 = tid < n_active ? active[tid] : 0;
+  static_assert(kNodeThreads >= kDecay, "one table entry per thread");
+  double dx = 0.0, tx = 0.0;
+  if (tid < kDecay) {
+    dx = p.dexp[tid];
+    tx = p.texp[tid];
+  }
+  if (status_failed(status)) return;
+  if (tid < kDecay) {
+    s_dexp[tid] = dx;
+    s_texp[tid] = tx;
+  }
+  if (tid == 0) s_err = 0;
+  if (gate) {
+    // a Pressure event (Alg. 2): it fires only when the resident tokens
+    // reach the budget it is given; otherwise every count stays as it is
+    int64_t m = 0;
+#pragma unroll 8
+    for (int x = tid; x < V; x += NT) m += t.n_kept[x];
+    m = block_sum<int64_t>(m, sm);
+    if (blockIdx.x == 0 && tid == 0) *ws.gated = m < budget;
+    if (m < budget) {
+      if (live) k_out[i] = c;
+      return;
+    }
+  } else if (blockIdx.x == 0 && tid == 0) {
+    *ws.gated = 0;
+  }
+  int32_t *const s_par = reinterpret_cast<int32_t *>(dyn);
+  int32_t *const s_down = s_par + V;
+  const int32_t *par = IN_LDS ? s_par : t.parent;
+  const int32_t *down = IN_LDS ? s_down : ws.down;
+  if constexpr (IN_LDS) {
+#pragma unroll 8
+    for (int x = tid; x < V; x += NT) {
+      s_par[x] = t.parent[x];
+      s_down[x] = INT32_MAX;
+    }
+  }
+  __syncthreads();
+  int err = 0;
+  for (int j = tid; j < n_active; j += NT) {
+    const int l = j == tid ? leaf0 : active[j];
+    if (l < 0 || l >= V) {
+      err |= 1;
+      continue;
+    }
+    if constexpr (IN_LDS) {
+      int k = 0;
+      for (int a = l;; ++k) {
+        atomicMin(&s_down[a], k);
+        const int pa = a > 0 ? s_par[a] : -1;
+        if (pa < 0 || pa >= a) break;       // (the block's own thread reports it)
+        a = pa;
+      }
+    }
+  }
+  __syncthreads();
+  // depth d_i and Delta_i = min over ancestors a (incl. i) of the steps up to a
+  // plus the distance from a down to its nearest active leaf
+  int64_t v[6] = {0, 0, 0, 0, INT64_MAX, INT64_MAX};
+  if (live) {
+    if (!((i == 0 ? par0 == -1 : (par0 >= 0 && par0 < i)) && n >= 0 && c >= 0 && c <= n)) err |= 1;
+    int d = 0, best = INT32_MAX;
+    for (int a = i;; ++d) {
+      const int dn = down[a];
+      if (dn != INT32_MAX) best = min(best, d + dn);
+      if (a == 0) break;
+      const int pa = par[a];
+      if (pa < 0 || pa >= a) {
+        err |= 1;
+        break;
+      }
+      a = pa;
+    }
+    const bool on = down[i] != INT32_MAX;
+    delta_out[i] = best;
+    on_path[i] = on ? 1 : 0;
+    if (on && p.k_protect == 0) {
+      // pinned (invariant (i), full protection): restored by rehydration to
+      // n_i, or c_i when evicted tokens stay lost
+      const int keep = p.rehydrate ? n : c;
+      k_out[i] = keep;
+      v[0] = keep;
+      ws.rec[i] = NodeRec{-1, 0, 1.0};
+    } else if (!err) {
+      const NodeTerms r = node_terms(p, s_dexp, s_texp, on, n, c, s0, d, best, err);
+      ws.rec[i] = NodeRec{r.F, r.cnt, r.cnt > 0 ? r.W : 1.0};
+      ws.w[i] = r.w;
+      v[1] = r.F;
+      // Pressure lowers only off-path blocks
+      if (!on) v[2] = r.F - min(p.k_min, c);
+      v[3] = r.cnt;
+      if (r.cnt > 0) {
+        v[4] = (int64_t)r.lo;
+        v[5] = INT64_MAX - (int64_t)r.hi;
+      }
+    }
+  }
+  if (err) atomicOr(&s_err, err);
+  block_reduce_n<4>(v, sm, NT);            // (its barriers also settle s_err)
+  if (tid == 0) {
+    const int64_t e = s_err;
+    ws.sums[blockIdx.x] = NodeSums{v[0], v[1], v[2], v[3], v[4], INT64_MAX - v[5],
+                                   (e & 1) | ((e >> 1) & 1) << 21 | ((e >> 2) & 1) << 42};
+  }
+}
+
+// block-wide sums of three counts kept as doubles (exact: below 2^53); sm holds
+// 48 values
+__device__ void block_sum3_f64(double (&v)[3], double *sm) {
+  const int lane = lane_id(), w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) v[q] = wave_sum(v[q]);
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) sm[16 * q + w] = v[q];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 3; ++q) v[q] = wave_sum(lane < nw ? sm[16 * q + lane] : 0.0);
+}
+
+// Larger trees, last launch (one workgroup): the totals, then alpha from the
+// price order statistic, or Pressure.  A search round counts the prices up to
+// kCutPts keys over every block; up to kCutThreads * kRegNodes blocks sit in registers
+// (REG), so a round costs its fp64 work, five operations per block and key,
+// and few keys a round, placed by interpolation, cost least.  The counts are
+// floor(x W), which may be off by one where x W lies within a rounding of an
+// integer: the bracket that they leave is counted exactly before it is used,
+// and a search that it does not confirm is done again on exact counts.
+// 9,841 blocks with scores drawn from [0, 1] take @CUT@ us here, against 250
+// of 320 us for rounds of 64 keys that every wave read from L2, and a listing
+// of all prices within rounding of the cut.  More blocks stream from the
+// workspace each round.
+template <bool REG>
+__global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget, AllocParams p,
+                                                int32_t *__restrict__ k_out,
+                                                const uint8_t *__restrict__ on_path,
+                                                int32_t *status, AllocWs ws, int n_sums) {
+  __shared__ int64_t sm[7 * 16];
+  __shared__ double sc[2][48];
+  __shared__ uint64_t s_cand[2 * kCandLds];
+  const int tid = threadIdx.x, V = t.V;
+  constexpr int NR = REG ? kRegNodes : 1;
+  // a block's floor and floor + count as doubles, as the search reads them
+  struct Blk {
+    double lo, hi, W;
+    __device__ __forceinline__ int F() const { return (int)lo; }
+    __device__ __forceinline__ int cnt() const { return (int)hi - (int)lo; }
+  };
+  auto blk = [](const NodeRec &n) __attribute__((always_inline)) {
+    return Blk{(double)n.F, (double)(n.F + n.cnt), n.W};
+  };
+  Blk rec[NR];
+  if constexpr (REG) {
+    // (issued together with the status word)
+    NodeRec raw[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) raw[r] = ws.rec[min(tid + r * kCutThreads, V - 1)];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      rec[r] = tid + r * kCutThreads < V ? blk(raw[r]) : Blk{-1.0, -1.0, 1.0};
+  }
+  if (status_failed(status)) return;
+  if (*ws.gated) return;
+  // f(i, block) for each of the thread's blocks: from the registers (the search
+  // only: a pass of this kind is unrolled), or as a loop over the workspace
+  // (which the L2 holds)
+  auto each_reg = [&](auto &&f) __attribute__((always_inline)) {
+    if constexpr (REG) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) f(tid + r * kCutThreads, rec[r]);
+    } else {
+#pragma unroll 4
+      for (int i = tid; i < V; i += kCutThreads) f(i, blk(ws.rec[i]));
+    }
+  };
+  auto each = [&](auto &&f) __attribute__((always_inline)) {
+    NodeRec next = ws.rec[min(tid, V - 1)];
+#pragma unroll 1
+    for (int i = tid; i < V; i += kCutThreads) {
+      const Blk cur = blk(next);
+      next = ws.rec[min(i + kCutThreads, V - 1)];
+      f(i, cur);
+    }
+  };
+  int64_t v[7] = {0, 0, 0, 0, 0, INT64_MAX, INT64_MAX};
+  for (int e = tid; e < n_sums; e += kCutThreads) {
+    const NodeSums s = ws.sums[e];
+    v[0] += s.path_tok;
+    v[1] += s.sum_F;
+    v[2] += s.sum_red;
+    v[3] += s.total;
+    v[4] += s.flags;
+    v[5] = min(v[5], s.kmin);
+    v[6] = min(v[6], INT64_MAX - s.kmax);
+  }
+  block_reduce_n<5>(v, sm, min(n_sums, kCutThreads));
+#pragma unroll
+  for (int q = 0; q < 7; ++q) v[q] = lane_value(v[q], 0);
+  const int64_t path_tok = v[0], sum_F = v[1], sum_red = v[2], total = v[3];
+  if (v[4]) {
+    constexpr int64_t k21 = (1 << 21) - 1;
+    if (tid == 0)
+      status_error(status, !(v[4] & k21) && ((v[4] >> 21) & k21) ? ARBOR_ENONFINITE : ARBOR_EINVAL);
+    return;
+  }
+  const int64_t b_off = budget - path_tok;
+  if (sum_F > b_off) {
+    pressure_drain(p, V, on_path, [&](int i) { return ws.rec[i].F; }, ws.w, t.n_kept, sum_red,
+                   sum_F - b_off, k_out, status, sm);
+    return;
+  }
+  const int64_t E = b_off - sum_F;
+  if (total <= E) {
+    each([&](int i, const Blk &n) __attribute__((always_inline)) {
+      if (n.lo >= 0.0) k_out[i] = (int)n.hi;
+    });
+    return;
+  }
+  // the thread's floors (a block's count is floor(x W), clamped, less its floor)
+  double F0 = 0.0;
+  each_reg([&](int, const Blk &n) __attribute__((always_inline)) { F0 += n.lo; });
+  uint64_t answer = 0;
+  for (bool exact = false;; exact = true) {
+    // count(<= ka) = cA <= E < cB = count(<= kb), from below every price to the
+    // largest one (keys of finite positive doubles; -1: below a zero price)
+    int64_t ka = v[5] - 1, kb = INT64_MAX - v[6];
+    double cA = 0.0, cB = (double)total;
+    const double Ed = (double)E;
+    bool even = true;                    // place the keys evenly, not by interpolation
+    for (int round = 0; kb - ka > 1 && cB - cA > (double)kCandLds; ++round) {
+      if (round >= kSnapFrom && (round - kSnapFrom) % kSnapEvery == 0) {
+        // the bracket's ends onto prices: many equal prices (blocks of one size
+        // and weight) would hold up the search to the last bit
+        int64_t w[3] = {0, INT64_MAX, INT64_MAX};
+        const double xa = ka >= 0 ? key_value((uint64_t)ka) : 0.0, xb = key_value((uint64_t)kb);
+        each([&](int, const Blk &n) __attribute__((always_inline)) {
+          const int m_lo = ka >= 0 ? last_le(xa, n.F(), n.cnt(), n.W) : n.F();
+          const int m_hi = last_le(xb, n.F(), n.cnt(), n.W);
+          if (m_hi > m_lo) {
+            w[1] = min(w[1], (int64_t)__double_as_longlong(price(m_lo + 1, n.W)));
+            w[2] = min(w[2], INT64_MAX - (int64_t)__double_as_longlong(price(m_hi, n.W)));
+          }
+        });
+        block_min_sum3(w, sm);
+        if (w[1] == INT64_MAX) break;    // (rounded counts, and no price at all)
+        ka = lane_value(w[1], 0) - 1;
+        kb = INT64_MAX - lane_value(w[2], 0);
+        if (kb - ka <= 1) break;
+      }
+      const int64_t span = kb - ka;
+      int64_t x[kCutPts];
+      if (even) {
+#pragma unroll
+        for (int q = 0; q < kCutPts; ++q) x[q] = ka + span / (kCutPts + 1) * (q + 1);
+      } else {
+        const double f = (Ed - cA + 0.5) / (cB - cA);
+        const int64_t xi = ka + lane_value((int64_t)(f * (double)span), 0), dx = span / 8;
+#pragma unroll
+        for (int q = 0; q < kCutPts; ++q) {
+          const int64_t o = (q - kCutPts / 2) * dx;
+          x[q] = o < kb - xi ? xi + o : kb - 1;
+        }
+      }
+      double c[kCutPts], xv[kCutPts];
+#pragma unroll
+      for (int q = 0; q < kCutPts; ++q) {
+        x[q] = min(max(x[q], ka + 1), kb - 1);
+        xv[q] = key_value((uint64_t)x[q]);
+        c[q] = -F0;
+      }
+      if (!exact) {
+        each_reg([&](int, const Blk &n) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < kCutPts; ++q)
+            c[q] += __builtin_fmin(__builtin_fmax(__builtin_floor(xv[q] * n.W), n.lo), n.hi);
+        });
+      } else {
+        each([&](int, const Blk &n) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < kCutPts; ++q) c[q] += (double)last_le(xv[q], n.F(), n.cnt(), n.W);
+        });
+      }
+      static_assert(kCutPts == 3, "one block_sum3_f64 per round");
+      block_sum3_f64(c, sc[round & 1]);
+      // (wave-uniform: kept in scalar registers, beside the blocks)
+#pragma unroll
+      for (int q = 0; q < kCutPts; ++q) c[q] = lane_value(c[q], 0);
+      // the keys ascend and their counts with them
+#pragma unroll
+      for (int q = 0; q < kCutPts; ++q)
+        if (c[q] <= Ed) {
+          ka = x[q];
+          cA = c[q];
+        }
+#pragma unroll
+      for (int q = kCutPts - 1; q >= 0; --q)
+        if (c[q] > Ed) {
+          kb = x[q];
+          cB = c[q];
+        }
+      // interpolation that shrinks the bracket less than even keys would gives
+      // way to them for a round
+      even = !even && kb - ka > span / (kCutPts + 1);
+    }
+    // the bracket's exact counts: the prices up to ka, and the thread's prices
+    // in (ka, kb] with their places in the list
+    const double xa = ka >= 0 ? key_value((uint64_t)ka) : 0.0, xb = key_value((uint64_t)kb);
+    int64_t below = 0, mine = 0;
+    auto range = [&](const Blk &n, int &m_lo, int &m_hi) __attribute__((always_inline)) {
+      bool near = ka < 0;
+      m_lo = last_fast(xa, n.lo, n.hi, n.W, near);
+      m_hi = last_fast(xb, n.lo, n.hi, n.W, near);
+      if (near) {
+        m_lo = ka >= 0 ? last_le(xa, n.F(), n.cnt(), n.W) : n.F();
+        m_hi = last_le(xb, n.F(), n.cnt(), n.W);
+      }
+    };
+    each([&](int, const Blk &n) __attribute__((always_inline)) {
+      int m_lo, m_hi;
+      range(n, m_lo, m_hi);
+      below += m_lo - n.F();
+      mine += m_hi - m_lo;
+    });
+    const int64_t v2[2] = {below, mine};
+    int64_t ex[2], tot[2];
+    __syncthreads();                       // (the search's last reads of its exchange)
+    block_exclusive_scan_n<2>(v2, ex, tot, sm);
+    if (tot[0] > E || tot[0] + tot[1] <= E) {
+      if (exact) return;                   // (cannot be: the counts were exact)
+      continue;
+    }
+    if (kb - ka <= 1) {
+      answer = (uint64_t)kb;
+      break;
+    }
+    if (tot[1] > kCandLds) {
+      if (exact) return;
+      continue;
+    }
+    // the listed prices and their order statistic
+    if (mine > 0) {
+      int64_t off = ex[1];
+      each([&](int, const Blk &n) __attribute__((always_inline)) {
+        int m_lo, m_hi;
+        range(n, m_lo, m_hi);
+#pragma unroll 1
+        for (int j = m_lo; j < m_hi; ++j)
+          s_cand[off++] = (uint64_t)__double_as_longlong(price(j + 1, n.W));
+      });
+    }
+    __syncthreads();
+    answer = select_rank(s_cand, s_cand + kCandLds, tot[1], E - tot[0], sm, true,
+                         (uint64_t)(ka + 1), (uint64_t)kb);
+    break;
+  }
+  // the prices below the cut, all of them eligible ones (the cut is)
+  const double cut = key_value(answer);
+  each([&](int i, const Blk &n) __attribute__((always_inline)) {
+    bool near = false;
+    int m = last_fast(cut, n.lo, n.hi, n.W, near);
+    if (near) m = last_lt(cut, n.F(), n.cnt(), n.W);
+    if (n.lo >= 0.0) k_out[i] = m;
+  });
+}
+
+// Small trees: one workgroup, all per-node state in LDS.
 __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__restrict__ active,
                                                       int n_active, int64_t budget,
                                                       const float *__restrict__ s_in, AllocParams p,
                                                       int32_t *__restrict__ k_out,
                                                       int32_t *__restrict__ delta_out,
                                                       uint8_t *__restrict__ on_path,
-                                                      int32_t *status, AllocWs ws, int gate) {
-  constexpr int in_lds = MODE;
+                                                      int32_t *status, int gate) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ int64_t sm[7 * 16];
   __shared__ int s_err;
-  __shared__ unsigned long long hist64[256];
-  __shared__ double s_cnt[2][2 * kSearchPts];
-  __shared__ uint64_t s_x[2][2 * kSearchPts];
+  __shared__ double s_cnt[2][kWave];
+  __shared__ uint64_t s_x[2][kWave];
   __shared__ double s_dexp[kDecay], s_texp[kDecay];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = lane_id();
@@ -387,14 +934,12 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
     }
   }
 
-  // listed prices: LDS after the node state when few enough, else workspace
-  const size_t node_lds = in_lds == 1 ? ((size_t)V * kNodeBytes + 15) / 16 * 16
-                                      : (in_lds == 2 ? ((size_t)V * 12 + 15) / 16 * 16 : 0);
+  // listed prices and the per-wave counts of the search after the node state
+  const size_t node_lds = ((size_t)V * kNodeBytes + 15) / 16 * 16;
   uint64_t *const cand_lds = reinterpret_cast<uint64_t *>(dyn + node_lds);
-  // per-wave counts of the search (in LDS mode only)
-  double *const s_part = reinterpret_cast<double *>(cand_lds + 2 * kCandLds);
+  double *const s_part = reinterpret_cast<double *>(cand_lds + kWave);
   Nodes nd;
-  if (in_lds == 1) {
+  {
     double *dp = reinterpret_cast<double *>(dyn);
     nd.W = dp;
     nd.w = dp + V;
@@ -408,33 +953,11 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
     nd.cnt = ip + 6 * V;
     nd.cap = ip + 7 * V;
     nd.path = reinterpret_cast<uint8_t *>(ip + 8 * V);
-
-    for (int i = tid; i < V; i += AT) {
-      nd.parent[i] = i == tid ? par0 : t.parent[i];
-      nd.n_full[i] = i == tid ? nf0 : t.n_full[i];
-      nd.n_kept[i] = i == tid ? nk0 : t.n_kept[i];
+    if (tid < V) {
+      nd.parent[tid] = par0;
+      nd.n_full[tid] = nf0;
+      nd.n_kept[tid] = nk0;
     }
-  } else {
-    nd.parent = const_cast<int32_t *>(t.parent);
-    nd.n_full = const_cast<int32_t *>(t.n_full);
-    nd.n_kept = t.n_kept;
-    nd.depth = ws.depth;
-    nd.down = ws.down;
-    if (in_lds == 2) {
-      // the chain walks of the geometry (and the listing that later reuses
-      // depth / down) run on LDS copies
-      int32_t *ip = reinterpret_cast<int32_t *>(dyn);
-      nd.parent = ip;
-      nd.depth = ip + V;
-      nd.down = ip + 2 * V;
-      for (int i = tid; i < V; i += AT) nd.parent[i] = i == tid ? par0 : t.parent[i];
-    }
-    nd.F = ws.F;
-    nd.cnt = ws.cnt;
-    nd.cap = ws.cap;
-    nd.W = ws.W;
-    nd.w = ws.w;
-    nd.path = on_path;
   }
   __syncthreads();
 
@@ -484,8 +1007,7 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
   // down to its nearest active leaf)
   // The eligible prices of each block (finite, at most alpha_max) and their
   // key range are counted here too, so one exchange gives every total.
-  const double amax = p.alpha_max;
-  int64_t path_tok = 0, sum_F = 0, sum_red = 0, total = 0, n_elig = 0;
+  int64_t path_tok = 0, sum_F = 0, sum_red = 0, total = 0;
   uint64_t kmin = ~0ull, kmax = 0ull;
   for (int i = tid; i < V; i += AT) {
     int best = 0x7fffffff;
@@ -498,72 +1020,49 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
     const int n = i == tid ? nf0 : nd.n_full[i];
     const int c = i == tid ? nk0 : nd.n_kept[i];
     const bool on = nd.path[i] != 0;
-    if (in_lds == 1) on_path[i] = nd.path[i];
-    // the most a block can keep: a Path* block is restored to n_i by
-    // rehydration (or keeps c_i when evicted tokens stay lost), any other
-    // block only ever loses tokens
-    const int cap = on && p.rehydrate ? n : c;
-    nd.cap[i] = cap;
+    on_path[i] = nd.path[i];
     if (on && p.k_protect == 0) {
-      // pinned (invariant (i), full protection)
-      k_out[i] = cap;
-      path_tok += cap;
+      // pinned (invariant (i), full protection): restored by rehydration to
+      // n_i, or c_i when evicted tokens stay lost
+      const int keep = p.rehydrate ? n : c;
+      k_out[i] = keep;
+      path_tok += keep;
+      nd.cap[i] = keep;
       nd.F[i] = 0;
       nd.W[i] = 0.0;
       nd.w[i] = 0.0;
       nd.cnt[i] = 0;
       continue;
     }
-    // s_i = clip(sigmoid(.), 0, 1) lies in [0, 1]
-    const float sf = i == tid ? s0 : s_in[i];
-    if (!(sf == sf)) atomicOr(&s_err, 2);
-    else if (!(sf >= 0.f && sf <= 1.f)) atomicOr(&s_err, 4);
-    const double s = (double)sf;
-    // Eq. 3 at the ratio floor r_min, capped; a Path* block under floor
-    // protection keeps at least k_protect
-    int f = max(p.k_min, min(p.l_tail, n));
-    f = max(f, (int)floor(p.r_min * (double)n));
-    f = min(cap, min(n, f));
-    if (on) f = max(f, min(cap, p.k_protect));
-    nd.F[i] = f;
-    // the Eq. 2 weight without alpha, in the same operation order as
-    // ((eta^[off path] * s^gamma) * e^{-lambda_d d}) * e^{-lambda_Delta Delta}
-    double w = (on ? 1.0 : p.eta) * pow_gamma(s, p.gamma);
-    w = w * (di < kDecay ? s_dexp[di] : exp(-p.lambda_d * (double)di));
-    w = w * (best < kDecay ? s_texp[best] : exp(-p.lambda_delta * (double)best));
-    // -0 (s = -0 with an odd gamma) as +0: the Pressure order compares bit
-    // patterns, in which -0 would rank above every positive weight
-    w = w == 0.0 ? 0.0 : w;
-    nd.w[i] = w;
-    const double W = w * (double)n;
-    nd.W[i] = W;
-    sum_F += f;
+    int err = 0;
+    const NodeTerms r = node_terms(p, s_dexp, s_texp, on, n, c, s0, di, best, err);
+    if (err) atomicOr(&s_err, err);
+    nd.cap[i] = r.cap;
+    nd.F[i] = r.F;
+    nd.W[i] = r.W;
+    nd.w[i] = r.w;
+    nd.cnt[i] = r.cnt;
+    sum_F += r.F;
     // Pressure lowers only off-path blocks
-    if (!on) sum_red += f - min(p.k_min, c);
-    const int cnt = eligible(f, cap, W, amax);
-    nd.cnt[i] = cnt;
-    total += cnt;
-    if (cnt > 0) {
-      const uint64_t lo = (uint64_t)__double_as_longlong(price(f + 1, W));
-      const uint64_t hi = (uint64_t)__double_as_longlong(price(f + cnt, W));
-      kmin = lo < kmin ? lo : kmin;
-      kmax = hi > kmax ? hi : kmax;
-      ++n_elig;
+    if (!on) sum_red += r.F - min(p.k_min, c);
+    total += r.cnt;
+    if (r.cnt > 0) {
+      kmin = r.lo < kmin ? r.lo : kmin;
+      kmax = r.hi > kmax ? r.hi : kmax;
     }
   }
   {
-    // five sums and two minima in one exchange (finite positive keys are
+    // four sums and two minima in one exchange (finite positive keys are
     // below 2^63: the maximum is taken as the minimum of INT64_MAX - key)
-    int64_t v[7] = {path_tok, sum_F, sum_red, total, n_elig,
+    int64_t v[6] = {path_tok, sum_F, sum_red, total,
                     kmin == ~0ull ? INT64_MAX : (int64_t)kmin, INT64_MAX - (int64_t)kmax};
-    block_reduce_n<5>(v, sm, V);
+    block_reduce_n<4>(v, sm, V);
     path_tok = v[0];
     sum_F = v[1];
     sum_red = v[2];
     total = v[3];
-    n_elig = v[4];
-    kmin = (uint64_t)v[5];
-    kmax = (uint64_t)(INT64_MAX - v[6]);
+    kmin = (uint64_t)v[4];
+    kmax = (uint64_t)(INT64_MAX - v[5]);
   }
   if (s_err) {
     if (tid == 0) status_error(status, (s_err & 2) ? ARBOR_ENONFINITE : ARBOR_EINVAL);
@@ -580,382 +1079,117 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
       return;
     }
 
-    // Beyond LDS mode the blocks with eligible prices are listed once (F,
-    // cnt, W side by side in the workspace), so that the search rounds, the
-    // listing and the fill below visit only them.
-    const int32_t *eF = nd.F;
-    int32_t *eC = nd.cnt;
-    const double *eW = nd.W;
-    int ne = V;
-    if constexpr (MODE != 1) {
-      const int per = (V + AT - 1) / AT;
-      const int i0 = min(V, tid * per), i1 = min(V, i0 + per);
-      int64_t mine = 0;
+    // -- few nodes: narrow on exact counts --------------------------------
+    // Keys ka < kb with count(<= ka) <= E < count(<= kb), from ka = the
+    // smallest price's key - 1 (-1 when that price is 0: below every
+    // price) and kb = the largest one's.  Each round tests ka, kb and 62
+    // keys between them, one key per lane; the waves split the blocks,
+    // whose exact counts (last_le) are added in wave order.  It stops when
+    // kb - ka = 1 (the answer is kb) or when at most 64 prices lie in
+    // (ka, kb], which are then listed and ranked by one wave.
+    int64_t ka = (int64_t)kmin - 1, kb = (int64_t)kmax;
+    int64_t cA = 0, cB = 0;
+    bool counted = false;
+    uint64_t answer = 0;
+    bool found = false;
+    for (int round = 0;; ++round) {
+      if (kb - ka <= 1) {
+        answer = (uint64_t)kb;
+        found = true;
+        break;
+      }
+      if (counted && cB - cA <= kWave) break;
+      const uint64_t span = (uint64_t)(kb - ka);
+      const uint64_t m = (uint64_t)lane;
+      const int64_t x = lane == kWave - 1
+                            ? kb
+                            : ka + (int64_t)((span / (kWave - 1)) * m +
+                                             ((span % (kWave - 1)) * m) / (kWave - 1));
+      double c = 0.0;
+      if (x >= 0) {
+        const double xv = key_value((uint64_t)x);
 #pragma unroll 4
-      for (int i = i0; i < i1; ++i) mine += nd.cnt[i] > 0 ? 1 : 0;
-      int64_t tot;
-      int64_t off = block_exclusive_scan<int64_t>(mine, sm, &tot);
-      for (int i = i0; i < i1; ++i) {
-        const int cnt = nd.cnt[i];
-        if (cnt > 0) {
-          ws.eF[off] = nd.F[i];
-          ws.eC[off] = cnt;
-          ws.eW[off] = nd.W[i];
-          ++off;
+        for (int i = wave; i < V; i += AT / kWave) {
+          const int cnt = nd.cnt[i];
+          const int F = nd.F[i];
+          const int mm = cnt > 0 ? last_le(xv, F, cnt, nd.W[i]) : F;
+          c += (double)(mm - F);
         }
+      }
+      s_part[tid] = c;
+      __syncthreads();
+      if (tid < kWave) {
+        double sum = 0.0;
+        for (int w = 0; w < AT / kWave; ++w) sum += s_part[w * kWave + tid];
+        s_cnt[round & 1][tid] = sum;
+        s_x[round & 1][tid] = (uint64_t)x;
       }
       __syncthreads();
-      eF = ws.eF;
-      eC = ws.eC;
-      eW = ws.eW;
-      ne = (int)tot;
-    }
-
-    // -- bracket: keys a (few prices <= a) and b (enough prices <= b) --------
-    // The rounded count is off by at most two prices per node, so
-    //   approx(a) <= E - 2 n_elig - 1  ->  exact(a) <= E - 1, and
-    //   approx(b) >= E + 2 n_elig + 1  ->  exact(b) >= E + 1:
-    // the order statistic lies in (a, b].  Each end has its own bracket
-    // [lo, hi] around the crossing of its threshold; waves 0..7 test 32
-    // points (four each) inside the bracket of a, waves 8..15 inside that of b.
-    const double t_lo = (double)(E - 2 * n_elig - 1);
-    const double t_hi = (double)(E + 2 * n_elig + 1);
-    // a: approx(a_lo) <= t_lo < approx(a_hi); b: approx(b_lo) < t_hi, and
-    // b_hi == kmax (exact count = total > E) or approx(b_hi) >= t_hi
-    // (a zero price -- W_i infinite -- leaves no key below the smallest one:
-    // then a stays "below everything" and every price up to b is listed)
-    const bool a_none = kmin == 0;
-    uint64_t a_lo = a_none ? 0 : kmin - 1, a_hi = kmax, b_lo = a_lo, b_hi = kmax;
-    double ca = 0.0, cb = (double)total;
-    bool a_done = a_none || t_lo < 0.0, b_done = a_none || t_hi > (double)total;
-    // stop once the bracket holds few prices: listing them costs less than
-    // another round
-    const double enough = 256.0 + 4.0 * (double)n_elig;
-    static_assert(2 * kSearchPts == kWave, "one lane per test point in the narrowing");
-    // (trees held in LDS skip this search: their exact counts below cost
-    // about as much as the rounded ones)
-    for (int round = 0; MODE != 1 && !(a_done && b_done) && cb - ca > enough; ++round) {
-      const bool end_b = wave >= kSearchWaves;
-      const int q0 = (wave % kSearchWaves) * kPtsPerWave;
-      const uint64_t lo = end_b ? b_lo : a_lo;
-      const uint64_t span = (end_b ? b_hi : a_hi) - lo;
-      uint64_t x[kPtsPerWave];
-      double xv[kPtsPerWave], c[kPtsPerWave];
-#pragma unroll
-      for (int p = 0; p < kPtsPerWave; ++p) {
-        x[p] = split_point<kSearchPts>(lo, span, q0 + p);
-        xv[p] = key_value(x[p]);
-        c[p] = 0.0;
-      }
-      if (!(end_b ? b_done : a_done)) {
-        // (selects rather than a branch, so that the loads of several nodes
-        // are in flight together; blocks without prices add 0)
-#pragma unroll 4
-        for (int e = lane; e < ne; e += kWave) {
-          const int cnt = eC[e];
-          const int F = eF[e];
-          const double W = eW[e];
-#pragma unroll
-          for (int p = 0; p < kPtsPerWave; ++p) {
-            const double y = approx_le(xv[p], F, cnt, W);
-            c[p] += cnt > 0 ? y : 0.0;
-          }
-        }
-#pragma unroll
-        for (int p = 0; p < kPtsPerWave; ++p) c[p] = wave_sum(c[p]);
-      }
-      if (lane < kPtsPerWave) {
-        const int slot = (end_b ? kSearchPts : 0) + q0 + lane;
-        double cl = c[0];
-        uint64_t xl = x[0];
-#pragma unroll
-        for (int p = 1; p < kPtsPerWave; ++p) {
-          cl = lane == p ? c[p] : cl;
-          xl = lane == p ? x[p] : xl;
-        }
-        s_cnt[round & 1][slot] = cl;
-        s_x[round & 1][slot] = xl;
-      }
-      __syncthreads();
-      // every wave narrows both brackets from the same counts: lane l holds
-      // point l of end a (l < 32) or point l - 32 of end b.  The points ascend
-      // and the counts with them, so the points at or below a threshold form
-      // a prefix: one ballot finds its last point and the first point after it.
-      const uint64_t xq = s_x[round & 1][lane];
+      // the keys ascend and their counts with them: the last one with
+      // count <= E is the new ka (lane 0 at least), the first one above E
+      // the new kb (lane 63 at least)
       const double cq = s_cnt[round & 1][lane];
-      const uint64_t m_a = ballot(lane < kSearchPts && cq <= t_lo);
-      const uint64_t m_b = ballot(lane >= kSearchPts && cq < t_hi) >> kSearchPts;
-      constexpr uint64_t kAll = (1ull << kSearchPts) - 1;
-      if (!a_done) {
-        if (m_a) {
-          const int ql = 63 - __builtin_clzll(m_a);
-          a_lo = lane_value(xq, ql);
-          ca = lane_value(cq, ql);
-        }
-        const uint64_t above = ~m_a & kAll;
-        if (above) {
-          const uint64_t xh = lane_value(xq, __builtin_ctzll(above));
-          a_hi = xh < a_hi ? xh : a_hi;
-        }
-        if (a_hi - a_lo <= 1) a_done = true;
-      }
-      if (!b_done) {
-        if (m_b) {
-          const uint64_t xl = lane_value(xq, kSearchPts + 63 - __builtin_clzll(m_b));
-          b_lo = xl > b_lo ? xl : b_lo;
-        }
-        const uint64_t reach = ~m_b & kAll;
-        if (reach) {
-          const int qh = kSearchPts + __builtin_ctzll(reach);
-          b_hi = lane_value(xq, qh);
-          cb = lane_value(cq, qh);
-        }
-        if (b_hi - b_lo <= 1) b_done = true;
-      }
+      const int64_t xq = (int64_t)s_x[round & 1][lane];
+      const uint64_t le = ballot(cq <= (double)E);
+      const int qa = 63 - __builtin_clzll(le);
+      const int qb = __builtin_ctzll(~le);
+      ka = lane_value(xq, qa);
+      kb = lane_value(xq, qb);
+      cA = (int64_t)lane_value(cq, qa);
+      cB = (int64_t)lane_value(cq, qb);
+      counted = true;
     }
-    const uint64_t a = a_lo, b = b_hi;
-
-    if constexpr (MODE == 1) {
-      // -- few nodes: narrow on exact counts --------------------------------
-      // Keys ka < kb with count(<= ka) <= E < count(<= kb), from ka = the
-      // smallest price's key - 1 (-1 when that price is 0: below every
-      // price) and kb = the largest one's.  Each round tests ka, kb and 62
-      // keys between them, one key per lane; the waves split the blocks,
-      // whose exact counts (last_le) are added in wave order.  It stops when
-      // kb - ka = 1 (the answer is kb) or when at most 64 prices lie in
-      // (ka, kb], which are then listed and ranked by one wave.
-      int64_t ka = a_none ? -1 : (int64_t)a, kb = (int64_t)b;
-      int64_t cA = 0, cB = 0;
-      bool counted = false;
-      uint64_t answer = 0;
-      bool found = false;
-      for (int round = 0;; ++round) {
-        if (kb - ka <= 1) {
-          answer = (uint64_t)kb;
-          found = true;
-          break;
-        }
-        if (counted && cB - cA <= kWave) break;
-        const uint64_t span = (uint64_t)(kb - ka);
-        const uint64_t m = (uint64_t)lane;
-        const int64_t x = lane == kWave - 1
-                              ? kb
-                              : ka + (int64_t)((span / (kWave - 1)) * m +
-                                               ((span % (kWave - 1)) * m) / (kWave - 1));
-        double c = 0.0;
-        if (x >= 0) {
-          const double xv = key_value((uint64_t)x);
-#pragma unroll 4
-          for (int i = wave; i < V; i += AT / kWave) {
-            const int cnt = nd.cnt[i];
-            const int F = nd.F[i];
-            const int mm = cnt > 0 ? last_le(xv, F, cnt, nd.W[i]) : F;
-            c += (double)(mm - F);
-          }
-        }
-        s_part[tid] = c;
-        __syncthreads();
-        if (tid < kWave) {
-          double sum = 0.0;
-          for (int w = 0; w < AT / kWave; ++w) sum += s_part[w * kWave + tid];
-          s_cnt[round & 1][tid] = sum;
-          s_x[round & 1][tid] = (uint64_t)x;
-        }
-        __syncthreads();
-        // the keys ascend and their counts with them: the last one with
-        // count <= E is the new ka (lane 0 at least), the first one above E
-        // the new kb (lane 63 at least)
-        const double cq = s_cnt[round & 1][lane];
-        const int64_t xq = (int64_t)s_x[round & 1][lane];
-        const uint64_t le = ballot(cq <= (double)E);
-        const int qa = 63 - __builtin_clzll(le);
-        const int qb = __builtin_ctzll(~le);
-        ka = lane_value(xq, qa);
-        kb = lane_value(xq, qb);
-        cA = (int64_t)lane_value(cq, qa);
-        cB = (int64_t)lane_value(cq, qb);
-        counted = true;
+    if (!found) {
+      // the cB - cA <= 64 prices in (ka, kb], placed by a block scan and
+      // ranked by one wave
+      uint64_t *const lst = cand_lds;
+      const double av1 = ka >= 0 ? key_value((uint64_t)ka) : 0.0, bv1 = key_value((uint64_t)kb);
+      int m_lo = 0, m_hi = 0;
+      double Wt = 0.0;
+      if (tid < V && nd.cnt[tid] > 0) {
+        const int F = nd.F[tid], cnt = nd.cnt[tid];
+        Wt = nd.W[tid];
+        m_lo = ka >= 0 ? last_le(av1, F, cnt, Wt) : F;
+        m_hi = last_le(bv1, F, cnt, Wt);
       }
-      if (!found) {
-        // the cB - cA <= 64 prices in (ka, kb], placed by a block scan and
-        // ranked by one wave
-        uint64_t *const lst = cand_lds;
-        const double av1 = ka >= 0 ? key_value((uint64_t)ka) : 0.0, bv1 = key_value((uint64_t)kb);
-        int m_lo = 0, m_hi = 0;
-        double Wt = 0.0;
-        if (tid < V && nd.cnt[tid] > 0) {
-          const int F = nd.F[tid], cnt = nd.cnt[tid];
-          Wt = nd.W[tid];
-          m_lo = ka >= 0 ? last_le(av1, F, cnt, Wt) : F;
-          m_hi = last_le(bv1, F, cnt, Wt);
+      int64_t tot;
+      const int64_t off = block_exclusive_scan<int64_t>((int64_t)(m_hi - m_lo), sm, &tot);
+      for (int j = m_lo; j < m_hi; ++j)
+        lst[off + (j - m_lo)] = (uint64_t)__double_as_longlong(price(j + 1, Wt));
+      __syncthreads();
+      if (wave == 0) {
+        const int n = (int)tot;
+        const int64_t r = E - cA;
+        const uint64_t key = lane < n ? lst[lane] : ~0ull;
+        int less = 0, leq = 0;
+        for (int q = 0; q < n; ++q) {
+          const uint64_t kq = lane_value(key, q);
+          less += kq < key ? 1 : 0;
+          leq += kq <= key ? 1 : 0;
         }
-        int64_t tot;
-        const int64_t off = block_exclusive_scan<int64_t>((int64_t)(m_hi - m_lo), sm, &tot);
-        for (int j = m_lo; j < m_hi; ++j)
-          lst[off + (j - m_lo)] = (uint64_t)__double_as_longlong(price(j + 1, Wt));
-        __syncthreads();
-        if (wave == 0) {
-          const int n = (int)tot;
-          const int64_t r = E - cA;
-          const uint64_t key = lane < n ? lst[lane] : ~0ull;
-          int less = 0, leq = 0;
-          for (int q = 0; q < n; ++q) {
-            const uint64_t kq = lane_value(key, q);
-            less += kq < key ? 1 : 0;
-            leq += kq <= key ? 1 : 0;
-          }
-          if (lane < n && less <= r && r < leq) s_x[0][0] = key;
-        }
-        __syncthreads();
-        answer = s_x[0][0];
-      }
-      const double cut = key_value(answer);
-      for (int i = tid; i < V; i += AT) {
-        if (nd.path[i] && p.k_protect == 0) continue;
-        const int F = nd.F[i];
-        const double W = nd.W[i];
-        k_out[i] = W > 0.0 ? last_lt(cut, F, nd.cap[i] - F, W) : F;
-      }
-      return;
-    }
-
-    // -- list the prices in (a, b] and count those <= a exactly -------------
-    // per listed block e: first listed j - 1 in depth[e], how many in
-    // down[e], offset in eC[e] (the geometry fields are no longer needed)
-    const double av = key_value(a), bv = key_value(b);
-    int64_t below = 0, run = 0;
-    for (int base = 0; base < ne; base += AT) {
-      const int e = base + tid;
-      int m_lo = 0, m_hi = 0, F = 0;
-      if (e < ne) {
-        const int cnt = eC[e];
-        if (cnt > 0) {
-          F = eF[e];
-          const double W = eW[e];
-          m_lo = a_none ? F : last_le(av, F, cnt, W);
-          m_hi = last_le(bv, F, cnt, W);
-        }
-      }
-      // offsets of the listed prices, and the count of prices <= a
-      const int64_t v2[2] = {(int64_t)(m_hi - m_lo), (int64_t)(m_lo - F)};
-      int64_t ex[2], tot[2];
-      block_exclusive_scan_n<2>(v2, ex, tot, sm, ne - base);
-      if (e < ne) {
-        nd.depth[e] = m_lo;
-        nd.down[e] = m_hi - m_lo;
-        eC[e] = (int)(run + ex[0]);
-      }
-      run += tot[0];
-      below += tot[1];
-    }
-    const int64_t total_c = run;
-    if (total_c > ws.buf_cap || total_c > 0x7fffffff) {
-      if (tid == 0) status_error(status, ARBOR_EWORKSPACE);
-      return;
-    }
-    // the listed prices and their order statistic (every listed key lies in
-    // (a, b]); LDS and workspace buffers take separate code paths, so that
-    // each compiles to its own kind of memory instruction
-    auto order_stat = [&](uint64_t *cand, uint64_t *cand2) __attribute__((always_inline)) {
-      // one thread per node over its listed prices (a few per node: the
-      // bracket holds a few hundred in all)
-      for (int e = tid; e < ne; e += AT) {
-        const int nl = nd.down[e];
-        const int m_lo = nd.depth[e], o = eC[e];
-        const double W = eW[e];
-        for (int j = 0; j < nl; ++j)
-          cand[o + j] = (uint64_t)__double_as_longlong(price(m_lo + 1 + j, W));
+        if (lane < n && less <= r && r < leq) s_x[0][0] = key;
       }
       __syncthreads();
-      return select_rank(cand, cand2, total_c, E - below, sm, true, a_none ? 0 : a + 1, b);
-    };
-    const uint64_t prefix = total_c <= kCandLds ? order_stat(cand_lds, cand_lds + kCandLds)
-                                                : order_stat(ws.buf0, ws.buf1);
-    const double cut = key_value(prefix);
+      answer = s_x[0][0];
+    }
+    const double cut = key_value(answer);
     for (int i = tid; i < V; i += AT) {
       if (nd.path[i] && p.k_protect == 0) continue;
       const int F = nd.F[i];
       const double W = nd.W[i];
-      // the prices below the cut (none when W_i = 0: all infinite)
       k_out[i] = W > 0.0 ? last_lt(cut, F, nd.cap[i] - F, W) : F;
     }
     return;
   }
 
-  // ---- pressure: drain the lowest-priority blocks (Alg. 2) ---------------
-  int64_t excess = sum_F - b_off;
-  if (sum_red < excess) {
-    for (int i = tid; i < V; i += AT) {
-      if (!nd.path[i]) k_out[i] = min(p.k_min, nd.n_kept[i]);
-      else if (p.k_protect > 0) k_out[i] = nd.F[i];   // Path* keeps its floor
-    }
-    if (tid == 0) status_warn(status, ARBOR_OVER_BUDGET);
-    return;
-  }
-  // smallest priority value W* whose cumulative reducible count reaches excess
-  uint64_t prefix = 0, pmask = 0;
-  int64_t need = excess;
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    for (int b = tid; b < 256; b += AT) hist64[b] = 0;
-    __syncthreads();
-    for (int i = tid; i < V; i += AT) {
-      if (nd.path[i]) continue;
-      const uint64_t key = (uint64_t)__double_as_longlong(nd.w[i]);
-      if ((key & pmask) != prefix) continue;
-      const int red = nd.F[i] - min(p.k_min, nd.n_kept[i]);
-      if (red > 0) atomicAdd(&hist64[(key >> shift) & 255ull], (unsigned long long)red);
-    }
-    __syncthreads();
-    int chosen = 255;
-    int64_t acc = 0;
-    for (int b = 0; b < 256; ++b) {
-      const int64_t h = (int64_t)hist64[b];
-      if (acc + h >= need) {
-        chosen = b;
-        break;
-      }
-      acc += h;
-    }
-    need -= acc;
-    prefix |= (uint64_t)chosen << shift;
-    pmask |= 255ull << shift;
-    __syncthreads();
-  }
-  // nodes below W* drain fully; nodes at W* drain in id order until `need`
-  int64_t run = 0;
-  for (int base = 0; base < V; base += AT) {
-    const int i = base + tid;
-    int64_t red = 0;
-    uint64_t key = 0;
-    const bool off = i < V && !nd.path[i];
-    if (off) {
-      red = nd.F[i] - min(p.k_min, nd.n_kept[i]);
-      key = (uint64_t)__double_as_longlong(nd.w[i]);
-    }
-    const bool tie = off && key == prefix;
-    int64_t tot;
-    const int64_t ex = block_exclusive_scan<int64_t>(tie ? red : 0, sm, &tot);
-    if (off) {
-      int kk = nd.F[i];
-      if (key < prefix) {
-        kk -= (int)red;
-      } else if (tie) {
-        const int64_t before = run + ex;
-        if (before < need) kk -= (int)min<int64_t>(red, need - before);
-      }
-      k_out[i] = kk;
-    } else if (i < V && p.k_protect > 0) {
-      k_out[i] = nd.F[i];                                // Path* keeps its floor
-    }
-    run += tot;
-  }
+  pressure_drain(p, V, nd.path, [&](int i) { return nd.F[i]; }, nd.w, nd.n_kept, sum_red, sum_F - b_off, k_out, status, sm);
 }
 
 }  // namespace
 
 size_t allocate_workspace(const arbor_sizes_t *sz) {
-  return (size_t)sz->num_nodes * (5 * 4 + 8 * 2 + 2 * 4 + 8 + 64) +
-         (size_t)sz->num_tokens * 16 + 8192;
+  const size_t V = (size_t)sz->num_nodes;
+  return V * (4 + sizeof(NodeRec) + 8) + (V / kNodeThreads + 1) * sizeof(NodeSums) + 8192;
 }
 
 // Per-event statistics of the device-side controller (arbor_walk): one
@@ -1010,22 +1244,6 @@ int launch_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_a
                     void *workspace, size_t workspace_bytes, hipStream_t stream, int gate) {
   Tree t = make_tree(tree);
   if (t.V <= 0) return ARBOR_OK;
-  Carve cv(workspace, workspace_bytes);
-  AllocWs ws;
-  ws.depth = cv.take<int32_t>(t.V);
-  ws.down = cv.take<int32_t>(t.V);
-  ws.F = cv.take<int32_t>(t.V);
-  ws.cnt = cv.take<int32_t>(t.V);
-  ws.cap = cv.take<int32_t>(t.V);
-  ws.W = cv.take<double>(t.V);
-  ws.w = cv.take<double>(t.V);
-  ws.eF = cv.take<int32_t>(t.V);
-  ws.eC = cv.take<int32_t>(t.V);
-  ws.eW = cv.take<double>(t.V);
-  ws.buf0 = cv.take<uint64_t>((size_t)t.N);
-  ws.buf1 = cv.take<uint64_t>((size_t)t.N);
-  ws.buf_cap = t.N;
-  if (!cv.ok) return ARBOR_EWORKSPACE;
   AllocParams p{params->alpha_max, params->gamma, params->lambda_d, params->lambda_delta,
                 params->eta, params->r_min, params->k_min, params->l_tail,
                 params->lazy_rehydration, params->k_protect, {}, {}};
@@ -1033,25 +1251,47 @@ int launch_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_a
     p.dexp[i] = exp(-params->lambda_d * (double)i);
     p.texp[i] = exp(-params->lambda_delta * (double)i);
   }
-  const int in_lds = t.V <= kLdsNodes ? 1 : (t.V <= kGeoNodes ? 2 : 0);
-  const void *fn = in_lds == 1 ? reinterpret_cast<const void *>(&allocate_kernel<1>)
-                               : (in_lds == 2 ? reinterpret_cast<const void *>(&allocate_kernel<2>)
-                                              : reinterpret_cast<const void *>(&allocate_kernel<0>));
-  const size_t lds = (in_lds == 1 ? ((size_t)t.V * kNodeBytes + 15) / 16 * 16 + AT * 8
-                                  : (in_lds == 2 ? ((size_t)t.V * 12 + 15) / 16 * 16 : 0)) +
-                     2 * (size_t)kCandLds * sizeof(uint64_t);
-  // more than 64 KiB of dynamic LDS has to be allowed explicitly
-  static_assert(kGeoNodes * 12 + 2 * kCandLds * 8 <= 150 * 1024, "within the LDS of a CU");
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return ARBOR_EHIP;
-#define ARBOR_ALLOC_LAUNCH(M)                                                                   \
-  hipLaunchKernelGGL(allocate_kernel<M>, dim3(1), dim3(AT), lds, stream, t, active, n_active,    \
-                     (int64_t)budget_tokens, s, p, k_out, delta_out, on_path_out, status, ws, gate)
-  if (in_lds == 1) ARBOR_ALLOC_LAUNCH(1);
-  else if (in_lds == 2) ARBOR_ALLOC_LAUNCH(2);
-  else ARBOR_ALLOC_LAUNCH(0);
-#undef ARBOR_ALLOC_LAUNCH
+  if (t.V <= kLdsNodes) {
+    const size_t lds = ((size_t)t.V * kNodeBytes + 15) / 16 * 16 + (kWave + AT) * 8;
+    static_assert(kLdsNodes <= AT && kLdsNodes * kNodeBytes + (kWave + AT) * 8 + 16 <= 64 * 1024,
+                  "one thread per node, and no more LDS than a launch may take unasked");
+    hipLaunchKernelGGL(allocate_kernel, dim3(1), dim3(AT), lds, stream, t, active, n_active,
+                       (int64_t)budget_tokens, s, p, k_out, delta_out, on_path_out, status, gate);
+    return hip_ok(hipGetLastError());
+  }
+  const int n_wg = (t.V + kNodeThreads - 1) / kNodeThreads;
+  Carve cv(workspace, workspace_bytes);
+  AllocWs ws;
+  ws.down = cv.take<int32_t>(t.V);
+  ws.rec = cv.take<NodeRec>(t.V);
+  ws.w = cv.take<double>(t.V);
+  ws.sums = cv.take<NodeSums>(n_wg);
+  ws.gated = cv.take<int32_t>(1);
+  if (!cv.ok) return ARBOR_EWORKSPACE;
+#define ARBOR_NODES_ARGS                                                                         \
+  t, active, n_active, (int64_t)budget_tokens, s, p, k_out, delta_out, on_path_out, status, ws, gate
+  if (t.V <= kGeoNodes) {
+    const size_t lds = (size_t)t.V * 8;
+    // more than 64 KiB of dynamic LDS has to be allowed explicitly
+    static_assert(kGeoNodes * 8 <= 140 * 1024, "within the LDS of a CU");
+    if (lds > 60 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(&alloc_nodes<true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return ARBOR_EHIP;
+    hipLaunchKernelGGL(alloc_nodes<true>, dim3(n_wg), dim3(kNodeThreads), lds, stream,
+                       ARBOR_NODES_ARGS);
+  } else {
+    hipLaunchKernelGGL(alloc_path, dim3(1), dim3(AT), 0, stream, t, active, n_active, status, ws);
+    hipLaunchKernelGGL(alloc_nodes<false>, dim3(n_wg), dim3(kNodeThreads), 0, stream,
+                       ARBOR_NODES_ARGS);
+  }
+#undef ARBOR_NODES_ARGS
+  if (t.V <= kCutThreads * kRegNodes)
+    hipLaunchKernelGGL(alloc_cut<true>, dim3(1), dim3(kCutThreads), 0, stream, t, (int64_t)budget_tokens, p,
+                       k_out, on_path_out, status, ws, n_wg);
+  else
+    hipLaunchKernelGGL(alloc_cut<false>, dim3(1), dim3(kCutThreads), 0, stream, t, (int64_t)budget_tokens,
+                       p, k_out, on_path_out, status, ws, n_wg);
   return hip_ok(hipGetLastError());
 }
 
