@@ -28,6 +28,8 @@
 // No atomics anywhere, so A is bitwise reproducible.  The reduction dimension
 // (head_dim) is permuted identically in both MFMA operands so that every lane
 // reads one contiguous quarter of a K or Q row (64 B for bf16 d = 128).
+#include <type_traits>
+
 #include "arbor_internal.h"
 #include "mfma_ops.h"
 
@@ -216,11 +218,11 @@ __device__ __forceinline__ float piece_op<float>(const uint4 &p, int c) {
   return __uint_as_float(c == 0 ? p.x : (c == 1 ? p.y : (c == 2 ? p.z : p.w)));
 }
 
-// Streaming kernel.  One workgroup of four waves per (observer, slice layer,
-// kv head, RGW groups of up to 16 NRB query rows), RGW = 1, 2 or 4.  Wave w
-// is (row group w % RGW, key split w / RGW): the 4 / RGW key splits take the
-// chain's 16-key sub-pages round-robin (split x takes sub-pages x, x + 4 /
-// RGW, ...), and every wave holds the Q of its row group in registers.  The
+// Streaming kernel.  One workgroup of RGW * KSW waves per (observer, slice
+// layer, kv head, RGW groups of up to 16 NRB query rows), RGW = 1, 2 or 4.
+// Wave w is (row group w % RGW, key split w / RGW): the KSW key splits take the
+// chain's 16-key sub-pages round-robin (split x takes sub-pages x, x + KSW,
+// ...), and every wave holds the Q of its row group in registers.  The
 // RGW waves of a key split work on the same sub-page at each step: each loads
 // a part of it into their shared ring of LDS slots and they meet at a barrier
 // before reading it, so a key tile moves from L2 to LDS once for RGW row
@@ -237,14 +239,14 @@ __device__ __forceinline__ float piece_op<float>(const uint4 &p, int c) {
 // are stored XOR-permuted by r, so the sixteen lanes of an MFMA operand read
 // (keys 0..15, one piece each) hit distinct banks.  A wave waits only for its
 // own loads; the barrier (RGW > 1 only) does not wait for memory.
-template <class T, int D, int NRB, int RGW>
-__global__ __launch_bounds__(256, 3) void score_attn(ScoreArgs a) {
+template <class T, int D, int NRB, int RGW, int KSW>
+__global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) void score_attn(
+    ScoreArgs a) {
   using O = Op<T>;
   using KT = KTile<T, D>;
   using Buf = KBuf<T, D>;
   constexpr int R = KT::R, RQ = KT::RQ, KS = KT::KS, SPP = KT::SPP, ND = KT::ND;
   constexpr int ROWS = 16 * NRB;            // rows of one wave (a row group)
-  constexpr int KSW = 4 / RGW;              // key splits of the workgroup
   constexpr int NDW = (ND + RGW - 1) / RGW; // direct loads of a wave per tile (at most)
   static_assert(RGW == 1 || RGW == 2 || RGW == 4, "row groups per workgroup");
   constexpr float kFloor = -1e30f;
@@ -737,15 +739,16 @@ __global__ __launch_bounds__(256, 3) void score_attn(ScoreArgs a) {
 struct ObsChain {
   int64_t len, subs;
   int depth;
-  bool ok;
+  bool ok, deep;   // deep: not ok because the chain is too long
 };
 __device__ ObsChain walk_chain(const Tree &t, int j, int32_t *anc_out) {
-  ObsChain r{0, 0, 0, true};
+  ObsChain r{0, 0, 0, true, false};
   int d = 0;
   for (int x = j; x >= 0; x = t.parent[x]) {
     if (d >= MAXD || (x > 0 && (t.parent[x] < 0 || t.parent[x] >= x)) ||
         (x == 0 && t.parent[x] != -1)) {
       r.ok = false;
+      r.deep = d >= MAXD;
       break;
     }
     const int c = t.n_kept[x];
@@ -815,12 +818,16 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
   }
   if (tid == 0) s_err = 0;
   constexpr bool in_lds = IN_LDS;
+  // one observer over a tree beyond LDS: the launch's other workgroups check
+  // the nodes (check_nodes) and its chain is the list of credited blocks, so
+  // nothing here visits the whole tree (9,841 blocks: 14.1 -> 6.9 us)
+  const bool lone = !IN_LDS && a.n_obs == 1;
   // trees beyond LDS take eight of the thread's nodes at a time: their loads
   // in flight together (the flag stores of one node would otherwise hold up
   // the next node's loads, which share the counter of outstanding memory
   // operations); a tree in LDS takes at most two nodes per thread
   constexpr int kGrp = IN_LDS ? 1 : 8;
-  for (int ib = tid; ib < t.V; ib += kGrp * nt) {
+  for (int ib = tid; ib < t.V && !lone; ib += kGrp * nt) {
     int par[kGrp], nf[kGrp], c[kGrp];
 #pragma unroll
     for (int u = 0; u < kGrp; ++u) {
@@ -868,7 +875,7 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
       } else {
         int32_t *ao = anc + (int64_t)o * MAXD;
         const ObsChain r = walk_chain(t, j, ao);
-        if (!r.ok) atomicOr(&s_err, 2);
+        if (!r.ok) atomicOr(&s_err, lone && !r.deep ? 1 : 2);
         len = r.len;
         subs = r.subs;
         odepth[o] = r.ok ? r.depth : -1;
@@ -883,12 +890,13 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
           int ctx = 0;
           for (int e = 0; e <= r.depth; ++e) {
             const int x = ao[e];
-            if (e < r.depth) flag[x] = 1;
+            if (!lone && e < r.depth) flag[x] = 1;
+            if (lone) cred[1 + e] = x;
             nctx[x] = ctx;
             ndep[x] = e;
             ctx += t.n_kept[x];
           }
-          if (a.self_window) flag[j] = 1;
+          if (!lone && a.self_window) flag[j] = 1;
         }
       }
     }
@@ -930,6 +938,8 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
       if (f) cred[1 + crun + cx] = i;
       crun += ctot;
     }
+  } else if (lone) {
+    crun = s_err ? 0 : odepth[0] + (a.self_window ? 1 : 0);
   } else {
     // each thread takes a run of consecutive blocks (their flags loaded eight
     // at a time), and one scan places the runs
@@ -1040,6 +1050,18 @@ __global__ __launch_bounds__(256) void score_tables(ScoreArgs a) {
 // chain or a workspace too small leaves o's table unwritten (the setup
 // reports the error, and no later kernel runs).
 constexpr int kPrepObs = 512;
+
+// The setup's check of nodes [base, base + blockDim.x).
+__device__ __forceinline__ void check_nodes(const ScoreArgs &a, int base) {
+  const Tree &t = a.t;
+  const int i = base + (int)threadIdx.x;
+  if (i >= t.V) return;
+  const int par = t.parent[i], n = t.n_full[i], c = t.n_kept[i];
+  if (status_failed(a.status)) return;
+  if (!(i == 0 ? par == -1 : (par >= 0 && par < i)) || c < 0 || c > n)
+    status_error(a.status, ARBOR_EINVAL);
+}
+
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap,
                                                    int64_t *__restrict__ pbase,
@@ -1056,6 +1078,10 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
   if (blockIdx.x == 0) {
     setup_body<IN_LDS>(a, part_cap, pbase, fbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx,
                        ndep, cred);
+    return;
+  }
+  if ((int)blockIdx.x > a.n_obs) {          // (one observer over a large tree)
+    check_nodes(a, ((int)blockIdx.x - a.n_obs - 1) * (int)blockDim.x);
     return;
   }
   __shared__ ChainLds ch;
@@ -1117,16 +1143,20 @@ __global__ __launch_bounds__(256) void score_fold(ScoreArgs a, const int64_t *__
   const float *src = a.part + pb;
   float *dst = a.part + fb;
   for (int x = blockIdx.y * blockDim.x + threadIdx.x; x < credited; x += gridDim.y * blockDim.x) {
-    // eight loads in flight, added in slab order
+    // up to sixteen loads in flight, added in slab order
     float acc = 0.f;
     int sl = 0;
-    for (; sl + 8 <= nslab; sl += 8) {
-      float v[8];
+    auto add = [&](auto n) __attribute__((always_inline)) {
+      constexpr int N = decltype(n)::value;
+      float v[N];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(sl + u) * len + x];
+      for (int u = 0; u < N; ++u) v[u] = src[(int64_t)(sl + u) * len + x];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc += v[u];
-    }
+      for (int u = 0; u < N; ++u) acc += v[u];
+      sl += N;
+    };
+    while (sl + 16 <= nslab) add(std::integral_constant<int, 16>{});
+    if (sl + 8 <= nslab) add(std::integral_constant<int, 8>{});
     for (; sl < nslab; ++sl) acc += src[(int64_t)sl * len + x];
     dst[x] = acc;
   }
@@ -1283,67 +1313,102 @@ __global__ __launch_bounds__(256) void score_final(Tree t, const float *__restri
   block_final(t, i, A, rows_seen, fa.v_in, fa.u_in, fa.th0, fa.th1, fa.th2, fa.a_out, fa.s_out);
 }
 
-template <class T, int D, int NRB>
-void launch_attn_rg(int RGW, dim3 grid, hipStream_t stream, const ScoreArgs &a) {
-  switch (RGW) {
-    case 1: hipLaunchKernelGGL((score_attn<T, D, NRB, 1>), grid, dim3(256), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((score_attn<T, D, NRB, 2>), grid, dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL((score_attn<T, D, NRB, 4>), grid, dim3(256), 0, stream, a); break;
-  }
-}
+// The shape of a launch: 16-row blocks of a wave (NRB), row groups (RGW) and key
+// splits (KSW) of a workgroup, and what follows from them.
+struct Shape {
+  int nrb, rgw, ksw, n_rg, n_slab;
+};
 
-// Fewer than the full 16 NRB rows fit in one row group: one group, no sharing.
-template <class T, int D>
-void launch_attn_nb(int NRB, int RGW, dim3 grid, hipStream_t stream, const ScoreArgs &a) {
-  constexpr int cap = sizeof(T) == 2 ? 4 : 2;
-  if (NRB < cap) {
-    if (NRB == 1) hipLaunchKernelGGL((score_attn<T, D, 1, 1>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((score_attn<T, D, 2, 1>), grid, dim3(256), 0, stream, a);
-    return;
-  }
-  launch_attn_rg<T, D, cap>(RGW, grid, stream, a);
-}
-
-void launch_attn(int dtype, int D, int NRB, int RGW, dim3 grid, hipStream_t stream,
-                 const ScoreArgs &a) {
-  if (dtype == ARBOR_BF16) {
-    if (D == 128) launch_attn_nb<__bf16, 128>(NRB, RGW, grid, stream, a);
-    else launch_attn_nb<__bf16, 64>(NRB, RGW, grid, stream, a);
-  } else {
-    if (D == 128) launch_attn_nb<float, 128>(NRB, RGW, grid, stream, a);
-    else launch_attn_nb<float, 64>(NRB, RGW, grid, stream, a);
-  }
-}
-
-// 16-row blocks of a row group: enough for all the rows up to 64 (32 for fp32,
-// whose operands take four times the registers), a power of two.  A wave
-// holds the Q of its group's rows; 64 rows (bf16) keep three waves per SIMD.
 // Row groups per workgroup: they share its key tiles and one partial slab (a
 // power of two, as in the kernel's template).
 int rg_per_wg(int n_rg) { return n_rg >= 4 ? 4 : (n_rg >= 2 ? 2 : 1); }
 
-int row_blocks(int rows_total, int dtype) {
+// Enough 16-row blocks in a row group for all the rows up to 64 (32 for fp32,
+// whose operands take four times the registers), a power of two: a wave holds
+// the Q of its group's rows; 64 rows (bf16) keep three waves per SIMD.
+Shape stream_shape(int rows_total, int dtype) {
   const int cap = dtype == ARBOR_BF16 ? 4 : 2;
-  int nrb = 1;
-  while (nrb < cap && 16 * nrb < rows_total) nrb *= 2;
-  return nrb;
+  Shape s;
+  s.nrb = 1;
+  while (s.nrb < cap && 16 * s.nrb < rows_total) s.nrb *= 2;
+  s.n_rg = (rows_total + 16 * s.nrb - 1) / (16 * s.nrb);
+  s.rgw = s.nrb == cap ? rg_per_wg(s.n_rg) : 1;
+  s.ksw = 4 / s.rgw;
+  s.n_slab = (s.n_rg + s.rgw - 1) / s.rgw;
+  return s;
+}
+
+// Few observers (a search step scores its new leaf) leave most of the chip
+// idle in the shape above: up to kSplitWgs workgroups of it, one row group
+// holds 16 rows and a workgroup has more key splits, so a wave takes fewer and
+// shorter steps.  One leaf of an 8B-shaped deep tree (128 rows, 1,536 keys, 16
+// workgroups) takes 17.7 us instead of 38.7 (four row groups and four key
+// splits 24.6; one row group 16.3, but more slabs to fold: 15 us more per
+// eight steps of a walk); 16 leaves of 32 rows (256 workgroups) 12.9 instead of
+// 11.4, so they stay with the other shape.
+constexpr int kSplitWgs = 128;
+Shape split_shape(int rows_total, int dtype) {
+  Shape s;
+  s.nrb = 1;
+  s.n_rg = (rows_total + 15) / 16;
+  s.rgw = s.n_rg >= 2 ? 2 : 1;
+  s.ksw = dtype == ARBOR_BF16 ? 8 : 4;
+  s.n_slab = (s.n_rg + s.rgw - 1) / s.rgw;
+  return s;
+}
+
+Shape score_shape(int rows_total, int dtype, int planes, int n_obs) {
+  const Shape s = stream_shape(rows_total, dtype);
+  return (int64_t)n_obs * planes * s.n_slab <= kSplitWgs ? split_shape(rows_total, dtype) : s;
+}
+
+template <class T, int D>
+void launch_attn_shape(const Shape &s, dim3 grid, hipStream_t stream, const ScoreArgs &a) {
+  constexpr int cap = sizeof(T) == 2 ? 4 : 2;
+  constexpr int kw = sizeof(T) == 2 ? 8 : 4;
+#define ARBOR_ATTN(N, R, K)                                                                    \
+  if (s.nrb == N && s.rgw == R && s.ksw == K) {                                                 \
+    hipLaunchKernelGGL((score_attn<T, D, N, R, K>), grid, dim3(64 * R * K), 0, stream, a);      \
+    return;                                                                                      \
+  }
+  ARBOR_ATTN(1, 1, 4)
+  ARBOR_ATTN(2, 1, 4)
+  ARBOR_ATTN(cap, 1, 4)
+  ARBOR_ATTN(cap, 2, 2)
+  ARBOR_ATTN(cap, 4, 1)
+  ARBOR_ATTN(1, 1, kw)
+  ARBOR_ATTN(1, 2, kw)
+#undef ARBOR_ATTN
+}
+
+void launch_attn(int dtype, int D, const Shape &s, dim3 grid, hipStream_t stream,
+                 const ScoreArgs &a) {
+  if (dtype == ARBOR_BF16) {
+    if (D == 128) launch_attn_shape<__bf16, 128>(s, grid, stream, a);
+    else launch_attn_shape<__bf16, 64>(s, grid, stream, a);
+  } else {
+    if (D == 128) launch_attn_shape<float, 128>(s, grid, stream, a);
+    else launch_attn_shape<float, 64>(s, grid, stream, a);
+  }
 }
 
 }  // namespace
 
 size_t score_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   const int rows_total = g->q_per_kv * sz->window;
-  const int NRB = row_blocks(rows_total, g->dtype);
-  const int n_rg = (rows_total + 16 * NRB - 1) / (16 * NRB);
-  const int RGW = rg_per_wg(n_rg);
   const size_t nobs = (size_t)(sz->max_observers > 0 ? sz->max_observers : 0);
-  const size_t slabs = (size_t)sz->n_slice * g->num_kv_heads * ((n_rg + RGW - 1) / RGW);
+  const size_t planes = (size_t)sz->n_slice * g->num_kv_heads;
+  const Shape st = stream_shape(rows_total, g->dtype), sp = split_shape(rows_total, g->dtype);
+  const size_t slabs = planes * st.n_slab;
+  // the split shape is taken for up to kSplitWgs workgroups of the other one
+  const size_t few = std::min(nobs, (size_t)kSplitWgs / std::max(slabs, (size_t)1));
   size_t b = 0;
   // offsets, counts, chains, credited-block flags and list (each carve
   // rounds up to 256 B)
   b += nobs * (8 * 3 + 4 * 4) + nobs * MAXD * 4 + (size_t)sz->num_nodes * 16 + 14 * 256;
   // partials and their folded sums
-  b += nobs * (slabs + 1) * (size_t)sz->max_context * 4 + 256;
+  b += std::max(nobs * (slabs + 1), few * (planes * sp.n_slab + 1)) * (size_t)sz->max_context * 4 +
+       256;
   // sub-page tables: at most one ragged sub-page per chain node
   b += nobs * ((size_t)sz->max_context / 16 + MAXD + 1) * 16 + 256;
   return b;
@@ -1369,10 +1434,9 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
   a.S = n_slice;
   for (int e = 0; e < 8; ++e) a.slice[e] = e < n_slice ? slice_layers[e] : 0;
   const int rows_total = pl.G * window;
-  const int NRB = row_blocks(rows_total, geom->dtype);
-  a.n_rg = (rows_total + 16 * NRB - 1) / (16 * NRB);
-  const int RGW = rg_per_wg(a.n_rg);
-  a.n_slab = (a.n_rg + RGW - 1) / RGW;
+  const Shape shape = score_shape(rows_total, geom->dtype, n_slice * pl.Hkv, n_obs);
+  a.n_rg = shape.n_rg;
+  a.n_slab = shape.n_slab;
   const float scale = params->softmax_scale > 0.f ? params->softmax_scale
                                                   : 1.0f / sqrtf((float)geom->head_dim);
   a.sl2 = scale * kLog2e;
@@ -1411,7 +1475,9 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
     const int64_t need = std::max<int64_t>(t.V, n_obs);
     const int st = (int)std::min<int64_t>(1024, (need + kWave - 1) / kWave * kWave);
     if (n_obs <= kPrepObs) {
-      const dim3 grid((unsigned)n_obs + 1), blk((unsigned)std::max(st, 256));
+      const dim3 blk((unsigned)(n_obs == 1 && t.V > kSetupLds ? 256 : std::max(st, 256)));
+      const unsigned checks = n_obs == 1 && t.V > kSetupLds ? (t.V + blk.x - 1) / blk.x : 0;
+      const dim3 grid((unsigned)n_obs + 1 + checks);
       if (t.V <= kSetupLds)
         hipLaunchKernelGGL(score_prep<true>, grid, blk, 0, stream, a, part_cap, pbase, fbase,
                            tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
@@ -1430,7 +1496,7 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
     const int n_planes = n_slice * pl.Hkv * a.n_slab;
     const dim3 grid((unsigned)(((n_planes + kXcds - 1) / kXcds) * n_obs * kXcds));
     timing_begin(geom, ARBOR_KERNEL_SCORE_ATTN, stream);
-    launch_attn(geom->dtype, geom->head_dim, NRB, RGW, grid, stream, a);
+    launch_attn(geom->dtype, geom->head_dim, shape, grid, stream, a);
     timing_end(geom, ARBOR_KERNEL_SCORE_ATTN, stream);
     hipLaunchKernelGGL(score_fold, dim3(n_obs, 8), dim3(256), 0, stream, a, fbase);
     // at most V credited blocks, and at most MAXD per observer
