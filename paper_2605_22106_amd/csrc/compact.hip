@@ -196,11 +196,14 @@ struct PlanEmit {
   }
 };
 
-// workgroups below node_blocks select and plan kSelWaves nodes each (one per
-// wave; their other waves exit at once, so the selections spread over as many
-// CUs as with small workgroups), the last one scans with all kScanWaves waves
-constexpr int kSelWaves = 4;
+// workgroups below node_blocks select and plan SW nodes each, one per wave, the
+// last one scans with all kScanWaves waves.  Up to kSpreadNodes nodes SW = 4
+// (a workgroup's other waves exit at once), so that the selections spread over
+// as many CUs as with small workgroups; more nodes fill the chip anyway, and
+// every wave selects: 9,841 nodes take 11.1 us instead of 12.8.
+constexpr int kSpreadNodes = 2048;
 constexpr int kScanWaves = 16;
+template <int SW>
 __global__ __launch_bounds__(kScanWaves * kWave) void select_plan(Tree t, Pool pl, const float *__restrict__ A,
                                                    const int32_t *__restrict__ k, int l_tail,
                                                    int n_sinks, int mode,
@@ -212,13 +215,13 @@ __global__ __launch_bounds__(kScanWaves * kWave) void select_plan(Tree t, Pool p
                                                    int32_t *__restrict__ changed,
                                                    int32_t *__restrict__ meta, int node_blocks,
                                                    int32_t *status) {
-  __shared__ SelectLds<kSelWaves> lds;
+  __shared__ SelectLds<SW> lds;
   if ((int)blockIdx.x == node_blocks) {
     scan_nodes(t, pl, k, push_base, changed, meta, status);
     return;
   }
-  if ((int)(threadIdx.x >> 6) >= kSelWaves) return;
-  const int i = blockIdx.x * kSelWaves + (threadIdx.x >> 6);
+  if ((int)(threadIdx.x >> 6) >= SW) return;
+  const int i = blockIdx.x * SW + (threadIdx.x >> 6);
   if (i >= t.V) return;
   const int64_t tb = t.tok_off[i];
   int first = INT_MAX;
@@ -401,12 +404,16 @@ int launch_select_compact(const arbor_geom_t *geom, arbor_tree_t *tree, arbor_po
   int32_t *changed = cv.take<int32_t>(t.V);
   int32_t *meta = cv.take<int32_t>(4);
   if (!cv.ok) return ARBOR_EWORKSPACE;
-  const int node_blocks = (t.V + kSelWaves - 1) / kSelWaves;
+  const int sw = t.V <= kSpreadNodes ? 4 : kScanWaves;
+  const int node_blocks = (t.V + sw - 1) / sw;
   timing_begin(geom, ARBOR_KERNEL_SELECT, stream);
-  hipLaunchKernelGGL(select_plan, dim3(node_blocks + 1), dim3(kScanWaves * kWave), 0, stream, t,
-                     pl, A, k,
-                     params->l_tail, params->n_sinks, params->select_mode, sel_pos, mv_src, mv_dst,
-                     first_moved, push_base, changed, meta, node_blocks, status);
+#define ARBOR_SELECT_LAUNCH(SW)                                                                 \
+  hipLaunchKernelGGL(select_plan<SW>, dim3(node_blocks + 1), dim3(kScanWaves * kWave), 0, stream, \
+                     t, pl, A, k, params->l_tail, params->n_sinks, params->select_mode, sel_pos,  \
+                     mv_src, mv_dst, first_moved, push_base, changed, meta, node_blocks, status)
+  if (sw == 4) ARBOR_SELECT_LAUNCH(4);
+  else ARBOR_SELECT_LAUNCH(kScanWaves);
+#undef ARBOR_SELECT_LAUNCH
   timing_end(geom, ARBOR_KERNEL_SELECT, stream);
   const int64_t planes = (int64_t)t.V * pl.L * pl.Hkv;
   const int move_blocks = (int)((planes + 3) / 4 < 8192 ? (planes + 3) / 4 : 8192);
