@@ -12,12 +12,13 @@
 //     one 256-thread workgroup per (row, chunk) streams its chunk into a
 //     partial (m, S, T); a second kernel merges a row's partials in chunk
 //     order (enough workgroups to cover the chip even for few rows);
-//   top-K, K <= KMAX: the same chunks also keep their own K largest values
-//     (the values above a bound taken from the threads' maxima, then a radix
-//     select over their order-preserving 32-bit keys, 8 bits per LDS
-//     histogram pass); the row's top K lie among those candidates, so a merge
-//     workgroup per row selects the K-th largest among them and sums the top
-//     K against the merged (m, S);
+//   top-K, K <= KMAX: the same chunks also keep their own K largest values,
+//     found among the few values above a bound taken from the threads'
+//     maxima; the row's top K lie among those candidates, so a merge
+//     workgroup per row finds them and sums them against the merged (m, S).
+//     Up to RMAX such values are ranked against one another (one thread
+//     each), more go through a radix select over their order-preserving
+//     32-bit keys, 8 bits per LDS histogram pass;
 //   top-K, larger K: one workgroup per row finds the K-th largest logit by a
 //     radix select over the whole row (11 + 11 + 10 bits), then sums the top
 //     and the rest in one more pass.
@@ -52,6 +53,18 @@ __device__ __forceinline__ Ent ent_merge(Ent a, Ent b) {
     r.t += (b.t + d * b.s) * f;
   }
   return r;
+}
+
+// The lanes' entries merged, in every lane: the wave's max, then each lane's
+// sums moved onto it once and added (two exponentials and three lane
+// reductions, against two and three shuffles for each of six merge steps).
+__device__ __forceinline__ Ent wave_ent(Ent e) {
+  const float m = wave_allreduce(e.m, [](float x, float y) { return fmaxf(x, y); });
+  if (m == -__builtin_inff()) return Ent{m, 0.f, 0.f};
+  const bool any = e.m > -__builtin_inff();
+  const float d = any ? e.m - m : 0.f;
+  const float f = any ? __builtin_amdgcn_exp2f(d) : 0.f;
+  return Ent{m, wave_sum(e.s * f), wave_sum((e.t + d * e.s) * f)};
 }
 
 // elements of one 16-byte load, widened to float
@@ -114,12 +127,11 @@ __device__ __forceinline__ void for_vecs(const uint4 *row, int64_t v0, int64_t v
   }
 }
 
-// (m, S, T) of vectors [v0, v1) of a row over the whole workgroup (every
+// (m, S, T) of the vectors that vecs hands out over the whole workgroup (every
 // thread gets the result); *bad_flag is set (LDS) if any value is NaN or
 // infinite.
-template <class T, int NT, class Each>
-__device__ Ent block_stats(const uint4 *row, int64_t v0, int64_t v1, bool &bad, Ent *s_ent,
-                           int *bad_flag, Each &&each) {
+template <class T, int NT, class Vecs, class Each>
+__device__ Ent block_stats(Vecs &&vecs, bool &bad, Ent *s_ent, int *bad_flag, Each &&each) {
   constexpr int N = Vec<T>::N;
   const int tid = threadIdx.x;
   Ent e{-__builtin_inff(), 0.f, 0.f};
@@ -150,14 +162,10 @@ __device__ Ent block_stats(const uint4 *row, int64_t v0, int64_t v1, bool &bad, 
       e.t = __builtin_fmaf(d, p, e.t);
     }
   };
-  for_vecs<NT>(row, v0, v1, add);
+  vecs(add);
   if (bad) atomicOr(bad_flag, 1);
-  // butterfly within the wave, then the waves in order
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    Ent o{__shfl_xor(e.m, off, kWave), __shfl_xor(e.s, off, kWave), __shfl_xor(e.t, off, kWave)};
-    e = ent_merge(e, o);
-  }
+  // within the wave, then the waves in order
+  e = wave_ent(e);
   if (lane_id() == 0) s_ent[tid >> 6] = e;
   __syncthreads();
   Ent all = s_ent[0];
@@ -189,7 +197,9 @@ __global__ __launch_bounds__(UT) void uncert_topk(const T *__restrict__ logits, 
 
   // ---- pass 1: (m, S, T) of the whole row -------------------------------
   bool bad = false;
-  const Ent all = block_stats<T, UT>(row, 0, nvec, bad, s_ent, &s_bad, [](float) {});
+  const Ent all = block_stats<T, UT>(
+      [&](auto &&f) __attribute__((always_inline)) { for_vecs<UT>(row, 0, nvec, f); }, bad, s_ent,
+      &s_bad, [](float) {});
   if (s_bad) {
     if (tid == 0) status_error(status, ARBOR_ENONFINITE);
     return;
@@ -297,11 +307,29 @@ __global__ __launch_bounds__(PT) void uncert_part(const T *__restrict__ logits, 
   if (threadIdx.x == 0) s_bad = 0;
   __syncthreads();
   bool bad = false;
-  const Ent e = block_stats<T, PT>(row, v0, v1, bad, s_ent, &s_bad, [](float) {});
+  const Ent e = block_stats<T, PT>(
+      [&](auto &&f) __attribute__((always_inline)) { for_vecs<PT>(row, v0, v1, f); }, bad, s_ent,
+      &s_bad, [](float) {});
   if (threadIdx.x == 0) part[(int64_t)r * n_chunk + c] = make_float4(e.m, e.s, e.t, s_bad ? 1.f : 0.f);
 }
 
-// Full vocabulary, part 2: one wave per row merges its partials in chunk order.
+// (m, S, T) of a row's chunk partials over one wave; bad: some chunk holds a
+// value that is not finite
+__device__ __forceinline__ Ent row_ent(const float4 *part, int n_chunk, bool &bad) {
+  Ent e{-__builtin_inff(), 0.f, 0.f};
+  bool b = false;
+  for (int c = lane_id(); c < n_chunk; c += kWave) {
+    const float4 p = part[c];
+    b |= p.w != 0.f;
+    e = ent_merge(e, Ent{p.x, p.y, p.z});
+  }
+  bad = ballot(b) != 0;
+  return wave_ent(e);
+}
+
+// Full vocabulary, part 2: one wave per row merges its partials, a lane for
+// each chunk (one after another in one lane: 6.1 us for 85 rows of 15 chunks,
+// now 2.9).
 __global__ __launch_bounds__(256) void uncert_merge(const float4 *__restrict__ part, int n_rows,
                                                     int n_chunk, int64_t vocab,
                                                     const int32_t *__restrict__ dst,
@@ -309,14 +337,10 @@ __global__ __launch_bounds__(256) void uncert_merge(const float4 *__restrict__ p
                                                     int32_t *status) {
   if (status_failed(status)) return;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= n_rows || lane_id() != 0) return;
-  Ent all{-__builtin_inff(), 0.f, 0.f};
-  bool bad = false;
-  for (int c = 0; c < n_chunk; ++c) {
-    const float4 p = part[(int64_t)r * n_chunk + c];
-    bad |= p.w != 0.f;
-    all = ent_merge(all, Ent{p.x, p.y, p.z});
-  }
+  if (r >= n_rows) return;
+  bool bad;
+  const Ent all = row_ent(part + (int64_t)r * n_chunk, n_chunk, bad);
+  if (lane_id() != 0) return;
   if (bad) {
     status_error(status, ARBOR_ENONFINITE);
     return;
@@ -366,6 +390,25 @@ __device__ uint32_t block_select(Visit &&visit, int &need, unsigned *hist, int *
   return prefix;
 }
 
+// Rank (0 = largest) of thread tid's key among the n <= RMAX keys of s_key,
+// equal keys in list order; every thread of the workgroup calls it.
+constexpr int RMAX = PT;
+constexpr int kSorted = 1 << 30;   // flag of a candidate count: the list is in rank order
+constexpr int kRankK = RMAX / 3;   // largest K whose candidates are tried this way
+__device__ __forceinline__ int block_rank(const uint32_t *s_key, int n) {
+  const int tid = threadIdx.x;
+  const uint32_t k = tid < n ? s_key[tid] : 0u;
+  int r = 0;
+  for (int j = 0; j < n; j += 4) {
+    const uint4 q = *reinterpret_cast<const uint4 *>(s_key + j);   // (past n: not counted)
+    const uint32_t v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      r += j + u < n && (v[u] > k || (v[u] == k && j + u < tid)) ? 1 : 0;
+  }
+  return r;
+}
+
 constexpr int CMAX = 2048;  // candidates selected in LDS by the chunk workgroups
 constexpr int MMAX = 1024;  // candidates selected in LDS by the merge workgroups
 
@@ -373,12 +416,16 @@ constexpr int MMAX = 1024;  // candidates selected in LDS by the merge workgroup
 // chunk's K largest values (all of them if the chunk holds fewer), with their
 // count.  A bound from the threads' maxima (below) lies at or under the
 // chunk's K-th largest value, so only the values at or above it can be among
-// the chunk's top K.  Those few are copied to LDS in a fixed order, a radix
-// select finds the K-th largest among them, and the values above it (in
-// order) and then the needed copies of it are written: the K-th largest is
-// always the last of a full list.  If too many values tie at the bound, the
-// radix select runs over the chunk itself.
-template <class T>
+// the chunk's top K.  Up to RMAX of them go to LDS and are written by rank
+// (so their order there does not matter).  More are copied to LDS in a fixed
+// order, a radix select finds the K-th largest among them, and the values
+// above it (in order) and then the needed copies of it are written: the K-th
+// largest is always the last of a full list.  If too many values tie at the
+// bound, the radix select runs over the chunk itself.
+// RES: the chunk has at most PVEC vectors per thread, which stay in registers
+// for every pass over them.
+constexpr int PVEC = 8;
+template <class T, bool RES>
 __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ logits, int64_t vocab,
                                                        int n_chunk, int top_k,
                                                        float4 *__restrict__ part,
@@ -392,19 +439,37 @@ __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ log
   __shared__ __attribute__((aligned(16))) uint32_t s_key[CMAX];
   __shared__ unsigned hist[256];
   __shared__ int s_pick[2];
+  __shared__ int s_n;
   __shared__ int64_t s_scan[17];
-  if (status_failed(status)) return;
   const int c = blockIdx.x, r = blockIdx.y;
   const int tid = threadIdx.x;
   const uint4 *row = reinterpret_cast<const uint4 *>(logits + (int64_t)r * vocab);
   const int64_t nvec = vocab / N;
   const int64_t per = (nvec + n_chunk - 1) / n_chunk;
   const int64_t v0 = min(nvec, (int64_t)c * per), v1 = min(nvec, v0 + per);
-  if (tid == 0) s_bad = 0;
+  uint4 reg[RES ? PVEC : 1];
+  if constexpr (RES) {
+    // (issued together with the status word; past the end clamped, not used)
+#pragma unroll
+    for (int j = 0; j < PVEC; ++j)
+      reg[j] = row[min(v0 + tid + (int64_t)j * PT, nvec - 1)];
+  }
+  if (status_failed(status)) return;
+  if (tid == 0) s_bad = s_n = 0;
   __syncthreads();
+  // this thread's vectors in a fixed order (v0 + tid, v0 + tid + PT, ...)
+  auto vecs = [&](auto &&f) __attribute__((always_inline)) {
+    if constexpr (RES) {
+#pragma unroll
+      for (int j = 0; j < PVEC; ++j)
+        if (v0 + tid + (int64_t)j * PT < v1) f(reg[j]);
+    } else {
+      for_vecs<PT>(row, v0, v1, f);
+    }
+  };
   bool bad = false;
   uint32_t kmax = 0u;             // 0: this thread holds no value
-  const Ent e = block_stats<T, PT>(row, v0, v1, bad, s_ent, &s_bad, [&](float x) {
+  const Ent e = block_stats<T, PT>(vecs, bad, s_ent, &s_bad, [&](float x) {
     const uint32_t k = ordered_key(x);
     kmax = k > kmax ? k : kmax;
   });
@@ -412,9 +477,8 @@ __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ log
   if (tid == 0) part[slot] = make_float4(e.m, e.s, e.t, s_bad ? 1.f : 0.f);
   if (s_bad) return;                                  // uniform: settled at the stats' sync
   float *out = cand + slot * KMAX;
-  // this thread's values in a fixed order (vectors v0 + tid, v0 + tid + PT, ...)
   auto visit = [&](auto &&f) __attribute__((always_inline)) {
-    for_vecs<PT>(row, v0, v1, [&](const uint4 &u) __attribute__((always_inline)) {
+    vecs([&](const uint4 &u) __attribute__((always_inline)) {
       float x[N];
       VV::get(u, x);
 #pragma unroll
@@ -440,6 +504,25 @@ __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ log
 #pragma unroll
   for (int w = 1; w < PT / kWave; ++w) theta = min(theta, s_key[w]);
   __syncthreads();                                  // s_key is reused below
+  // the values at or above the bound, ranked when few (for a larger K they
+  // hardly ever are)
+  if (top_k <= kRankK) {
+    visit([&](uint32_t key) __attribute__((always_inline)) {
+      if (key >= theta) {
+        const int at = atomicAdd(&s_n, 1);
+        if (at < RMAX) s_key[at] = key;
+      }
+    });
+    __syncthreads();
+    const int n = s_n;
+    if (n <= RMAX) {
+      const int rk = block_rank(s_key, n);
+      if (tid < n && rk < top_k) out[rk] = key_float(s_key[tid]);
+      if (tid == 0) cand_n[slot] = min(n, top_k) | kSorted;
+      return;
+    }
+    __syncthreads();
+  }
   int mine = 0;
   visit([&](uint32_t key) __attribute__((always_inline)) { mine += key >= theta ? 1 : 0; });
   int64_t n_c;
@@ -503,6 +586,9 @@ __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ log
 // the row's top K has fewer than K larger values in its chunk), so the top K
 // of the candidates are the row's: ranked in LDS when few, else found by a
 // radix select.  The rest of the mass is the "other" outcome.
+// Bound by latency: 16 rows of 31 chunks, K = 40, take 10.8 us (18.1 with the
+// chunks' last values as the only bound, which leaves some 900 candidates for
+// the radix select; 23.2 with the chunks merged one after another as well).
 __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict__ part,
                                                         const float *__restrict__ cand,
                                                         const int32_t *__restrict__ cand_n,
@@ -520,30 +606,55 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
   if (status_failed(status)) return;
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
+  const float *cr = cand + (int64_t)r * n_chunk * KMAX;
+  const int32_t *cn = cand_n + (int64_t)r * n_chunk;
+  // candidate j of chunk c sits at cr[c * KMAX + j], j < cn[c]
+  // candidate counts in LDS when the chunks are few enough
+  __shared__ int s_cn[PT];
+  __shared__ uint32_t s_lb;
+  __shared__ int s_n;
   if (tid == 0) {
-    Ent all{-__builtin_inff(), 0.f, 0.f};
-    int bad = 0;
-    for (int c = 0; c < n_chunk; ++c) {
-      const float4 p = part[(int64_t)r * n_chunk + c];
-      bad |= p.w != 0.f;
-      all = ent_merge(all, Ent{p.x, p.y, p.z});
+    s_lb = 0u;
+    s_n = 0;
+  }
+  __syncthreads();
+  if (tid < kWave) {
+    bool bad;
+    const Ent all = row_ent(part + (int64_t)r * n_chunk, n_chunk, bad);
+    if (tid == 0) {
+      s_all = all;
+      s_bad = bad;
     }
-    s_all = all;
-    s_bad = bad;
+  }
+  // a lower bound on the row's K-th largest: a chunk that kept K candidates
+  // holds K values at or above its own K-th largest, which it wrote last; and
+  // of the chunks' j-th largest values the ceil(K / j)-th largest has K values
+  // at or above it (with j for about half the chunks, a few values per chunk
+  // are left where the first bound leaves most of the candidates)
+  const int jth = min(top_k, (2 * top_k + n_chunk - 1) / n_chunk);
+  const int mth = (top_k + jth - 1) / jth;
+  for (int c = tid; c < n_chunk; c += PT) {
+    const int nf = cn[c], n = nf & (kSorted - 1);
+    const float last = cr[(int64_t)c * KMAX + top_k - 1];
+    const float vj = cr[(int64_t)c * KMAX + jth - 1];
+    if (c < PT) {
+      s_cn[c] = n;
+      s_key[c] = (nf & kSorted) && n >= jth ? ordered_key(vj) : 0u;
+    }
+    if (n == top_k) atomicMax(&s_lb, ordered_key(last));
   }
   __syncthreads();
   if (s_bad) {
     if (tid == 0) status_error(status, ARBOR_ENONFINITE);
     return;
   }
+  if (n_chunk <= RMAX) {
+    const int rk = block_rank(s_key, n_chunk);
+    if (tid < n_chunk && rk == mth - 1) atomicMax(&s_lb, s_key[tid]);
+    __syncthreads();
+  }
   const Ent all = s_all;
-  const float *cr = cand + (int64_t)r * n_chunk * KMAX;
-  const int32_t *cn = cand_n + (int64_t)r * n_chunk;
-  // candidate j of chunk c sits at cr[c * KMAX + j], j < cn[c]
-  // candidate counts in LDS when the chunks are few enough
-  __shared__ int s_cn[PT];
-  if (n_chunk <= PT) s_cn[tid] = tid < n_chunk ? cn[tid] : 0;
-  __syncthreads();
+  const uint32_t lb = s_lb;
   float st = 0.f, tt = 0.f;
   auto add = [&](float x) __attribute__((always_inline)) {
     const float d = x * kLog2e - all.m;
@@ -553,15 +664,42 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
   };
   int need = 0;
   uint32_t tau = 0u;
-  // a lower bound on the row's K-th largest: a chunk that kept K candidates
-  // holds K values at or above its own K-th largest, which it wrote last
-  __shared__ uint32_t s_lb;
-  if (tid == 0) s_lb = 0u;
+  // the candidates at or above lb, ranked when few (then their sums run in rank
+  // order, whatever order they were found in)
+  bool few = n_chunk <= PT && top_k <= kRankK;
+  if (few) {
+    for (int q0 = 0; q0 < n_chunk * top_k; q0 += 4 * PT) {
+      float v[4];
+      int cq[4], jq[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = min(q0 + u * PT + tid, n_chunk * top_k - 1);
+        cq[u] = q / top_k;
+        jq[u] = q - cq[u] * top_k;
+        v[u] = cr[(int64_t)cq[u] * KMAX + jq[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t key = ordered_key(v[u]);
+        if (q0 + u * PT + tid < n_chunk * top_k && jq[u] < s_cn[cq[u]] && key >= lb) {
+          const int at = atomicAdd(&s_n, 1);
+          if (at < RMAX) s_key[at] = key;
+        }
+      }
+    }
+    __syncthreads();
+    few = s_n <= RMAX;
+  }
+  if (few) {
+    const int n = s_n;
+    const int rk = block_rank(s_key, n);
+    const uint32_t key = tid < n ? s_key[tid] : 0u;
+    __syncthreads();
+    if (tid < n && rk < top_k) s_key[rk] = key;
+    __syncthreads();
+    if (tid < top_k) add(key_float(s_key[tid]));
+  } else {
   __syncthreads();
-  for (int c = tid; c < n_chunk; c += PT)
-    if (cn[c] == top_k) atomicMax(&s_lb, ordered_key(cr[(int64_t)c * KMAX + top_k - 1]));
-  __syncthreads();
-  const uint32_t lb = s_lb;
   static_assert(KMAX == PT, "one candidate slot per thread");
   // thread t looks at candidate t of every chunk (loads of eight chunks in
   // flight; unconditional, since slot t always lies in the buffer)
@@ -604,7 +742,7 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
     auto visit_v = [&](auto &&f) __attribute__((always_inline)) {
       for (int q = tid; q < n_chunk * KMAX; q += PT) {
         const int c = q / KMAX, j = q % KMAX;
-        if (j < cn[c]) f(cr[q]);
+        if (j < (cn[c] & (kSorted - 1))) f(cr[q]);
       }
     };
     auto visit = [&](auto &&f) __attribute__((always_inline)) {
@@ -615,6 +753,7 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
     visit_v([&](float x) __attribute__((always_inline)) {
       if (ordered_key(x) > tau) add(x);
     });
+  }
   }
   st = block_sum_f(st, s_f);
   tt = block_sum_f(tt, s_f);
@@ -675,14 +814,17 @@ int launch_uncertainty(const void *logits, int32_t dtype, int32_t n_rows, int64_
     float *cand = cv.take<float>(slots * KMAX);
     int32_t *cand_n = cv.take<int32_t>(slots);
     if (!cv.ok) return ARBOR_EWORKSPACE;
-    if (bf)
-      hipLaunchKernelGGL(uncert_topk_part<__bf16>, dim3(ch, n_rows), dim3(PT), 0, stream,
-                         static_cast<const __bf16 *>(logits), vocab, ch, top_k, part, cand,
-                         cand_n, status);
-    else
-      hipLaunchKernelGGL(uncert_topk_part<float>, dim3(ch, n_rows), dim3(PT), 0, stream,
-                         static_cast<const float *>(logits), vocab, ch, top_k, part, cand,
-                         cand_n, status);
+    const int64_t nvec = vocab / (bf ? 8 : 4);
+    const bool res = (nvec + ch - 1) / ch <= (int64_t)PVEC * PT;
+#define ARBOR_TOPK_PART(T, R)                                                                   \
+  hipLaunchKernelGGL((uncert_topk_part<T, R>), dim3(ch, n_rows), dim3(PT), 0, stream,            \
+                     static_cast<const T *>(logits), vocab, ch, top_k, part, cand, cand_n,       \
+                     status)
+    if (bf && res) ARBOR_TOPK_PART(__bf16, true);
+    else if (bf) ARBOR_TOPK_PART(__bf16, false);
+    else if (res) ARBOR_TOPK_PART(float, true);
+    else ARBOR_TOPK_PART(float, false);
+#undef ARBOR_TOPK_PART
     hipLaunchKernelGGL(uncert_topk_merge, dim3(n_rows), dim3(PT), 0, stream, part, cand, cand_n,
                        ch, top_k, vocab, dst, u_out, n_out, status);
     return hip_ok(hipGetLastError());
