@@ -21,9 +21,9 @@
 //           C = K Q^T for the row log-sum-exp, then C = Q K^T for per-key
 //           sums of exp2(z - lse) -> one partial per credited context key
 //           and workgroup (its row groups added in order);
-//   fold    per observer: sum its (slice layer, kv head, workgroup) partials;
-//   reduce  per credited block i and 64-slot chunk: sum the folded partials of
-//           every observer below i in observer order (fp64) into A, rows_seen;
+//   reduce  per credited block i and 64-slot chunk: sum each observer's (slice
+//           layer, kv head, workgroup) partials, and those of every observer
+//           below i (fp64, in a fixed order) into A, rows_seen;
 //   final   a_i = sum_p A_i(p) / rows_seen_i, s_i = clip(sigmoid(theta.phi)).
 // No atomics anywhere, so A is bitwise reproducible.  The reduction dimension
 // (head_dim) is permuted identically in both MFMA operands so that every lane
@@ -778,18 +778,16 @@ __device__ ObsChain walk_chain(const Tree &t, int j, int32_t *anc_out) {
 
 // One workgroup for the whole call, O(V + n_obs depth): validates the tree,
 // walks every observer chain (one thread per observer, root first into anc),
-// forms the offsets of the partials, folded sums and sub-page tables as
-// prefixes over observers, and lists the blocks that receive credit (proper
+// forms the offsets of the partials and sub-page tables as prefixes over
+// observers, and lists the chunks of the blocks that receive credit (proper
 // ancestors of some observer; the observers themselves in the self-window
 // mode) in ascending id, so that the reduction visits only those.
-// fbase / tbase hold the prefixes of the chain lengths and sub-page counts
-// until the totals are known.
+// tbase holds the prefixes of the sub-page counts until the totals are known.
 // IN_LDS (trees of up to kSetupLds nodes) is a template argument, so that the
 // tree's arrays are read with LDS or global instructions rather than flat ones.
 template <bool IN_LDS>
 __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
                                                     int64_t *__restrict__ pbase,
-                                                    int64_t *__restrict__ fbase,
                                                     int64_t *__restrict__ tbase,
                                                     int32_t *__restrict__ nsp,
                                                     int32_t *__restrict__ ctxlen,
@@ -798,8 +796,8 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
                                                     int32_t *__restrict__ flag,
                                                     int32_t *__restrict__ nctx,
                                                     int32_t *__restrict__ ndep,
-                                                    int32_t *__restrict__ cred) {
-  __shared__ int64_t sm[17];
+                                                    int2 *__restrict__ cred) {
+  __shared__ int64_t sm[2 * 16];
   __shared__ int s_err;
   // parent links and block sizes in LDS for trees of up to kSetupLds nodes, so
   // the chain walks do not wait on global memory at every step
@@ -813,7 +811,7 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
             c0 = n0 ? t.n_kept[tid] : 0;
   const int obs0 = tid < a.n_obs ? a.obs[tid] : 0;
   if (status_failed(a.status)) {
-    if (threadIdx.x == 0) cred[0] = 0;
+    if (threadIdx.x == 0) cred[0].x = 0;
     return;
   }
   if (tid == 0) s_err = 0;
@@ -861,7 +859,7 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
   }
   __syncthreads();
   const int slabs = a.S * a.pl.Hkv * a.n_slab;
-  int64_t run = 0, frun = 0, trun = 0;
+  int64_t run = 0, trun = 0;
   for (int base = 0; base < a.n_obs; base += nt) {
     const int o = base + tid;
     int64_t len = 0, subs = 0;
@@ -891,7 +889,6 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
           for (int e = 0; e <= r.depth; ++e) {
             const int x = ao[e];
             if (!lone && e < r.depth) flag[x] = 1;
-            if (lone) cred[1 + e] = x;
             nctx[x] = ctx;
             ndep[x] = e;
             ctx += t.n_kept[x];
@@ -900,26 +897,21 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
         }
       }
     }
-    int64_t tot, ftot, ttot;
-    const int64_t ex = block_exclusive_scan<int64_t>(len * slabs, sm, &tot);
-    const int64_t fx = block_exclusive_scan<int64_t>(len, sm, &ftot);
-    const int64_t tx = block_exclusive_scan<int64_t>(subs, sm, &ttot);
+    const int64_t v2[2] = {len * slabs, subs};
+    int64_t ex[2], tot[2];
+    block_exclusive_scan_n<2>(v2, ex, tot, sm, a.n_obs - base);
     if (o < a.n_obs) {
-      pbase[o] = run + ex;
-      fbase[o] = frun + fx;
-      tbase[o] = trun + tx;
+      pbase[o] = run + ex[0];
+      tbase[o] = trun + ex[1];
     }
-    run += tot;
-    frun += ftot;
-    trun += ttot;
+    run += tot[0];
+    trun += tot[1];
   }
   __syncthreads();
-  // the folded sums follow the partials, then the sub-page tables (16-byte
-  // entries, 16-byte aligned)
-  const int64_t tab0 = (run + frun + 3) & ~(int64_t)3;
+  // the sub-page tables (16-byte entries, 16-byte aligned) follow the partials
+  const int64_t tab0 = (run + 3) & ~(int64_t)3;
   const bool fits = tab0 + 4 * trun <= part_cap;
   for (int o = tid; o < a.n_obs; o += nt) {
-    fbase[o] += run;
     tbase[o] = tab0 + 4 * tbase[o];
   }
   if (tid == 0) {
@@ -927,19 +919,28 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
     else if (s_err & 2) status_error(a.status, ARBOR_EUNSUPPORTED);
     else if (!fits) status_error(a.status, ARBOR_EWORKSPACE);
   }
-  // the credited blocks in ascending id
+  // the credited blocks' 64-slot chunks in ascending block id (one at least for
+  // each: its first chunk also counts the rows)
   int64_t crun = 0;
-  if constexpr (IN_LDS) {
-    for (int base = 0; base < t.V; base += nt) {
+  auto chunks_of = [&](int x) { return max(1, (t.n_kept[x] + kWave - 1) / kWave); };
+  const int64_t room = (int64_t)t.V + t.N / kWave + 1;   // entries of the list
+  auto put = [&](int64_t at, int x, int n) {
+    for (int q = 0; q < n && at + q < room; ++q) cred[1 + at + q] = make_int2(x, q);
+  };
+  if (lone || IN_LDS) {
+    const int count = lone ? (s_err ? 0 : odepth[0] + (a.self_window ? 1 : 0)) : t.V;
+    for (int base = 0; base < count; base += nt) {
       const int i = base + tid;
-      const int f = i < t.V ? flag[i] : 0;
+      int x = i, n = 0;
+      if (i < count) {
+        if (lone) x = anc[i];
+        n = lone || flag[i] ? chunks_of(x) : 0;
+      }
       int64_t ctot;
-      const int64_t cx = block_exclusive_scan<int64_t>(f, sm, &ctot);
-      if (f) cred[1 + crun + cx] = i;
+      const int64_t cx = block_exclusive_scan<int64_t>(n, sm, &ctot);
+      put(crun + cx, x, n);
       crun += ctot;
     }
-  } else if (lone) {
-    crun = s_err ? 0 : odepth[0] + (a.self_window ? 1 : 0);
   } else {
     // each thread takes a run of consecutive blocks (their flags loaded eight
     // at a time), and one scan places the runs
@@ -951,7 +952,8 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
 #pragma unroll
       for (int u = 0; u < kGrp; ++u) f[u] = ib + u < r1 ? flag[ib + u] : 0;
 #pragma unroll
-      for (int u = 0; u < kGrp; ++u) mine += f[u];
+      for (int u = 0; u < kGrp; ++u)
+        if (f[u]) mine += chunks_of(ib + u);
     }
     int64_t off = block_exclusive_scan<int64_t>(mine, sm, &crun);
     for (int ib = r0; ib < r1 && mine > 0; ib += kGrp) {
@@ -960,16 +962,19 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
       for (int u = 0; u < kGrp; ++u) f[u] = ib + u < r1 ? flag[ib + u] : 0;
 #pragma unroll
       for (int u = 0; u < kGrp; ++u)
-        if (f[u]) cred[1 + off++] = ib + u;
+        if (f[u]) {
+          const int n = chunks_of(ib + u);
+          put(off, ib + u, n);
+          off += n;
+        }
     }
   }
-  if (tid == 0) cred[0] = (s_err || !fits) ? 0 : (int32_t)crun;
+  if (tid == 0) cred[0].x = (s_err || !fits) ? 0 : (int32_t)min(crun, room);
 }
 
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void score_setup(ScoreArgs a, int64_t part_cap,
                                                     int64_t *__restrict__ pbase,
-                                                    int64_t *__restrict__ fbase,
                                                     int64_t *__restrict__ tbase,
                                                     int32_t *__restrict__ nsp,
                                                     int32_t *__restrict__ ctxlen,
@@ -978,8 +983,8 @@ __global__ __launch_bounds__(1024) void score_setup(ScoreArgs a, int64_t part_ca
                                                     int32_t *__restrict__ flag,
                                                     int32_t *__restrict__ nctx,
                                                     int32_t *__restrict__ ndep,
-                                                    int32_t *__restrict__ cred) {
-  setup_body<IN_LDS>(a, part_cap, pbase, fbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx,
+                                                    int2 *__restrict__ cred) {
+  setup_body<IN_LDS>(a, part_cap, pbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx,
                      ndep, cred);
 }
 
@@ -1044,12 +1049,12 @@ __global__ __launch_bounds__(256) void score_tables(ScoreArgs a) {
 // Setup and tables in one launch (up to kPrepObs observers): workgroup 0 runs
 // the setup; workgroup 1 + o builds observer o's table without waiting for
 // it.  It walks every observer's chain itself (one thread per observer, the
-// setup's checks) for the sums that place the tables after the partials and
-// folded sums, and the prefix of the sub-page counts that places o's table:
+// setup's checks) for the sums that place the tables after the partials, and the prefix of the sub-page counts that places o's table:
 // the same integers the setup computes, so the offsets agree.  A malformed
 // chain or a workspace too small leaves o's table unwritten (the setup
 // reports the error, and no later kernel runs).
 constexpr int kPrepObs = 512;
+constexpr int kFewObs = 32;    // up to this many, four waves reduce a chunk
 
 // The setup's check of nodes [base, base + blockDim.x).
 __device__ __forceinline__ void check_nodes(const ScoreArgs &a, int base) {
@@ -1065,7 +1070,6 @@ __device__ __forceinline__ void check_nodes(const ScoreArgs &a, int base) {
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap,
                                                    int64_t *__restrict__ pbase,
-                                                   int64_t *__restrict__ fbase,
                                                    int64_t *__restrict__ tbase,
                                                    int32_t *__restrict__ nsp,
                                                    int32_t *__restrict__ ctxlen,
@@ -1074,9 +1078,9 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
                                                    int32_t *__restrict__ flag,
                                                    int32_t *__restrict__ nctx,
                                                    int32_t *__restrict__ ndep,
-                                                   int32_t *__restrict__ cred) {
+                                                   int2 *__restrict__ cred) {
   if (blockIdx.x == 0) {
-    setup_body<IN_LDS>(a, part_cap, pbase, fbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx,
+    setup_body<IN_LDS>(a, part_cap, pbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx,
                        ndep, cred);
     return;
   }
@@ -1085,7 +1089,7 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
     return;
   }
   __shared__ ChainLds ch;
-  __shared__ int64_t sm[17];
+  __shared__ int64_t sm[2 * 16];
   __shared__ int64_t s_pre;
   __shared__ int s_bad;
   const Tree &t = a.t;
@@ -1097,7 +1101,7 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
   if (tid == 0) s_bad = 0;
   __syncthreads();
   const int slabs = a.S * a.pl.Hkv * a.n_slab;
-  int64_t run = 0, frun = 0, trun = 0;
+  int64_t run = 0, trun = 0;
   for (int base = 0; base < a.n_obs; base += nt) {
     const int oo = base + tid;
     int64_t len = 0, subs = 0;
@@ -1113,53 +1117,17 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
         if (oo == o) ch.depth = r.depth;
       }
     }
-    int64_t tot, ftot, ttot;
-    block_exclusive_scan<int64_t>(len * slabs, sm, &tot);
-    block_exclusive_scan<int64_t>(len, sm, &ftot);
-    const int64_t tx = block_exclusive_scan<int64_t>(subs, sm, &ttot);
-    if (oo == o) s_pre = trun + tx;
-    run += tot;
-    frun += ftot;
-    trun += ttot;
+    const int64_t v2[2] = {len * slabs, subs};
+    int64_t ex[2], tot[2];
+    block_exclusive_scan_n<2>(v2, ex, tot, sm, a.n_obs - base);
+    if (oo == o) s_pre = trun + ex[1];
+    run += tot[0];
+    trun += tot[1];
   }
   __syncthreads();
-  const int64_t tab0 = (run + frun + 3) & ~(int64_t)3;
+  const int64_t tab0 = (run + 3) & ~(int64_t)3;
   if (s_bad || tab0 + 4 * trun > part_cap) return;
   table_body(a, ch, j, reinterpret_cast<int4 *>(a.part + tab0 + 4 * s_pre));
-}
-
-// Fold the (slice layer, kv head, workgroup) slabs of every observer: one
-// column sum per (observer, credited context key), summed in slab order.
-__global__ __launch_bounds__(256) void score_fold(ScoreArgs a, const int64_t *__restrict__ fbase) {
-  const int o = blockIdx.x;
-  // (loaded together with the status word)
-  const int len = a.ctxlen[o];
-  const int jo = a.obs[o];
-  const int64_t pb = a.pbase[o], fb = fbase[o];
-  if (status_failed(a.status)) return;
-  const int own_c = a.t.n_kept[jo];
-  const int credited = a.self_window ? len : len - own_c;
-  const int nslab = a.S * a.pl.Hkv * a.n_slab;
-  const float *src = a.part + pb;
-  float *dst = a.part + fb;
-  for (int x = blockIdx.y * blockDim.x + threadIdx.x; x < credited; x += gridDim.y * blockDim.x) {
-    // up to sixteen loads in flight, added in slab order
-    float acc = 0.f;
-    int sl = 0;
-    auto add = [&](auto n) __attribute__((always_inline)) {
-      constexpr int N = decltype(n)::value;
-      float v[N];
-#pragma unroll
-      for (int u = 0; u < N; ++u) v[u] = src[(int64_t)(sl + u) * len + x];
-#pragma unroll
-      for (int u = 0; u < N; ++u) acc += v[u];
-      sl += N;
-    };
-    while (sl + 16 <= nslab) add(std::integral_constant<int, 16>{});
-    if (sl + 8 <= nslab) add(std::integral_constant<int, 8>{});
-    for (; sl < nslab; ++sl) acc += src[(int64_t)sl * len + x];
-    dst[x] = acc;
-  }
 }
 
 // a_i and s_i of block i from its A (one wave).
@@ -1201,105 +1169,123 @@ struct FinalArgs {
   float *a_out, *s_out;
 };
 
-// A += folded sums of every observer below block i (observer order, fp64);
-// rows_seen_i grows.  Workgroup x takes the x-th credited block of the setup's
-// list.  The four waves of a workgroup split the observers of a 64-slot chunk
-// and are combined in wave order.
-__global__ __launch_bounds__(256) void score_reduce(ScoreArgs a, const int64_t *__restrict__ fbase,
-                                                    const int32_t *__restrict__ cred,
-                                                    float *__restrict__ A,
-                                                    int64_t *__restrict__ rows_seen) {
-  __shared__ int64_t hbase[256];
-  __shared__ int s_wcnt[4];
-  __shared__ double s_acc[4][64];
+// A += the column sums of every observer below block i, rows_seen_i grows:
+// workgroups take the (block i, 64-slot chunk) entries of the setup's list in
+// turn.  An observer's partials of a slot, one per (slice layer, kv head,
+// workgroup), are added in slab order (fp32, sixteen loads in flight); the W
+// waves split the observers and are combined in wave order (fp64).
+// (With a launch of its own for the slab sums, 16 leaves over a 341-block tree
+// took 3.4 + 7.3 us, now 5.4; 85 observers of the 8B shape 4.9 + 5.8, now 8.9;
+// 341 of the 70B shape 23 + 20, now 44.)
+template <int W>
+__global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2 *__restrict__ cred,
+                                                         float *__restrict__ A,
+                                                         int64_t *__restrict__ rows_seen) {
+  constexpr int HB = 256;               // observers looked at together
+  static_assert(W * kWave >= HB, "one thread per observer");
+  constexpr int HW = HB / kWave;
+  __shared__ int64_t hbase[HB];
+  __shared__ int hlen[HB];
+  __shared__ int s_wcnt[HW];
+  __shared__ double s_acc[W][kWave];
+  __shared__ int64_t s_sum[17];
   // (loaded together with the status word; the list entry past its end is
-  // allocated, and unused then; so are the first 256 observers' depths and
-  // window sizes, which do not depend on the block)
-  const int ncred = cred[0];
-  const int i = cred[1 + blockIdx.x];
-  const bool o0 = (int)threadIdx.x < a.n_obs;
-  const int od0 = o0 ? a.odepth[threadIdx.x] : -1;
-  const int64_t fb0 = o0 ? fbase[threadIdx.x] : 0;
-  const int wn0 = o0 ? min(a.W, a.t.n_full[a.obs[threadIdx.x]]) : 0;
+  // allocated, and unused then; so are the first observers' fields, which do
+  // not depend on the block)
+  const int tid = threadIdx.x;
+  const int n_items = cred[0].x;
+  int2 item = cred[1 + blockIdx.x];
+  const bool o0 = tid < a.n_obs && tid < HB;
+  const int od0 = o0 ? a.odepth[tid] : -1, len0 = o0 ? a.ctxlen[tid] : 0;
+  const int64_t pb0 = o0 ? a.pbase[tid] : 0;
+  const int obs0 = o0 ? a.obs[tid] : -1;
   if (status_failed(a.status)) return;
-  if ((int)blockIdx.x >= ncred) return;
   const Tree &t = a.t;
   const Pool &pl = a.pl;
-  const int c = t.n_kept[i];
-  // chunk splits past the block's last chunk have nothing to add (split 0
-  // still counts the rows)
-  if (blockIdx.y > 0 && (int)blockIdx.y * 64 >= c) return;
   const int lane = lane_id();
-  const int wave = threadIdx.x >> 6;
-  const float *fold = a.part;
-  // (every credited block lies on an observer's chain, whose depth and
-  // context offset the setup recorded)
-  const int di = a.ndep[i], ctxoff = a.nctx[i];
-  const int64_t tb = t.tok_off[i];
-  const int64_t po = t.page_off[i];
-  int64_t rows_add = 0;
-  const int nchunk = (c + 63) / 64;
-  for (int ob = 0; ob < a.n_obs; ob += 256) {
-    const int o = ob + threadIdx.x;
-    bool hit = false;
-    if (o < a.n_obs) {
-      const int od = ob == 0 ? od0 : a.odepth[o];
-      hit = (od > di && a.anc[(int64_t)o * MAXD + di] == i) || (a.self_window && a.obs[o] == i);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nslab = a.S * pl.Hkv * a.n_slab;
+  for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
+    if (w != (int)blockIdx.x) item = cred[1 + w];
+    const int i = item.x, chk = item.y;
+    const int s = chk * kWave + lane;
+    const int c = t.n_kept[i];
+    // (every credited block lies on an observer's chain, whose depth and
+    // context offset the setup recorded)
+    const int di = a.ndep[i], ctxoff = a.nctx[i];
+    const int64_t tb = t.tok_off[i], po = t.page_off[i];
+    const bool live = s < c;
+    int64_t tok = 0;
+    float a_old = 0.f;
+    if (wave == 0 && live) {              // (ahead of the sums)
+      const int page = t.page_table[po + s / pl.P];
+      tok = tb + pl.slot_pos[(int64_t)page * pl.P + s % pl.P];
+      a_old = A[tok];
     }
-    const uint64_t bm = ballot(hit);
-    if (lane == 0) s_wcnt[wave] = popc(bm);
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += s_wcnt[w];
-    const int nh = s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
-    if (hit) {
-      hbase[before + rank_below(bm, lane)] = (ob == 0 ? fb0 : fbase[o]) + ctxoff;
-      if (blockIdx.y == 0)
-        rows_add += (int64_t)a.S * pl.Hkv * pl.G *
-                    (ob == 0 ? wn0 : min(a.W, t.n_full[a.obs[o]]));
-    }
-    __syncthreads();
-    if (nh > 0) {
-      for (int chk = blockIdx.y; chk < nchunk; chk += gridDim.y) {
-        const int s = chk * 64 + lane;
-        double acc = 0.0;
-        if (s < c) {
-          // (sixteen, then four loads in flight, added one by one in order)
-          int h = wave;
-          for (; h + 60 < nh; h += 64) {
-            float f[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) f[u] = fold[hbase[h + 4 * u] + s];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) acc += (double)f[u];
-          }
-          for (; h + 12 < nh; h += 16) {
-            const float f0 = fold[hbase[h] + s];
-            const float f1 = fold[hbase[h + 4] + s];
-            const float f2 = fold[hbase[h + 8] + s];
-            const float f3 = fold[hbase[h + 12] + s];
-            acc += (double)f0;
-            acc += (double)f1;
-            acc += (double)f2;
-            acc += (double)f3;
-          }
-          for (; h < nh; h += 4) acc += (double)fold[hbase[h] + s];
-        }
-        s_acc[wave][lane] = acc;
-        __syncthreads();
-        if (wave == 0 && s < c) {
-          const double tot = ((s_acc[0][lane] + s_acc[1][lane]) + s_acc[2][lane]) + s_acc[3][lane];
-          const int page = t.page_table[po + s / pl.P];
-          const int pos = pl.slot_pos[(int64_t)page * pl.P + s % pl.P];
-          A[tb + pos] = (float)((double)A[tb + pos] + tot);
-        }
-        __syncthreads();
+    double acc = 0.0;
+    int64_t rows_add = 0;
+    for (int ob = 0; ob < a.n_obs; ob += HB) {
+      const int o = ob + tid;
+      bool hit = false;
+      int jo = -1;
+      if (tid < HB && o < a.n_obs) {
+        jo = ob == 0 ? obs0 : a.obs[o];
+        const int od = ob == 0 ? od0 : a.odepth[o];
+        hit = (od > di && a.anc[(int64_t)o * MAXD + di] == i) || (a.self_window && jo == i);
       }
+      const uint64_t bm = ballot(hit);
+      if (wave < HW && lane == 0) s_wcnt[wave] = popc(bm);
+      __syncthreads();
+      int before = 0, nh = 0;
+#pragma unroll
+      for (int v = 0; v < HW; ++v) {
+        before += v < wave ? s_wcnt[v] : 0;
+        nh += s_wcnt[v];
+      }
+      if (hit) {
+        const int at = before + rank_below(bm, lane);
+        hbase[at] = (ob == 0 ? pb0 : a.pbase[o]) + ctxoff;
+        hlen[at] = ob == 0 ? len0 : a.ctxlen[o];
+        if (chk == 0) rows_add += (int64_t)a.S * pl.Hkv * pl.G * min(a.W, t.n_full[jo]);
+      }
+      __syncthreads();
+      if (live) {
+        for (int h = wave; h < nh; h += W) {
+          const float *src = a.part + hbase[h] + s;
+          const int64_t len = hlen[h];
+          float f = 0.f;
+          int sl = 0;
+          auto add = [&](auto n) __attribute__((always_inline)) {
+            constexpr int N = decltype(n)::value;
+            float v[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) v[u] = src[(sl + u) * len];
+#pragma unroll
+            for (int u = 0; u < N; ++u) f += v[u];
+            sl += N;
+          };
+          while (sl + 16 <= nslab) add(std::integral_constant<int, 16>{});
+          if (sl + 8 <= nslab) add(std::integral_constant<int, 8>{});
+          if (sl + 4 <= nslab) add(std::integral_constant<int, 4>{});
+          for (; sl < nslab; ++sl) f += src[sl * len];
+          acc += (double)f;
+        }
+      }
+      __syncthreads();                    // the lists are reused
     }
-  }
-  if (blockIdx.y == 0) {
-    rows_add = block_sum<int64_t>(rows_add, reinterpret_cast<int64_t *>(&s_acc[0][0]));
-    if (threadIdx.x == 0) rows_seen[i] += rows_add;
+    s_acc[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && live) {
+      double tot = 0.0;
+#pragma unroll
+      for (int v = 0; v < W; ++v) tot += s_acc[v][lane];
+      A[tok] = (float)((double)a_old + tot);
+    }
+    if (chk == 0) {
+      rows_add = block_sum<int64_t>(rows_add, s_sum);
+      if (tid == 0) rows_seen[i] += rows_add;
+    }
+    __syncthreads();
   }
 }
 
@@ -1405,10 +1391,10 @@ size_t score_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   size_t b = 0;
   // offsets, counts, chains, credited-block flags and list (each carve
   // rounds up to 256 B)
-  b += nobs * (8 * 3 + 4 * 4) + nobs * MAXD * 4 + (size_t)sz->num_nodes * 16 + 14 * 256;
-  // partials and their folded sums
-  b += std::max(nobs * (slabs + 1), few * (planes * sp.n_slab + 1)) * (size_t)sz->max_context * 4 +
-       256;
+  b += nobs * (8 * 2 + 4 * 4) + nobs * MAXD * 4 + (size_t)sz->num_nodes * 20 +
+       (size_t)sz->num_tokens / kWave * 8 + 14 * 256;
+  // partials
+  b += std::max(nobs * slabs, few * planes * sp.n_slab) * (size_t)sz->max_context * 4 + 256;
   // sub-page tables: at most one ragged sub-page per chain node
   b += nobs * ((size_t)sz->max_context / 16 + MAXD + 1) * 16 + 256;
   return b;
@@ -1445,7 +1431,6 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
   Carve cv(workspace, workspace_bytes);
   const size_t nobs = n_obs > 0 ? (size_t)n_obs : 1;
   int64_t *pbase = cv.take<int64_t>(nobs);
-  int64_t *fbase = cv.take<int64_t>(nobs);
   int64_t *tbase = cv.take<int64_t>(nobs);
   int32_t *nsp = cv.take<int32_t>(2 * nobs);
   int32_t *ctxlen = cv.take<int32_t>(nobs);
@@ -1454,7 +1439,7 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
   int32_t *flag = cv.take<int32_t>((size_t)t.V);
   int32_t *nctx = cv.take<int32_t>((size_t)t.V);
   int32_t *ndep = cv.take<int32_t>((size_t)t.V);
-  int32_t *cred = cv.take<int32_t>((size_t)t.V + 1);
+  int2 *cred = cv.take<int2>((size_t)t.V + (size_t)(t.N / kWave) + 2);
   if (!cv.ok) return ARBOR_EWORKSPACE;
   float *part = reinterpret_cast<float *>(cv.rest());
   const int64_t part_cap = (int64_t)(cv.remaining() / 4);
@@ -1479,18 +1464,18 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
       const unsigned checks = n_obs == 1 && t.V > kSetupLds ? (t.V + blk.x - 1) / blk.x : 0;
       const dim3 grid((unsigned)n_obs + 1 + checks);
       if (t.V <= kSetupLds)
-        hipLaunchKernelGGL(score_prep<true>, grid, blk, 0, stream, a, part_cap, pbase, fbase,
+        hipLaunchKernelGGL(score_prep<true>, grid, blk, 0, stream, a, part_cap, pbase,
                            tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
       else
-        hipLaunchKernelGGL(score_prep<false>, grid, blk, 0, stream, a, part_cap, pbase, fbase,
+        hipLaunchKernelGGL(score_prep<false>, grid, blk, 0, stream, a, part_cap, pbase,
                            tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
     } else {
       if (t.V <= kSetupLds)
         hipLaunchKernelGGL(score_setup<true>, dim3(1), dim3(st), 0, stream, a, part_cap, pbase,
-                           fbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
+                           tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
       else
         hipLaunchKernelGGL(score_setup<false>, dim3(1), dim3(st), 0, stream, a, part_cap, pbase,
-                           fbase, tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
+                           tbase, nsp, ctxlen, odepth, anc, flag, nctx, ndep, cred);
       hipLaunchKernelGGL(score_tables, dim3(n_obs), dim3(256), 0, stream, a);
     }
     const int n_planes = n_slice * pl.Hkv * a.n_slab;
@@ -1498,14 +1483,16 @@ int launch_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor
     timing_begin(geom, ARBOR_KERNEL_SCORE_ATTN, stream);
     launch_attn(geom->dtype, geom->head_dim, shape, grid, stream, a);
     timing_end(geom, ARBOR_KERNEL_SCORE_ATTN, stream);
-    hipLaunchKernelGGL(score_fold, dim3(n_obs, 8), dim3(256), 0, stream, a, fbase);
-    // at most V credited blocks, and at most MAXD per observer
+    // at most V credited blocks, and at most MAXD per observer; more observers
+    // take more waves for each chunk
     const int64_t max_cred = std::min<int64_t>(t.V, (int64_t)n_obs * MAXD);
-    // 64-slot chunk splits per block: 64 (one chunk each up to 4,096 kept
-    // slots) while the grid stays small, else 16
-    const unsigned ysplit = max_cred <= 512 ? 64u : 16u;
-    hipLaunchKernelGGL(score_reduce, dim3((unsigned)max_cred, ysplit), dim3(256), 0, stream, a,
-                       fbase, cred, A, rows_seen);
+    const int64_t items = max_cred + t.N / kWave;
+    if (n_obs > kFewObs)
+      hipLaunchKernelGGL(score_reduce<16>, dim3((unsigned)std::min<int64_t>(items, 512)),
+                         dim3(16 * kWave), 0, stream, a, cred, A, rows_seen);
+    else
+      hipLaunchKernelGGL(score_reduce<4>, dim3((unsigned)std::min<int64_t>(items, 2048)),
+                         dim3(4 * kWave), 0, stream, a, cred, A, rows_seen);
   }
   hipLaunchKernelGGL(score_final, dim3((t.V + 3) / 4), dim3(256), 0, stream, t, A, rows_seen, fa,
                      status);
