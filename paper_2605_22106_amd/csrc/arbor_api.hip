@@ -20,7 +20,8 @@ int launch_select_compact(const arbor_geom_t *, arbor_tree_t *, arbor_pool_t *, 
                           const int32_t *, const arbor_params_t *, int32_t *, int32_t *, void *,
                           size_t, hipStream_t);
 int launch_rehydrate(const arbor_geom_t *, arbor_tree_t *, arbor_pool_t *, const uint8_t *,
-                     const void *, const void *, int32_t *, void *, size_t, hipStream_t);
+                     const void *, const void *, int32_t *, void *, size_t, hipStream_t,
+                     const int32_t *, int64_t *);
 int launch_decode(const arbor_geom_t *, const arbor_tree_t *, const arbor_pool_t *,
                   const int32_t *, int32_t, int32_t, int32_t, const void *, void *, int32_t,
                   float *, float, const arbor_decode_credit_t *, int32_t *, void *, size_t,
@@ -72,6 +73,22 @@ static int check_pool(const arbor_pool_t *p) {
     const int rc_ = (x);       \
     if (rc_ != ARBOR_OK) return rc_; \
   } while (0)
+
+namespace arbor {
+// arbor_rehydrate, with a walk's event statistics beside its plan when
+// stats_row is given
+int checked_rehydrate(const arbor_geom_t *geom, arbor_tree_t *tree, arbor_pool_t *pool,
+                      const uint8_t *on_path, const void *host_k, const void *host_v,
+                      int32_t *status, void *workspace, size_t workspace_bytes,
+                      hipStream_t stream, const int32_t *stats_k, int64_t *stats_row) {
+  ARBOR_TRY(check_geom(geom));
+  ARBOR_TRY(check_tree(tree));
+  ARBOR_TRY(check_pool(pool));
+  if (!status || !on_path || !host_k || !host_v) return ARBOR_EINVAL;
+  return launch_rehydrate(geom, tree, pool, on_path, host_k, host_v, status, workspace,
+                          workspace_bytes, stream, stats_k, stats_row);
+}
+}  // namespace arbor
 
 extern "C" {
 
@@ -185,12 +202,8 @@ int arbor_rehydrate(const arbor_geom_t *geom, arbor_tree_t *tree, arbor_pool_t *
                     const uint8_t *on_path, const void *host_k, const void *host_v,
                     int32_t *status, void *workspace, size_t workspace_bytes,
                     hipStream_t stream) {
-  ARBOR_TRY(check_geom(geom));
-  ARBOR_TRY(check_tree(tree));
-  ARBOR_TRY(check_pool(pool));
-  if (!status || !on_path || !host_k || !host_v) return ARBOR_EINVAL;
-  return launch_rehydrate(geom, tree, pool, on_path, host_k, host_v, status, workspace,
-                          workspace_bytes, stream);
+  return checked_rehydrate(geom, tree, pool, on_path, host_k, host_v, status, workspace,
+                           workspace_bytes, stream, nullptr, nullptr);
 }
 
 int arbor_tree_decode_attn(const arbor_geom_t *geom, const arbor_tree_t *tree,

@@ -11,6 +11,9 @@ namespace arbor {
 int launch_allocate(const arbor_tree_t *, const int32_t *, int32_t, int64_t, const float *,
                     const arbor_params_t *, int32_t *, int32_t *, uint8_t *, int32_t *, void *,
                     size_t, hipStream_t, int gate);
+int checked_rehydrate(const arbor_geom_t *, arbor_tree_t *, arbor_pool_t *, const uint8_t *,
+                      const void *, const void *, int32_t *, void *, size_t, hipStream_t,
+                      const int32_t *, int64_t *);
 int launch_walk_stats(const arbor_tree_t *, const int32_t *, const uint8_t *, int64_t, int, int,
                       int64_t *, int32_t *, hipStream_t);
 }  // namespace arbor
@@ -46,13 +49,14 @@ extern "C" int arbor_walk(const arbor_geom_t *geom, arbor_tree_t *tree, arbor_po
     // Transition: reallocate for the new Path*
     WALK_TRY(arbor_allocate(tree, leaf, 1, w->budget_tokens, w->s, params, w->k, w->delta,
                             w->on_path, status, workspace, workspace_bytes, stream));
-    if (row)
-      WALK_TRY(launch_walk_stats(tree, w->k, w->on_path, w->budget_tokens, 1,
-                                 params->lazy_rehydration, row, status, stream));
-    // lazy rehydration of the new chain before it is attended
+    // lazy rehydration of the new chain before it is attended, with the event's
+    // statistics beside its plan
     if (params->lazy_rehydration)
-      WALK_TRY(arbor_rehydrate(geom, tree, pool, w->on_path, w->host_k, w->host_v, status,
-                               workspace, workspace_bytes, stream));
+      WALK_TRY(checked_rehydrate(geom, tree, pool, w->on_path, w->host_k, w->host_v, status,
+                                 workspace, workspace_bytes, stream, w->k, row));
+    else if (row)
+      WALK_TRY(launch_walk_stats(tree, w->k, w->on_path, w->budget_tokens, 1, 0, row, status,
+                                 stream));
     // the new leaf's window queries credit its ancestors
     if (scored)
       WALK_TRY(arbor_score(geom, tree, pool, leaf, 1,
