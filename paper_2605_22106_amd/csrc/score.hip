@@ -258,7 +258,6 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
   // pass 1: the key sums of the last four steps, per key split, key and row
   // group (used when RGW > 1)
   __shared__ __attribute__((aligned(16))) float s_cs[KSW][4][16 * RGW];
-  __shared__ int s_bad;
   // XCD-aware order: workgroup n runs on XCD n % 8, so XCD x takes the
   // (slice layer, kv head, RGW row groups) planes p = x, x + 8, ...; it runs the
   // observers in reverse list order, each over all its planes in turn.  For
@@ -275,16 +274,18 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
   const int o = a.n_obs - 1 - idx / ppx;
   const int plane = (idx % ppx) * kXcds + xcd;
   if (plane >= n_planes) return;
-  if (threadIdx.x == 0) s_bad = status_failed(a.status);
-  __syncthreads();
-  if (s_bad) return;
+  // the observer's fields are loaded together with the status word
+  const int j = a.obs[o];
+  const int nsp0 = a.nsp[2 * o], nsp1 = a.nsp[2 * o + 1];
+  const int64_t tb_o = a.tbase[o], pb_o = a.pbase[o];
+  const int len_o = a.ctxlen[o];
+  if (status_failed(a.status)) return;
   const Tree &t = a.t;
   const Pool &pl = a.pl;
   const int slg = plane / n_rgp;
   const int si = slg / pl.Hkv;
   const int g = slg % pl.Hkv;
   const int layer = a.slice[si];
-  const int j = a.obs[o];
   // the chain's sub-page table: entry sp = (plane row, slot, context offset,
   // valid slots | own << 8 | mask flags)
   const int tid = threadIdx.x;
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
   const int lbase = 16 * (R * r + ((q * RQ) ^ (r & KT::XM)));
 
   // the chain's sub-page table as 16-byte vectors (read into registers)
-  const int4 *tabv = reinterpret_cast<const int4 *>(a.part + a.tbase[o]);
+  const int4 *tabv = reinterpret_cast<const int4 *>(a.part + tb_o);
   // one sub-page: a buffer resource over its BYTES (set up in scalar
   // registers), so each lane supplies only a 32-bit offset
   auto issue = [&](Buf &B, int row) __attribute__((always_inline)) {
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
     nm[rb] = nm0;
     l[rb] = 0.f;
   }
-  run(a.nsp[2 * o],
+  run(nsp0,
       [&](const uint4 (&kp)[RQ], int slot, int meta, int ctx) __attribute__((always_inline)) {
         StepState st;
         st.meta = meta;
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
   // wave's write has completed) the wave rgw = m mod RGW adds the RGW values
   // in row-group order and stores them; a window's last three steps are
   // stored after its final barrier.
-  float *pout = a.part + a.pbase[o] + (int64_t)(slg * a.n_slab + rg / RGW) * a.ctxlen[o];
+  float *pout = a.part + pb_o + (int64_t)(slg * a.n_slab + rg / RGW) * len_o;
   float colsum = 0.f;
   int m = 0;                            // step of the window (stores pending)
   int ctx1 = 0, ctx2 = 0, ctx3 = 0;     // context offsets of steps m-1, m-2, m-3
@@ -653,7 +654,7 @@ __global__ __launch_bounds__(64 * RGW *KSW, RGW *KSW > 12 ? RGW * KSW / 4 : 3) v
     for (int u = 1; u < RGW; ++u) x += v[u];
     if (lane < nv) pout[ctx + lane] = x;
   };
-  run(a.nsp[2 * o + 1],
+  run(nsp1,
       [&](const uint4 (&kp)[RQ], int slot, int meta, int ctx) __attribute__((always_inline)) {
         StepState st;
         st.meta = meta;
