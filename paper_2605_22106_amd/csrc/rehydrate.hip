@@ -36,7 +36,7 @@ __global__ __launch_bounds__(1024) void rehyd_plan(Tree t, Pool pl, const uint8_
   }
   __shared__ int64_t sm[2 * 16];
   if (status_failed(status)) {
-    if (threadIdx.x == 0) meta[0] = 0;
+    if (threadIdx.x == 0) meta[0] = meta[2] = 0;
     return;
   }
   const int P = pl.P;
@@ -92,12 +92,15 @@ __global__ __launch_bounds__(1024) void rehyd_plan(Tree t, Pool pl, const uint8_
   if (threadIdx.x == 0) {
     const int top = *pl.free_top;
     if (run_pages > top) {
-      status_error(status, ARBOR_ENOPAGES);
+      // nothing to move; the last launch raises the error, so that the
+      // statistics beside this workgroup see the status that the event began with
       meta[0] = 0;
+      meta[2] = 1;
       return;
     }
     meta[0] = (int32_t)run_nodes;
     meta[1] = top;
+    meta[2] = 0;
     *pl.free_top = top - (int32_t)run_pages;
   }
 }
@@ -252,6 +255,10 @@ __global__ __launch_bounds__(256) void rehyd_finalize(Tree t, Pool pl,
                                                       const int32_t *__restrict__ meta,
                                                       int32_t *status) {
   if (status_failed(status)) return;
+  if (meta[2]) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) status_error(status, ARBOR_ENOPAGES);
+    return;
+  }
   const int lane = lane_id();
   const int P = pl.P;
   const int top = meta[1];

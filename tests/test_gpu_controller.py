@@ -156,3 +156,32 @@ def test_scored_walk_in_one_call_equals_event_by_event():
     assert np.array_equal(A0.view(np.uint32), A1.view(np.uint32))
     assert np.array_equal(s0.view(np.uint32), s1.view(np.uint32))
     assert_same_pool(p0, p1)
+
+
+def test_walk_without_free_pages_keeps_the_events_statistics():
+    """An event whose rehydration finds too few pages fails, changes nothing in the
+    pool, and still has its statistics; the events after it have none."""
+    st, parent, _, _ = _case(3)
+    kv = to_gpu(st)
+    N = st["num_tokens"]
+    s = torch.full((len(parent),), 0.5, device="cuda")
+    A = torch.rand(N, device="cuda")
+    budget = int(0.25 * N)
+    b = Bufs(kv, st, 3)
+    stt = status()
+    _walk(kv, st, b, [13], budget, BASE, A, s, stt, 0)
+    assert int(stt) >= 0
+    kv.free_top.zero_()
+    before = gpu_to_oracle(kv)
+    leaf = len(parent) - 1
+    k, _, on_path, _ = O.allocate(before["parent"], before["n_full"], before["n_kept"], [leaf],
+                                  budget, s.cpu().numpy(), BASE)
+    c, n = np.asarray(before["n_kept"]), np.asarray(before["n_full"])
+    want = [int(k.sum()), int((n - c)[(np.asarray(on_path) != 0) & (c < n)].sum()),
+            int(np.maximum(c - k, 0).sum()), 0]
+    b.stats.fill_(-9)
+    _walk(kv, st, b, [leaf, 13], budget, BASE, A, s, stt, 0)
+    assert int(stt) == L.ENOPAGES
+    assert want[1] > 0 and b.stats[0].tolist() == want
+    assert b.stats[1].tolist() == [-9] * 4
+    assert_same_pool(gpu_to_oracle(kv), before)
