@@ -127,8 +127,13 @@ __device__ void scan_nodes(const Tree &t, const Pool &pl, const int32_t *__restr
     pages += freed(c, ki);
     nodes += ki < c ? 1 : 0;
   }
-  if (status_failed(status)) {
-    if (threadIdx.x == 0) meta[0] = 0;
+  // one thread reads the status for all: the planning waves of the launch may
+  // raise an error meanwhile, and a part of the waves must not leave alone
+  __shared__ int s_failed;
+  if (tid == 0) s_failed = status_failed(status);
+  __syncthreads();
+  if (s_failed) {
+    if (tid == 0) meta[0] = 0;
     return;
   }
   const int64_t v2[2] = {pages, nodes};

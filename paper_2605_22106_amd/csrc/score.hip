@@ -811,11 +811,18 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
   const int par0 = n0 ? t.parent[tid] : 0, nf0 = n0 ? t.n_full[tid] : 0,
             c0 = n0 ? t.n_kept[tid] : 0;
   const int obs0 = tid < a.n_obs ? a.obs[tid] : 0;
-  if (status_failed(a.status)) {
-    if (threadIdx.x == 0) cred[0].x = 0;
+  // one thread reads the status for all: other workgroups of the launch may
+  // raise an error meanwhile, and a part of the waves must not leave alone
+  __shared__ int s_failed;
+  if (tid == 0) {
+    s_err = 0;
+    s_failed = status_failed(a.status);
+  }
+  __syncthreads();
+  if (s_failed) {
+    if (tid == 0) cred[0].x = 0;
     return;
   }
-  if (tid == 0) s_err = 0;
   constexpr bool in_lds = IN_LDS;
   // one observer over a tree beyond LDS: the launch's other workgroups check
   // the nodes (check_nodes) and its chain is the list of credited blocks, so
@@ -1098,9 +1105,10 @@ __global__ __launch_bounds__(1024) void score_prep(ScoreArgs a, int64_t part_cap
   const int tid = threadIdx.x;
   const int nt = blockDim.x;
   const int j = a.obs[o];
-  if (status_failed(a.status)) return;
-  if (tid == 0) s_bad = 0;
+  // read once for the workgroup: the setup may raise an error meanwhile
+  if (tid == 0) s_bad = status_failed(a.status) ? 2 : 0;
   __syncthreads();
+  if (s_bad == 2) return;
   const int slabs = a.S * a.pl.Hkv * a.n_slab;
   int64_t run = 0, trun = 0;
   for (int base = 0; base < a.n_obs; base += nt) {

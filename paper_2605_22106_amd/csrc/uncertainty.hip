@@ -187,13 +187,18 @@ __global__ __launch_bounds__(UT) void uncert_topk(const T *__restrict__ logits, 
   __shared__ unsigned hist[2048];
   __shared__ int s_bin, s_above, s_bad;
   __shared__ int64_t s_scan[17];
-  if (status_failed(status)) return;
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
   const uint4 *row = reinterpret_cast<const uint4 *>(logits + (int64_t)r * vocab);
   const int64_t nvec = vocab / N;
-  if (tid == 0) s_bad = 0;
+  // one thread reads the status for all: another row may raise an error meanwhile
+  __shared__ int s_failed;
+  if (tid == 0) {
+    s_bad = 0;
+    s_failed = status_failed(status);
+  }
   __syncthreads();
+  if (s_failed) return;
 
   // ---- pass 1: (m, S, T) of the whole row -------------------------------
   bool bad = false;
@@ -603,7 +608,8 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
   __shared__ float s_f[PT / kWave];
   __shared__ Ent s_all;
   __shared__ int s_bad;
-  if (status_failed(status)) return;
+  // one thread reads the status for all: another row may raise an error meanwhile
+  __shared__ int s_failed;
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
   const float *cr = cand + (int64_t)r * n_chunk * KMAX;
@@ -616,8 +622,10 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
   if (tid == 0) {
     s_lb = 0u;
     s_n = 0;
+    s_failed = status_failed(status);
   }
   __syncthreads();
+  if (s_failed) return;
   if (tid < kWave) {
     bool bad;
     const Ent all = row_ent(part + (int64_t)r * n_chunk, n_chunk, bad);
