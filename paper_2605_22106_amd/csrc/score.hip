@@ -1395,15 +1395,17 @@ size_t score_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   const size_t planes = (size_t)sz->n_slice * g->num_kv_heads;
   const Shape st = stream_shape(rows_total, g->dtype), sp = split_shape(rows_total, g->dtype);
   const size_t slabs = planes * st.n_slab;
-  // the split shape is taken for up to kSplitWgs workgroups of the other one
-  const size_t few = std::min(nobs, (size_t)kSplitWgs / std::max(slabs, (size_t)1));
+  // the split shape is taken for up to kSplitWgs workgroups of the other one,
+  // each of at most 256 rows, for which it has up to 8 slabs (32 rows each);
+  // calls of fewer rows, slice layers or observers than sized for fit as well
+  const size_t few = std::min(nobs * planes * sp.n_slab, (size_t)kSplitWgs * 8);
   size_t b = 0;
   // offsets, counts, chains, credited-block flags and list (each carve
   // rounds up to 256 B)
   b += nobs * (8 * 2 + 4 * 4) + nobs * MAXD * 4 + (size_t)sz->num_nodes * 20 +
        (size_t)sz->num_tokens / kWave * 8 + 14 * 256;
   // partials
-  b += std::max(nobs * slabs, few * planes * sp.n_slab) * (size_t)sz->max_context * 4 + 256;
+  b += std::max(nobs * slabs, few) * (size_t)sz->max_context * 4 + 256;
   // sub-page tables: at most one ragged sub-page per chain node
   b += nobs * ((size_t)sz->max_context / 16 + MAXD + 1) * 16 + 256;
   return b;
