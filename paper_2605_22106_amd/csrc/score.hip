@@ -1184,8 +1184,9 @@ struct FinalArgs {
 // workgroup), are added in slab order (fp32, sixteen loads in flight); the W
 // waves split the observers and are combined in wave order (fp64).
 // (With a launch of its own for the slab sums, 16 leaves over a 341-block tree
-// took 3.4 + 7.3 us, now 5.4; 85 observers of the 8B shape 4.9 + 5.8, now 8.9;
-// 341 of the 70B shape 23 + 20, now 44.)
+// took 3.4 + 7.3 us, now 5.4; 85 observers of the 8B shape 4.8 + 6.1, now 8.1;
+// 341 of the 70B shape 23 + 21, now 45.)
+constexpr int kCutChunks = 32;   // a root of more chunks is not cut into parts (below)
 template <int W>
 __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2 *__restrict__ cred,
                                                          float *__restrict__ A,
@@ -1204,6 +1205,8 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
   const int tid = threadIdx.x;
   const int n_items = cred[0].x;
   int2 item = cred[1 + blockIdx.x];
+  const int2 first = cred[1];
+  const int c_root = a.t.n_kept[0];
   const bool o0 = tid < a.n_obs && tid < HB;
   const int od0 = o0 ? a.odepth[tid] : -1, len0 = o0 ? a.ctxlen[tid] : 0;
   const int64_t pb0 = o0 ? a.pbase[tid] : 0;
@@ -1214,10 +1217,25 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nslab = a.S * pl.Hkv * a.n_slab;
-  for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
-    if (w != (int)blockIdx.x) item = cred[1 + w];
+  // many observers: every one of them is below the root, whose chunks would
+  // take the longest, so each is cut into four parts of 16 slots, in which four
+  // observers are added at a time; parts 1 to 3 follow the list.  A root of 16
+  // chunks below 340 observers takes 20.2 us instead of 28.0, below 84 8.1
+  // instead of 9.5; one of 64 chunks keeps the chip busy uncut (45.1 us, cut 47.7)
+  int n_root = W > 4 && n_items > 0 && first.x == 0 ? max(1, (c_root + kWave - 1) / kWave) : 0;
+  if (n_root > kCutChunks) n_root = 0;
+  for (int w = blockIdx.x; w < n_items + 3 * n_root; w += gridDim.x) {
+    int part = 0;
+    if (w >= n_items) {
+      item = make_int2(0, (w - n_items) / 3);
+      part = 1 + (w - n_items) % 3;
+    } else if (w != (int)blockIdx.x) {
+      item = cred[1 + w];
+    }
     const int i = item.x, chk = item.y;
-    const int s = chk * kWave + lane;
+    const bool cut = i == 0 && n_root > 0;
+    const int obs_of = cut ? lane >> 4 : 0, step = cut ? 4 : 1;
+    const int s = chk * kWave + (cut ? 16 * part + (lane & 15) : lane);
     const int c = t.n_kept[i];
     // (every credited block lies on an observer's chain, whose depth and
     // context offset the setup recorded)
@@ -1226,7 +1244,7 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
     const bool live = s < c;
     int64_t tok = 0;
     float a_old = 0.f;
-    if (wave == 0 && live) {              // (ahead of the sums)
+    if (wave == 0 && live && obs_of == 0) {   // (ahead of the sums)
       const int page = t.page_table[po + s / pl.P];
       tok = tb + pl.slot_pos[(int64_t)page * pl.P + s % pl.P];
       a_old = A[tok];
@@ -1255,11 +1273,11 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
         const int at = before + rank_below(bm, lane);
         hbase[at] = (ob == 0 ? pb0 : a.pbase[o]) + ctxoff;
         hlen[at] = ob == 0 ? len0 : a.ctxlen[o];
-        if (chk == 0) rows_add += (int64_t)a.S * pl.Hkv * pl.G * min(a.W, t.n_full[jo]);
+        if (chk == 0 && part == 0) rows_add += (int64_t)a.S * pl.Hkv * pl.G * min(a.W, t.n_full[jo]);
       }
       __syncthreads();
       if (live) {
-        for (int h = wave; h < nh; h += W) {
+        for (int h = wave * step + obs_of; h < nh; h += W * step) {
           const float *src = a.part + hbase[h] + s;
           const int64_t len = hlen[h];
           float f = 0.f;
@@ -1284,13 +1302,17 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
     }
     s_acc[wave][lane] = acc;
     __syncthreads();
-    if (wave == 0 && live) {
+    if (wave == 0) {
       double tot = 0.0;
 #pragma unroll
       for (int v = 0; v < W; ++v) tot += s_acc[v][lane];
-      A[tok] = (float)((double)a_old + tot);
+      if (cut) {
+        tot += __shfl_xor(tot, 16, kWave);
+        tot += __shfl_xor(tot, 32, kWave);
+      }
+      if (live && obs_of == 0) A[tok] = (float)((double)a_old + tot);
     }
-    if (chk == 0) {
+    if (chk == 0 && part == 0) {
       rows_add = block_sum<int64_t>(rows_add, s_sum);
       if (tid == 0) rows_seen[i] += rows_add;
     }

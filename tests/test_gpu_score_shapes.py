@@ -68,3 +68,19 @@ def test_score_one_observer_of_a_large_tree(sw):
     A, rows, _, _, sg = _gpu_score(st, kv, p, A0=A0, observers=torch.tensor([1], dtype=torch.int32))
     assert sg == L.EINVAL
     assert np.array_equal(A, A0) and not rows.any()
+
+
+@pytest.mark.parametrize("n_root,n_obs", [(1, 33), (15, 300), (16, 34), (17, 257), (64, 63),
+                                          (65, 300), (129, 40), (2048, 33), (2049, 33)])
+def test_score_root_parts_of_many_observers(n_root, n_obs):
+    """More than 32 observers: the root's chunks are reduced in parts of 16 slots and
+    groups of four observers, 256 observers at a time; beyond 2,048 slots uncut."""
+    parent, n_full = synth.random_tree(n_obs + 1, 20, n_obs)
+    n_full[0] = n_root
+    st = synth.build_state(parent, n_full, layers=2, kv_heads=2, q_per_kv=2, head_dim=64,
+                           dtype="bf16", seed=n_root, shuffle_pages=True, window=3,
+                           active=[n_obs], host_store=False)
+    kv, ost = to_gpu(st), oracle_state(st)
+    for sw in (0, 1):
+        _both(st, kv, ost, list(range(1, n_obs + 1)),
+              dict(PARAMS, score_self_window=sw))
