@@ -66,7 +66,8 @@ typedef enum {
   ARBOR_EUNSUPPORTED = -4,  /* shape outside what the kernels implement            */
   ARBOR_ENONFINITE = -5,    /* NaN in A or s; NaN or infinite logit                */
   ARBOR_EWORKSPACE = -6,    /* workspace too small for this tree                   */
-  ARBOR_ECORRUPT = -7       /* pool bookkeeping inconsistent (free stack overflow) */
+  ARBOR_ECORRUPT = -7       /* bookkeeping inconsistent (free stack overflow; a
+                               workspace that changed during a call)               */
 } arbor_status_t;
 
 typedef enum { ARBOR_BF16 = 0, ARBOR_F32 = 1 } arbor_dtype_t;
@@ -246,7 +247,8 @@ int arbor_score(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbor_
  * int32 [V].  fp64 arithmetic, no contraction; s^gamma is correctly rounded
  * for gamma in {1, 2, 3, 4} and the device pow otherwise.
  * Errors: EINVAL (malformed tree, bad leaf ids, n_active < 1, an off-path s
- * outside [0, 1]), ENONFINITE (NaN s off the path).
+ * outside [0, 1]), ENONFINITE (NaN s off the path), ECORRUPT (the workspace
+ * changed during the call).
  */
 int arbor_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_active,
                    int64_t budget_tokens, const float *s, const arbor_params_t *params,

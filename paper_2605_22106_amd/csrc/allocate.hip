@@ -834,17 +834,17 @@ __global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget,
     int64_t ex[2], tot[2];
     __syncthreads();                       // (the search's last reads of its exchange)
     block_exclusive_scan_n<2>(v2, ex, tot, sm);
-    if (tot[0] > E || tot[0] + tot[1] <= E) {
-      if (exact) return;                   // (cannot be: the counts were exact)
-      continue;
-    }
-    if (kb - ka <= 1) {
+    const bool held = tot[0] <= E && tot[0] + tot[1] > E;
+    if (held && kb - ka <= 1) {
       answer = (uint64_t)kb;
       break;
     }
-    if (tot[1] > kCandLds) {
-      if (exact) return;
-      continue;
+    if (!held || tot[1] > kCandLds) {
+      if (!exact) continue;
+      // exact counts that do not agree with themselves: the blocks changed
+      // under the search.  No count was written, so no later launch may run.
+      if (tid == 0) status_error(status, ARBOR_ECORRUPT);
+      return;
     }
     // the listed prices and their order statistic
     if (mine > 0) {
