@@ -725,7 +725,8 @@ __global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget,
     });
     return;
   }
-  // the thread's floors (a block's count is floor(x W), clamped, less its floor)
+  // the floors of the thread's register slots, padding included (a slot's count
+  // is floor(x W), clamped, less its floor)
   double F0 = 0.0;
   each_reg([&](int, const Blk &n) __attribute__((always_inline)) { F0 += n.lo; });
   uint64_t answer = 0;
@@ -775,7 +776,7 @@ __global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget,
       for (int q = 0; q < kCutPts; ++q) {
         x[q] = min(max(x[q], ka + 1), kb - 1);
         xv[q] = key_value((uint64_t)x[q]);
-        c[q] = -F0;
+        c[q] = exact ? 0.0 : -F0;
       }
       if (!exact) {
         each_reg([&](int, const Blk &n) __attribute__((always_inline)) {
@@ -784,9 +785,11 @@ __global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget,
             c[q] += __builtin_fmin(__builtin_fmax(__builtin_floor(xv[q] * n.W), n.lo), n.hi);
         });
       } else {
+        // (over the blocks alone, without the slots' padding: each brings its floor)
         each([&](int, const Blk &n) __attribute__((always_inline)) {
 #pragma unroll
-          for (int q = 0; q < kCutPts; ++q) c[q] += (double)last_le(xv[q], n.F(), n.cnt(), n.W);
+          for (int q = 0; q < kCutPts; ++q)
+            c[q] += (double)(last_le(xv[q], n.F(), n.cnt(), n.W) - n.F());
         });
       }
       static_assert(kCutPts == 3, "one block_sum3_f64 per round");
