@@ -1206,6 +1206,17 @@ int launch_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_a
                     void *workspace, size_t workspace_bytes, hipStream_t stream, int gate) {
   Tree t = make_tree(tree);
   if (t.V <= 0) return ARBOR_OK;
+  // (a workspace too small is refused for trees of any size, also for those whose
+  // state fits LDS)
+  const int n_wg = (t.V + kNodeThreads - 1) / kNodeThreads;
+  Carve cv(workspace, workspace_bytes);
+  AllocWs ws;
+  ws.down = cv.take<int32_t>(t.V);
+  ws.rec = cv.take<NodeRec>(t.V);
+  ws.w = cv.take<double>(t.V);
+  ws.sums = cv.take<NodeSums>(n_wg);
+  ws.gated = cv.take<int32_t>(1);
+  if (!cv.ok) return ARBOR_EWORKSPACE;
   AllocParams p{params->alpha_max, params->gamma, params->lambda_d, params->lambda_delta,
                 params->eta, params->r_min, params->k_min, params->l_tail,
                 params->lazy_rehydration, params->k_protect, {}, {}};
@@ -1221,15 +1232,6 @@ int launch_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_a
                        (int64_t)budget_tokens, s, p, k_out, delta_out, on_path_out, status, gate);
     return hip_ok(hipGetLastError());
   }
-  const int n_wg = (t.V + kNodeThreads - 1) / kNodeThreads;
-  Carve cv(workspace, workspace_bytes);
-  AllocWs ws;
-  ws.down = cv.take<int32_t>(t.V);
-  ws.rec = cv.take<NodeRec>(t.V);
-  ws.w = cv.take<double>(t.V);
-  ws.sums = cv.take<NodeSums>(n_wg);
-  ws.gated = cv.take<int32_t>(1);
-  if (!cv.ok) return ARBOR_EWORKSPACE;
 #define ARBOR_NODES_ARGS                                                                         \
   t, active, n_active, (int64_t)budget_tokens, s, p, k_out, delta_out, on_path_out, status, ws, gate
   if (t.V <= kGeoNodes) {

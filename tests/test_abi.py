@@ -8,6 +8,7 @@ import re
 import pytest
 
 from paper_2605_22106_amd import _lib as L
+from paper_2605_22106_amd import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -138,3 +139,15 @@ def test_a_workspace_also_fits_every_smaller_call(dtype):
         nb, ns = (lib.arbor_workspace_size(ctypes.byref(g), ctypes.byref(
             L.Sizes(341, 40000, 5120, *x))) for x in (big, small))
         assert ns <= nb, (big, small)
+
+
+@pytest.mark.parametrize("nodes", [1, 13, 512, 513, 20000])
+def test_allocate_refuses_a_small_workspace(nodes):
+    """Before anything is enqueued, also where the kernel keeps its state in LDS."""
+    lib, any_ptr = L.load(), 256
+    t = L.TreeS(nodes, 40 * nodes, *([any_ptr] * 6))
+    p = L.params_struct(dict(synth.DEFAULT_PARAMS))
+    for ws, size in ((None, 0), (any_ptr, 8 * nodes)):
+        assert lib.arbor_allocate(ctypes.byref(t), any_ptr, 1, 100, any_ptr, ctypes.byref(p),
+                                  any_ptr, any_ptr, any_ptr, any_ptr, ws, size,
+                                  None) == L.EWORKSPACE
