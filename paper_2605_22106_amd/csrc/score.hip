@@ -922,10 +922,21 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
   for (int o = tid; o < a.n_obs; o += nt) {
     tbase[o] = tab0 + 4 * tbase[o];
   }
+  // a malformed tree comes before the other errors.  Where other workgroups check
+  // the nodes (lone), those wait for the reduction's launch to raise them, and
+  // the attention meanwhile finds a chain without keys.
+  int later = 0;
   if (tid == 0) {
-    if (s_err & 1) status_error(a.status, ARBOR_EINVAL);
-    else if (s_err & 2) status_error(a.status, ARBOR_EUNSUPPORTED);
-    else if (!fits) status_error(a.status, ARBOR_EWORKSPACE);
+    const int code = (s_err & 1)   ? ARBOR_EINVAL
+                     : (s_err & 2) ? ARBOR_EUNSUPPORTED
+                     : !fits       ? ARBOR_EWORKSPACE
+                                   : ARBOR_OK;
+    if (lone && code != ARBOR_EINVAL) {
+      later = code;
+      if (later < 0) nsp[0] = nsp[1] = 0;
+    } else if (code < 0) {
+      status_error(a.status, code);
+    }
   }
   // the credited blocks' 64-slot chunks in ascending block id (one at least for
   // each: its first chunk also counts the rows)
@@ -977,7 +988,7 @@ __device__ __forceinline__ void setup_body(const ScoreArgs &a, int64_t part_cap,
         }
     }
   }
-  if (tid == 0) cred[0].x = (s_err || !fits) ? 0 : (int32_t)min(crun, room);
+  if (tid == 0) cred[0] = make_int2((s_err || !fits) ? 0 : (int32_t)min(crun, room), later);
 }
 
 template <bool IN_LDS>
@@ -1203,7 +1214,8 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
   // allocated, and unused then; so are the first observers' fields, which do
   // not depend on the block)
   const int tid = threadIdx.x;
-  const int n_items = cred[0].x;
+  const int2 head = cred[0];
+  const int n_items = head.x;
   int2 item = cred[1 + blockIdx.x];
   const int2 first = cred[1];
   const int c_root = a.t.n_kept[0];
@@ -1212,6 +1224,10 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
   const int64_t pb0 = o0 ? a.pbase[tid] : 0;
   const int obs0 = o0 ? a.obs[tid] : -1;
   if (status_failed(a.status)) return;
+  if (head.y < 0) {               // an error that the setup left to this launch
+    if (blockIdx.x == 0 && tid == 0) status_error(a.status, head.y);
+    return;
+  }
   const Tree &t = a.t;
   const Pool &pl = a.pl;
   const int lane = lane_id();

@@ -9,7 +9,7 @@ import torch
 from oracle import arbor_oracle as O
 from paper_2605_22106_amd import _lib as L
 from paper_2605_22106_amd import synth
-from tests.gpu_helpers import status, to_gpu, workspace
+from tests.gpu_helpers import check_rc, status, to_gpu, workspace
 from tests.helpers import np_float, oracle_state
 from tests.test_gpu_parity import PARAMS, _close, _gpu_score
 
@@ -84,3 +84,36 @@ def test_score_root_parts_of_many_observers(n_root, n_obs):
     for sw in (0, 1):
         _both(st, kv, ost, list(range(1, n_obs + 1)),
               dict(PARAMS, score_self_window=sw))
+
+
+@pytest.mark.parametrize("deep,small,malformed,code", [
+    (True, False, False, L.EUNSUPPORTED), (True, False, True, L.EINVAL),
+    (False, True, False, L.EWORKSPACE), (False, True, True, L.EINVAL),
+    (False, False, True, L.EINVAL), (True, True, True, L.EINVAL)])
+def test_score_one_observer_error_codes(deep, small, malformed, code):
+    """One observer over a large tree: the blocks are checked by other workgroups than its
+    chain and the workspace, and a malformed block comes first whatever finds out first."""
+    V, tail = 4200, 64 if deep else 40                 # a chain of tail + 1 blocks, then leaves
+    parent = [-1] + list(range(tail)) + [0] * (V - 1 - tail)
+    n_full = [200] + [20] * tail + [2] * (V - 1 - tail)
+    st = synth.build_state(parent, n_full, layers=1, kv_heads=2, q_per_kv=2, head_dim=64,
+                           dtype="bf16", seed=1, window=5, active=[tail], observers=[tail],
+                           host_store=False)
+    kv = to_gpu(st)
+    if malformed:
+        kv.n_kept[V - 3] = n_full[V - 3] + 1
+    ws = workspace(kv, max_observers=1, window=5, n_slice=1)
+    if small:                                          # room for the offsets and chains only
+        ws = ws[:20 * V + st["num_tokens"] // 8 + 16 * 256]
+    g = torch.Generator().manual_seed(3)
+    A0, rows0 = torch.rand(st["num_tokens"], generator=g), torch.arange(V)
+    a0, s0 = torch.rand(V, generator=g), torch.rand(V, generator=g)
+    for _ in range(20):
+        A, rows, a, s, stt = A0.cuda(), rows0.cuda(), a0.cuda(), s0.cuda(), status()
+        check_rc(L.arbor_score(kv, st["observers"].cuda(), st["q_win"].cuda().contiguous(), 5, [0],
+                               st["v_sig"].cuda(), st["u_sig"].cuda(), A, rows, a, s, PARAMS, stt,
+                               ws))
+        torch.cuda.synchronize()
+        assert int(stt) == code
+        for x, y in ((A, A0), (rows, rows0), (a, a0), (s, s0)):
+            assert torch.equal(x.cpu(), y)
