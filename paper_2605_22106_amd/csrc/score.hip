@@ -1432,10 +1432,12 @@ size_t score_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   const size_t nobs = (size_t)(sz->max_observers > 0 ? sz->max_observers : 0);
   const size_t planes = (size_t)sz->n_slice * g->num_kv_heads;
   const Shape st = stream_shape(rows_total, g->dtype), sp = split_shape(rows_total, g->dtype);
-  const size_t slabs = planes * st.n_slab;
+  // the stream shape's slabs of any row count up to this one: three row groups make
+  // two, four make one again, from where on they only grow
+  const size_t slabs = planes * std::max(st.n_slab, st.n_rg >= 3 ? 2 : 1);
   // the split shape is taken for up to kSplitWgs workgroups of the other one,
-  // each of at most 256 rows, for which it has up to 8 slabs (32 rows each);
-  // calls of fewer rows, slice layers or observers than sized for fit as well
+  // each of at most 256 rows, for which it has up to 8 slabs (32 rows each).
+  // So calls of fewer rows, slice layers or observers than sized for fit as well.
   const size_t few = std::min(nobs * planes * sp.n_slab, (size_t)kSplitWgs * 8);
   size_t b = 0;
   // offsets, counts, chains, credited-block flags and list (each carve
