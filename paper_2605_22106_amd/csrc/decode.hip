@@ -39,6 +39,7 @@ constexpr int kChunks[] = {1024, 512, 256, 128, 64};
 constexpr int kNChunks = 5;
 constexpr int kMinChunk = 64, kMaxChunk = 1024;
 constexpr int kMinUnits = 4096;
+constexpr int kPartSlots = 256;   // slots of a unit that share a reference max
 constexpr int kPlanLds = 4096;    // trees up to this many nodes are walked from LDS
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -441,15 +442,15 @@ __device__ __forceinline__ KVFrag<T, D, GSP> fetch_kv(const UnitAddr &ua, int pg
 // Online-softmax update of one wave's rows with one fragment.  Slots past a
 // sub-page's resident count may hold anything: only a ragged sub-page (the
 // last of a node) masks its logits and zeroes its value rows.  The output is
-// rescaled only when some row's running max moved.
-// zs (when keep_z) receives the fragment's masked logits in log2 units, the
-// weights the decode-time credit normalises later; the caller stores them.
+// rescaled only when some row's running max moved.  A logit is scaled and
+// taken relative to the max in one fused step, so it is rounded once.
+// zs (when keep_z) receives the fragment's masked products of query and key,
+// which the decode-time credit turns into weights later; the caller stores them.
 template <class T, int D, int GSP>
 __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
                                        const typename Op<T>::reg (&q)[KVFrag<T, D, GSP>::KS],
                                        float sl2, int g4, float &m_run, float &l_run,
-                                       f32x4 (&o)[D / 16], f32x4 (&ot)[D / 16], bool keep_z,
-                                       float (&zs)[GSP][4]) {
+                                       f32x4 (&o)[D / 16], bool keep_z, float (&zs)[GSP][4]) {
   typedef KVFrag<T, D, GSP> F;
   constexpr int NC = F::NC;
   float sv[GSP][4];
@@ -460,7 +461,7 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
 #pragma unroll
     for (int ks = 0; ks < F::KS; ++ks) acc = Op<T>::mma(f.k[sp][ks], q[ks], acc);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sv[sp][e] = acc[e] * sl2;
+    for (int e = 0; e < 4; ++e) sv[sp][e] = acc[e];
     if (f.nval[sp] < 16) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -478,7 +479,7 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
     }
   }
   gmax = across_rows(gmax, [](float x, float y) { return fmaxf(x, y); });
-  const float mn = fmaxf(m_run, gmax);
+  const float mn = fmaxf(m_run, gmax * sl2);
   const bool moved = mn != m_run;
   const float alpha = m_run > -__builtin_inff() ? __builtin_amdgcn_exp2f(m_run - mn) : 0.f;
   m_run = mn;
@@ -488,10 +489,7 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
     for (int e = 0; e < 4; ++e) {
       const float fe = __shfl(alpha, 4 * g4 + e, kWave);
 #pragma unroll
-      for (int cc = 0; cc < NC; ++cc) {
-        o[cc][e] *= fe;
-        ot[cc][e] *= fe;
-      }
+      for (int cc = 0; cc < NC; ++cc) o[cc][e] *= fe;
     }
   }
   const float nm = m_run > -__builtin_inff() ? -m_run : 0.f;
@@ -510,12 +508,14 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const int sp = sp0 + t / 4, e = t % 4;
-        p[t] = sp < GSP ? __builtin_amdgcn_exp2f(sv[sp < GSP ? sp : 0][e] + nm) : 0.f;
+        p[t] = sp < GSP ? __builtin_amdgcn_exp2f(
+                              __builtin_fmaf(sv[sp < GSP ? sp : 0][e], sl2, nm))
+                        : 0.f;
         const __bf16 hi = (__bf16)p[t];
         ph[t] = hi;
         pl[t] = (__bf16)(p[t] - (float)hi);
       }
-      // (pairwise: the running sum of a 1,024-slot chunk takes 32 terms, not 256)
+      // (pairwise: the running sum of 256 slots takes 8 terms, not 64)
       l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
@@ -534,7 +534,8 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
     for (int sp = 0; sp < GSP; ++sp) {
       float p[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(sv[sp][e] + nm);
+      for (int e = 0; e < 4; ++e)
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[sp][e], sl2, nm));
       l_run += (p[0] + p[1]) + (p[2] + p[3]);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
@@ -621,13 +622,46 @@ __device__ __forceinline__ void decode_unit(const DecArgs &a, const Meta &mt, co
     }
   F cur = fetch_kv<T, D, GSP>(ua, pg, s_begin, s_end, n_sub, 0, pl.P);
   float m_run = -__builtin_inff(), l_run = 0.f;
-  // o holds the sums of up to kFlush slots, ot those before: a chunk of 1,024
-  // slots is summed to the accuracy of one of 256 (one level: 4.9e-7 from the
-  // 64-bit outputs on the 70B shape, against 4.1e-7)
-  constexpr int kFlush = 256 / (16 * GSP);
-  f32x4 o[NC], ot[NC];
+  f32x4 o[NC];
 #pragma unroll
-  for (int cc = 0; cc < NC; ++cc) o[cc] = ot[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int cc = 0; cc < NC; ++cc) o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // A longer unit is summed in parts of kPartSlots, each against its own max, and
+  // the parts are merged as partials of units of that size would be: weights far
+  // below the max carry the rounding of their distance to it, so one max for
+  // 1,024 slots lost accuracy (fp32 outputs of the 70B shape, nodes of 512
+  // slots: 4.4e-7 from 64 bits, in parts 3.6e-7).
+  constexpr int kPart = kPartSlots / (16 * GSP);
+  float m_tot, l_tot;               // (set by the first part)
+  f32x4 ot[NC];
+  auto first_part = [&]() __attribute__((always_inline)) {
+    m_tot = m_run;
+    l_tot = l_run;
+    m_run = -__builtin_inff();
+    l_run = 0.f;
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      ot[cc] = o[cc];
+      o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  auto merge_part = [&]() __attribute__((always_inline)) {
+    const float mn = fmaxf(m_tot, m_run);
+    const float ft = m_tot > -__builtin_inff() ? __builtin_amdgcn_exp2f(m_tot - mn) : 0.f;
+    const float fr = m_run > -__builtin_inff() ? __builtin_amdgcn_exp2f(m_run - mn) : 0.f;
+    l_tot = __builtin_fmaf(l_tot, ft, l_run * fr);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float te = __shfl(ft, 4 * g4 + e, kWave), re = __shfl(fr, 4 * g4 + e, kWave);
+#pragma unroll
+      for (int cc = 0; cc < NC; ++cc) {
+        ot[cc][e] = __builtin_fmaf(ot[cc][e], te, o[cc][e] * re);
+        o[cc][e] = 0.f;
+      }
+    }
+    m_tot = mn;
+    m_run = -__builtin_inff();
+    l_run = 0.f;
+  };
   // the logits of fragment gi are stored after fragment gi + 1's loads are
   // issued: a wave's loads and stores share one counter, so a wait for loads
   // issued after the stores would wait for the stores as well
@@ -645,17 +679,19 @@ __device__ __forceinline__ void decode_unit(const DecArgs &a, const Meta &mt, co
       cur = fetch_kv<T, D, GSP>(ua, pg, s_begin, s_end, n_sub, gi * GSP, pl.P);
       if (KZ && zrow) store_z(gi - 1);
     }
-    attend<T, D, GSP>(cur, q, a.sl2, g4, m_run, l_run, o, ot, KZ && zrow != nullptr, zs);
-    if (gi % kFlush == kFlush - 1) {
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) {
-        ot[cc] += o[cc];
-        o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    attend<T, D, GSP>(cur, q, a.sl2, g4, m_run, l_run, o, KZ && zrow != nullptr, zs);
+    if (gi % kPart == kPart - 1 && gi + 1 < n_grp) {
+      if (gi < kPart) first_part();
+      else merge_part();
     }
   }
+  if (n_grp > kPart) {
+    merge_part();
+    m_run = m_tot;
+    l_run = l_tot;
 #pragma unroll
-  for (int cc = 0; cc < NC; ++cc) o[cc] += ot[cc];
+    for (int cc = 0; cc < NC; ++cc) o[cc] = ot[cc];
+  }
   if (KZ && zrow && n_grp > 0) store_z(n_grp - 1);
   // partial rows of this unit: (max, sum) pairs and outputs
   const int64_t prow = ((int64_t)lr * pl.Hkv + g) * mt.rows + un.rowbase;
@@ -840,20 +876,21 @@ __device__ __forceinline__ void merge_rows(const DecArgs &a, const Meta &mt, voi
   }
 }
 
-// Decode-time credit (Sec. 4 Execution (iii)): the softmax weight exp2(z -
-// lse2) of every decode query row on every key of a unit, from the logits z
-// the attention units kept for the credited slice layers, summed over the
-// rows whose leaf lies strictly below the unit's node (and, in the
-// self-window mode, the leaf's own rows on keys before its newest position)
-// and over the slice layers (a layer listed m times counts m times) and kv
-// heads, and added to A at the key's token.  A row's log2 LSE, lse2 = M +
-// log2(sum_k l_k exp2(m_k - M)) over the (max m_k, sum l_k) of the partials of
-// its leaf's chain, is formed here from those partials, so the credit does not
-// wait for the merge and runs beside it in the same launch.
+// Decode-time credit (Sec. 4 Execution (iii)): the softmax weight exp2(c z - M)
+// / L of every decode query row on every key of a unit, from the products z of
+// query and key that the attention units kept for the credited slice layers (c
+// the softmax scale in log2 units), summed over the rows whose leaf lies
+// strictly below the unit's node (and, in the self-window mode, the leaf's own
+// rows on keys before its newest position) and over the slice layers (a layer
+// listed m times counts m times) and kv heads, and added to A at the key's
+// token.  A row's max M and sum L = sum_k l_k exp2(m_k - M) over the (max m_k,
+// sum l_k) of the partials of its leaf's chain are formed here from those
+// partials, so the credit does not wait for the merge and runs beside it in the
+// same launch.
 // One workgroup of kCreditWaves waves per 64 slots of a chunk, one lane per
 // slot.  The unit's (row, distinct slice layer, kv head) triples, in
 // the order (z * Hkv + g) * R + r, are staged in LDS up to kCreditTile at a
-// time: each triple's lse2 and its weight, the layer's multiplicity, in one of
+// time: each triple's M and its weight, the layer's multiplicity over L, in one of
 // two tables, for the rows of other leaves and for the node's own.  Rows are
 // innermost because the (max, sum) pairs of a partial's rows lie side by side,
 // so that the lanes of a load share cache lines (with the kv heads innermost
@@ -949,7 +986,7 @@ __device__ __forceinline__ float2 chain_ml(const DecArgs &a, const Meta &mt, int
 __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
                                               const CreditArgs &cr, int blk, int nblk) {
   __shared__ float s_oth[kCreditWaves][kWave], s_own[kCreditWaves][kWave];
-  __shared__ float s_l2[kCreditTile], s_wo[kCreditTile], s_wn[kCreditTile];
+  __shared__ float s_m[kCreditTile], s_wo[kCreditTile], s_wn[kCreditTile];
   __shared__ float2 s_ml[kCreditThreads];
   const Tree &t = a.t;
   const Pool &pl = a.pl;
@@ -971,6 +1008,9 @@ __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
   const float *z0 = a.rest + mt.z;
   const int64_t z_slab = (int64_t)mt.z_total * 64;
   const int per = cr.U * Hkv;
+  // (in a vector register: the fused step below reads one scalar register, M)
+  float c2 = a.sl2;
+  asm volatile("" : "+v"(c2));
   const int pieces = mt.chunk / kWave;
   constexpr int kLast = kCreditWaves - 1;
   for (int64_t w = blk; w < (int64_t)mt.n_units * pieces; w += nblk) {
@@ -1032,13 +1072,14 @@ __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
       if (mine && tj == 0) {
         float2 v = s_ml[ti];
         for (int j = 1; j < tpt; ++j) v = ml_merge(v, s_ml[j * tri + ti]);
-        const float m = (float)cr.mult[z];
+        // (M + log2 L in one number would round M's distance to the logits)
+        const float m = v.y > 0.f ? (float)cr.mult[z] / v.y : 0.f;
         const bool own_row = a.leaves[b] == node;
-        s_l2[ti] = v.y > 0.f ? v.x + __log2f(v.y) : -__builtin_inff();
+        s_m[ti] = v.y > 0.f ? v.x : __builtin_inff();
         s_wo[ti] = own_row ? 0.f : m;
         s_wn[ti] = own_row ? m : 0.f;
       } else if ((int)threadIdx.x >= nt) {
-        s_l2[threadIdx.x] = s_wo[threadIdx.x] = s_wn[threadIdx.x] = 0.f;
+        s_m[threadIdx.x] = s_wo[threadIdx.x] = s_wn[threadIdx.x] = 0.f;
       }
       __syncthreads();
       for (; e0 < t0 + nt; e0 += kCreditWaves * kCreditBatch) {
@@ -1047,10 +1088,12 @@ __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
         if (more) credit_load(nxt, zb, it, R, per, z_slab, zstride);
         static_assert(kCreditBatch == 16, "one row of lanes per batch");
         const int i = e0 - t0 + kCreditWaves * (lane & (kCreditBatch - 1));
-        const float l2 = s_l2[i], wo = s_wo[i], wn = s_wn[i];
+        const float mx = s_m[i], wo = s_wo[i], wn = s_wn[i];
 #pragma unroll
         for (int u = 0; u < kCreditBatch; ++u) {
-          const float p = key_ok ? __builtin_amdgcn_exp2f(cur[u] - lane_value(l2, u)) : 0.f;
+          const float p = key_ok ? __builtin_amdgcn_exp2f(
+                                       __builtin_fmaf(cur[u], c2, -lane_value(mx, u)))
+                                 : 0.f;
           oth = __builtin_fmaf(lane_value(wo, u), p, oth);
           own = __builtin_fmaf(lane_value(wn, u), p, own);
         }

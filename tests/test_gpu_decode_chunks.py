@@ -72,3 +72,48 @@ def test_decode_chunks(layers, root, leaves, G, dtype):
                                      np.zeros(kv.num_nodes, np.int64), self_window=1)
             assert np.allclose(A.cpu().numpy(), Ao, rtol=1e-4, atol=1e-30)
             assert np.array_equal(rows.cpu().numpy(), ro)
+
+
+@pytest.mark.parametrize("node,d,step", [(512, 128, 16), (1024, 64, 8), (1500, 64, 8)])
+def test_decode_long_chunks_are_as_accurate_as_short_ones(node, d, step):
+    """64 layers in one call (chunks of 1,024 slots) and in calls of `step` layers (256
+    slots): the fp32 outputs of the first are no further from 64 bits (the two per cent are
+    the spread of a norm over 262,144 rounded values and more).  Heavy keys spread the
+    logits, so that most weights lie far below their row's max."""
+    layers, G = 64, 8
+    parent = [-1, 0, 0, 1, 1, 2, 2]
+    n_full = [2 * node + 40] + [node] * 6
+    leaves = [3, 4, 5, 6] * 2
+    st = synth.build_state(parent, n_full, layers=layers, kv_heads=8, q_per_kv=G, head_dim=d,
+                           dtype="bf16", seed=node, shuffle_pages=True, heavy_frac=0.02,
+                           active=leaves, host_store=False)
+    kv = to_gpu(st)
+    q = st["q_dec"].cuda().contiguous()
+    lt = torch.tensor(leaves, dtype=torch.int32, device="cuda")
+    ws = workspace(kv, max_leaves=len(leaves), max_layers=layers)
+    stt = status()
+    whole, each = (torch.empty((len(leaves), layers, 8 * G, d), device="cuda") for _ in range(2))
+    check_rc(L.arbor_tree_decode_attn(kv, lt, 0, layers, q, whole, None, 0.0, stt, ws))
+    for l in range(0, layers, step):
+        out = torch.empty((len(leaves), step, 8 * G, d), device="cuda")
+        check_rc(L.arbor_tree_decode_attn(kv, lt, l, l + step, q[:, l:l + step].contiguous(), out,
+                                          None, 0.0, stt, ws))
+        each[:, l:l + step] = out
+    torch.cuda.synchronize()
+    assert int(stt) == L.OK
+    po, P = st["page_off"].tolist(), st["page_size"]
+    num = torch.zeros(2, dtype=torch.float64)
+    den = 0.0
+    for b, chain in enumerate(([0, 1, 3], [0, 1, 4], [0, 2, 5], [0, 2, 6])):
+        idx = torch.cat([(kv.page_table[po[i]:po[i + 1]].long()[:, None] * P +
+                          torch.arange(P, device="cuda")).flatten()[:n_full[i]] for i in chain])
+        for l in range(layers):
+            k, v = (t[l].transpose(1, 2).reshape(-1, 8, d)[idx].double().transpose(0, 1).contiguous()
+                    for t in (kv.k, kv.v))
+            z = torch.bmm(q[b, l].view(8, G, d).double(), k.transpose(1, 2).contiguous()) / d ** 0.5
+            o = torch.bmm(torch.softmax(z, -1), v).view(8 * G, d)
+            den += float((o * o).sum())
+            for x, t in enumerate((whole, each)):
+                num[x] += float((t[b, l].double() - o).square().sum())
+    err = (num / den).sqrt().tolist()
+    assert err[0] <= 1.02 * err[1], err
