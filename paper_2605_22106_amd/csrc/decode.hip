@@ -27,7 +27,7 @@ namespace {
 constexpr int MAXD = ARBOR_MAX_DEPTH + 1;
 static_assert(MAXD == kWave, "one wave covers a chain");
 // Slots of a chain node that one work unit takes: the plan picks the largest
-// of kChunks that still gives kMinUnits units, so that a call over few keys
+// of kChunks that still gives kMinUnits units (fp32 pools: below), so that a call over few keys
 // (one layer of a model's own loop) is cut finely enough to fill the chip and
 // one over many keys writes and merges few partials.  Measured: one layer of a
 // 341-block tree under 16 leaves takes 35 us at 64 slots, 91 at the former 256
@@ -40,6 +40,14 @@ constexpr int kNChunks = 5;
 constexpr int kMinChunk = 64, kMaxChunk = 1024;
 constexpr int kMinUnits = 4096;
 constexpr int kPartSlots = 256;   // slots of a unit that share a reference max
+// fp32 pools, whose slots are twice the bytes: units of at most 256 slots (so
+// none is summed in parts, whose second accumulator would leave two waves per
+// SIMD instead of three), and half as many of them are enough.  16 layers of the
+// 8B shape take 109.7 us with at least 2,048 units of 256 slots, 119 with
+// 4,096 of 128; 8 layers of the 70B shape 306 us, with units of 512 slots in parts 390.
+constexpr int kFirstChunkF32 = 2;
+constexpr int kMinUnitsF32 = 2048;
+static_assert(kChunks[kFirstChunkF32] <= kPartSlots, "no parts");
 constexpr int kPlanLds = 4096;    // trees up to this many nodes are walked from LDS
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -119,7 +127,8 @@ struct CreditArgs {
 // leaves' nodes of its depth.  The units are written by all threads, each
 // finding its unit's entry by a binary search.  SMALL / FEW are template
 // arguments, so that every access compiles to an LDS or a global instruction
-// rather than a flat one.
+// rather than a flat one; BF16, the pool's type, sets the rule of
+// the chunk size.
 // Bound by latency: 16 leaves of a 341-block tree take 8.2 us; with a
 // comparison against every leaf and each node's thread writing its units
 // 14.8, and 9.7 for the former plan, which scanned all V nodes.
@@ -138,7 +147,7 @@ struct Place {
   int rank, first, nl;
 };
 
-template <bool SMALL, bool FEW>
+template <bool SMALL, bool FEW, bool BF16>
 __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   constexpr bool MASKS = SMALL && FEW;
   constexpr int kEnt = FEW ? kPlanLeaves * MAXD : 1;
@@ -270,9 +279,10 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     s += dpp_move<dpp::kQuadXor2>(s);
     s += dpp_move<dpp::kRowHalfMirror>(s);
     s += dpp_move<dpp::kRowMirror>(s);
-    const uint64_t m = ballot(s >= kMinUnits);
+    const uint64_t m = ballot(s >= (BF16 ? kMinUnits : kMinUnitsF32));
 #pragma unroll
-    for (int k = kNChunks - 2; k >= 0; --k) C = (m >> (16 * k)) & 1 ? kChunks[k] : C;
+    for (int k = kNChunks - 2; k >= (BF16 ? 0 : kFirstChunkF32); --k)
+      C = (m >> (16 * k)) & 1 ? kChunks[k] : C;
   }
   const int lc = 31 - __builtin_clz(C);      // chunks of c slots: (c + C - 1) >> lc
   // units, partial rows, leaf-list places and logit slots of every node, in
@@ -429,6 +439,10 @@ __device__ __forceinline__ KVFrag<T, D, GSP> fetch_kv(const UnitAddr &ua, int pg
 #pragma unroll
     for (int ks = 0; ks < F::KS; ++ks)
       f.k[sp][ks] = Op<T>::load(reinterpret_cast<const T *>(kp + frag_col<T>(ks, 0) * (int)sizeof(T)));
+    // fp32 rows of 512 bytes: all loads of K go out before those of V, and none is
+    // held back to its use (the compiler otherwise waits for each 16 bytes of K
+    // in turn: 121 us for 16 layers of the 8B shape instead of 110)
+    if constexpr (sizeof(T) == 4 && D == 128) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const typename F::VT *vr = reinterpret_cast<const typename F::VT *>(vp + e * ua.row_bytes);
@@ -546,10 +560,11 @@ __device__ __forceinline__ void attend(KVFrag<T, D, GSP> &f,
 }
 
 // Sub-pages a wave loads at once: 16 KB of K and V in flight per wave, one
-// fragment at a time.  Measured on the llama8b and dpts trees: with a single
-// buffer the waves fit three to a SIMD, whose loads overlap one another's
-// work; double-buffered fragments, or larger ones, leave one or two waves per
-// SIMD and stream HBM more slowly.
+// fragment at a time.  With a single buffer two waves fit a SIMD for bf16
+// pools of d = 128 (195 registers, scored 206) and three or four (plain fp32, d = 64)
+// otherwise, and their loads overlap one another's work.  Double-buffered
+// fragments, or larger ones, leave one wave per SIMD (two where there were
+// three) and stream HBM more slowly, measured on the llama8b and dpts trees.
 template <class T, int D>
 constexpr int sub_pages_per_fetch() {
   constexpr int per = 32 * D * (int)sizeof(T);   // K and V of one 16-slot sub-page
@@ -631,6 +646,7 @@ __device__ __forceinline__ void decode_unit(const DecArgs &a, const Meta &mt, co
   // 1,024 slots lost accuracy (fp32 outputs of the 70B shape, nodes of 512
   // slots: 4.4e-7 from 64 bits, in parts 3.6e-7).
   constexpr int kPart = kPartSlots / (16 * GSP);
+  constexpr bool PARTS = sizeof(T) == 2;
   float m_tot, l_tot;               // (set by the first part)
   f32x4 ot[NC];
   auto first_part = [&]() __attribute__((always_inline)) {
@@ -680,12 +696,12 @@ __device__ __forceinline__ void decode_unit(const DecArgs &a, const Meta &mt, co
       if (KZ && zrow) store_z(gi - 1);
     }
     attend<T, D, GSP>(cur, q, a.sl2, g4, m_run, l_run, o, KZ && zrow != nullptr, zs);
-    if (gi % kPart == kPart - 1 && gi + 1 < n_grp) {
+    if (PARTS && gi % kPart == kPart - 1 && gi + 1 < n_grp) {
       if (gi < kPart) first_part();
       else merge_part();
     }
   }
-  if (n_grp > kPart) {
+  if (PARTS && n_grp > kPart) {
     merge_part();
     m_run = m_tot;
     l_run = l_tot;
@@ -1193,7 +1209,8 @@ size_t decode_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   // partial rows over all planes: a chunk size below the largest is taken only
   // while the next larger one gives fewer than kMinUnits units (16 rows at
   // most each, and at most two chunks for one)
-  const size_t least = nl * (ctx / kMaxChunk + MAXD + 1) * G * planes;
+  const int longest = g->dtype == ARBOR_BF16 ? kMaxChunk : kChunks[kFirstChunkF32];
+  const size_t least = nl * (ctx / longest + MAXD + 1) * G * planes;
   const size_t most = std::min(rows * planes, (size_t)kMinUnits * 32);
   b += std::max(least, most) * (g->head_dim + 2) * 4;
   // logits of the credited slice layers (scored decode)
@@ -1259,12 +1276,17 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   // small tree takes a smaller workgroup, whose barriers are cheaper
   const int64_t plan_need = std::max<int64_t>(small ? t.V : 0, (int64_t)n_leaves * 8);
   const int plan_threads = (int)std::min<int64_t>(1024, (plan_need + kWave - 1) / kWave * kWave);
-#define ARBOR_PLAN_LAUNCH(S, F) \
-  hipLaunchKernelGGL((decode_plan<S, F>), dim3(1), dim3(plan_threads), 0, stream, a, ent)
-  if (small && few) ARBOR_PLAN_LAUNCH(true, true);
-  else if (small) ARBOR_PLAN_LAUNCH(true, false);
-  else if (few) ARBOR_PLAN_LAUNCH(false, true);
-  else ARBOR_PLAN_LAUNCH(false, false);
+#define ARBOR_PLAN_LAUNCH(S, F, B) \
+  hipLaunchKernelGGL((decode_plan<S, F, B>), dim3(1), dim3(plan_threads), 0, stream, a, ent)
+  auto plan = [&](auto b) {
+    constexpr bool B = decltype(b)::value;
+    if (small && few) ARBOR_PLAN_LAUNCH(true, true, B);
+    else if (small) ARBOR_PLAN_LAUNCH(true, false, B);
+    else if (few) ARBOR_PLAN_LAUNCH(false, true, B);
+    else ARBOR_PLAN_LAUNCH(false, false, B);
+  };
+  if (geom->dtype == ARBOR_BF16) plan(std::true_type{});
+  else plan(std::false_type{});
 #undef ARBOR_PLAN_LAUNCH
   const CreditArgs *crp = credit ? &cr : nullptr;
   if (geom->dtype == ARBOR_BF16) {

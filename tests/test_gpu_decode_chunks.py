@@ -27,7 +27,7 @@ def _tree(root, nodes):
 CASES = [(1, 1, [4], 4, "bf16"), (1, 63, [4, 9], 8, "bf16"), (1, 1100, [4, 5, 6, 9], 4, "bf16"),
          (1, 64, [1, 4, 8], 1, "f32"), (8, 1025, [4, 5, 6, 7, 8, 9] * 3, 8, "bf16"),
          (8, 700, [4], 1, "f32"), (64, 2049, [4, 5, 6, 9, 9], 8, "bf16"),
-         (64, 1024, [7], 4, "bf16"), (2, 300, [4, 5, 6, 7, 8, 9, 1, 0] * 9, 2, "bf16")]
+         (64, 1024, [7], 4, "bf16"), (64, 2049, [4, 5, 9], 4, "f32"), (24, 1025, [4, 6], 8, "f32"), (2, 300, [4, 5, 6, 7, 8, 9, 1, 0] * 9, 2, "bf16")]
 
 
 @pytest.mark.parametrize("layers,root,leaves,G,dtype", CASES)
