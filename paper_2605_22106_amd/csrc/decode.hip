@@ -64,14 +64,16 @@ struct __attribute__((aligned(16))) Unit {
   int32_t first;     // unit of the chunk's row block 0
   int32_t zbase;     // its kept logits, [R][slots rounded up to 64]: first block of 64
   int32_t node;
-  int32_t pad[3];
+  int32_t piece0;    // credit calls with a list of pieces: the chunk's first one
+  int32_t pad[2];
 };
 static_assert(sizeof(Unit) == 48, "three 16-byte loads");
 
 struct Meta {
   int32_t n_units, rows, chunk, z_total;
-  int32_t max_np, pad;
+  int32_t max_np, n_pieces;
   int64_t parts;     // float offsets from `rest`: leaf_part entries, max_np per leaf,
+  int64_t pieces;    //   the unit of each listed 64-slot piece (credit calls),
   int64_t ml;        //   (max, sum) of the partial rows,
   int64_t part;      //   their unnormalised outputs,
   int64_t z;         //   kept logits
@@ -91,6 +93,7 @@ struct DecArgs {
   int32_t *lanc;        // [n_leaves][MAXD] chain of each leaf, root first
   int32_t *ldepth;
   int32_t *leaf_np;     // partials of each leaf's chain
+  int32_t *ent_p0;      // [n_leaves][MAXD]: first listed piece of an entry's node
   // units, leaf_part (first partial row of the leaf's heads, per partial), the
   // partials and the kept logits follow one another here
   float *rest;
@@ -133,6 +136,7 @@ struct CreditArgs {
 // comparison against every leaf and each node's thread writing its units
 // 14.8, and 9.7 for the former plan, which scanned all V nodes.
 constexpr int kPlanLeaves = 64;
+constexpr int kCreditGroups = 256;   // workgroups that credit
 
 // per-entry state, [n_leaves][MAXD] each (workspace for many leaves); entry
 // e = leaf * ds + depth for chains of at most ds blocks
@@ -151,7 +155,7 @@ template <bool SMALL, bool FEW, bool BF16>
 __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   constexpr bool MASKS = SMALL && FEW;
   constexpr int kEnt = FEW ? kPlanLeaves * MAXD : 1;
-  __shared__ int64_t sm[3 * 16];
+  __shared__ int64_t sm[4 * 16];
   __shared__ int s_cu[kNChunks * 16];
   __shared__ int s_err, s_maxd, s_maxnp;
   // the parent links are not needed once the chains are known: u0 takes their place
@@ -288,11 +292,14 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   // units, partial rows, leaf-list places and logit slots of every node, in
   // the order of its first leaf's chain; v[0] carries units (high half) and
   // leaf-list entries (low half)
-  int64_t run[3] = {0, 0, 0};
+  // (in a credit call whose chunks have several 64-slot pieces v[3] counts those,
+  // for the list from which the credit's workgroups take them)
+  const bool pieced = a.zS > 0 && C > kWave;
+  int64_t run[4] = {0, 0, 0, 0};
   for (int base = 0; base < n_e; base += nt) {
     const int e = base + tid;
     const int b = e / ds, d = e - b * ds;
-    int64_t v[3] = {0, 0, 0};
+    int64_t v[4] = {0, 0, 0, 0};
     if (e < n_e && d <= ldepp[b]) {
       const int c = en.kept[e];
       const int chunks = (c + C - 1) >> lc;
@@ -310,10 +317,24 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
         v[0] = ((int64_t)chunks * ((R + 15) / 16) << 32) | pc.nl;
         v[1] = (int64_t)chunks * R;
         v[2] = (int64_t)R * ((c + 63) / 64);
+        v[3] = (c + 63) / 64;
       }
     }
-    int64_t ex[3], tot[3];
-    block_exclusive_scan_n<3>(v, ex, tot, sm, n_e - base);
+    int64_t ex[4], tot[4];
+    if (pieced) {
+      block_exclusive_scan_n<4>(v, ex, tot, sm, n_e - base);
+      if (e < n_e) a.ent_p0[e] = (int)(run[3] + ex[3]);
+    } else {
+      const int64_t v3[3] = {v[0], v[1], v[2]};
+      int64_t ex3[3], tot3[3];
+      block_exclusive_scan_n<3>(v3, ex3, tot3, sm, n_e - base);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        ex[k] = ex3[k];
+        tot[k] = tot3[k];
+      }
+      tot[3] = 0;
+    }
     if (e < n_e) {
       en.u0[e] = (int)((run[0] + ex[0]) >> 32);
       en.loff[e] = (int)(uint32_t)(run[0] + ex[0]);
@@ -321,14 +342,19 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
       en.z0[e] = (int)(run[2] + ex[2]);
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) run[k] += tot[k];
+    for (int k = 0; k < 4; ++k) run[k] += tot[k];
   }
   __syncthreads();
   const int64_t n_units = run[0] >> 32;
   const int max_np = s_maxnp;
+  // no list where every place of every unit has a workgroup of its own anyway
+  // (building one took 0.9 us)
+  const bool listed = pieced && n_units * (C / kWave) > kCreditGroups;
+  if (!listed) run[3] = 0;
   const int64_t parts = n_units * (int64_t)(sizeof(Unit) / 4);
+  const int64_t pieces = parts + (int64_t)nb * max_np;
   if (tid == 0) {
-    // the units and the partial lists, the partials, then (credit calls) the
+    // the units, the partial and piece lists, the partials, then (credit calls) the
     // slice-layer logits of every node's rows and slots, in blocks
     // of 64 floats: [slice][kv head][z_total]
     Meta m;
@@ -338,9 +364,10 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     m.chunk = C;
     m.z_total = (int32_t)run[2];
     m.max_np = max_np;
-    m.pad = 0;
+    m.n_pieces = (int32_t)run[3];
     m.parts = parts;
-    m.ml = (parts + (int64_t)nb * max_np + 3) & ~(int64_t)3;
+    m.pieces = pieces;
+    m.ml = (pieces + run[3] + 3) & ~(int64_t)3;
     m.part = (m.ml + run[1] * planes * 2 + 3) & ~(int64_t)3;
     m.z = m.part + run[1] * planes * a.pl.D;
     const int64_t need = m.z + (int64_t)a.zS * a.pl.Hkv * run[2] * 64;
@@ -352,6 +379,8 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   }
   // the units
   Unit *units = reinterpret_cast<Unit *>(a.rest);
+  int32_t *piece_unit = reinterpret_cast<int32_t *>(a.rest) + pieces;
+  const int64_t piece_cap = a.rest_cap - pieces;
   const int64_t unit_cap = a.rest_cap / (int64_t)(sizeof(Unit) / 4);
   for (int64_t i = tid; i < n_units && i < unit_cap; i += nt) {
     int lo = 0, hi = n_e - 1;                 // the last entry with u0 <= i
@@ -363,6 +392,7 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     const int b = lo / ds, d = lo - b * ds;
     const int x = en.up[b * MAXD + ldepp[b] - d];
     const int po = (int)t.page_off[x];
+    const int p0 = listed ? a.ent_p0[lo] : 0;
     const int c = en.kept[lo];
     const int R = place(lo, b, x).nl * G;
     const int nbr = (R + 15) / 16;
@@ -377,8 +407,12 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     u.first = en.u0[lo] + q * nbr;
     u.zbase = en.z0[lo] + R * (q << (lc - 6));
     u.node = x;
-    u.pad[0] = u.pad[1] = u.pad[2] = 0;
+    u.piece0 = p0 + (q << (lc - 6));
+    u.pad[0] = u.pad[1] = 0;
     units[i] = u;
+    if (listed && u.first == (int)i)
+      for (int j = 0; j * kWave < u.n_slots; ++j)
+        if (u.piece0 + j < piece_cap) piece_unit[u.piece0 + j] = (int32_t)i;
   }
   // the leaves below each node, and each leaf's partials, root first (so the
   // merge needs no chain walk)
@@ -998,7 +1032,12 @@ __device__ __forceinline__ float2 chain_ml(const DecArgs &a, const Meta &mt, int
   return r;
 }
 
-// the credit of the 64-slot pieces blk, blk + nblk, ... of the plan's chunks
+// The credit of the 64-slot pieces blk, blk + nblk, ... of the plan's chunks.
+// They are numbered as units and places in them, or taken from the plan's list of
+// the live ones where there are more such places than workgroups: without it the
+// live pieces fell on few of them (blocks of 128 slots in chunks of 1,024 have two
+// of sixteen: the launch of 16 leaves and 32 layers took 43.8 us, now 24.2, and
+// that of 64 leaves of the 70B shape and 8 layers 673, now 168).
 __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
                                               const CreditArgs &cr, int blk, int nblk) {
   __shared__ float s_oth[kCreditWaves][kWave], s_own[kCreditWaves][kWave];
@@ -1027,12 +1066,15 @@ __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
   // (in a vector register: the fused step below reads one scalar register, M)
   float c2 = a.sl2;
   asm volatile("" : "+v"(c2));
-  const int pieces = mt.chunk / kWave;
+  const bool listed = mt.n_pieces > 0;
+  const int32_t *piece_unit = reinterpret_cast<const int32_t *>(a.rest) + mt.pieces;
+  const int per_unit = mt.chunk / kWave;
+  const int64_t n_w = listed ? mt.n_pieces : (int64_t)mt.n_units * per_unit;
   constexpr int kLast = kCreditWaves - 1;
-  for (int64_t w = blk; w < (int64_t)mt.n_units * pieces; w += nblk) {
-    const int u = (int)(w / pieces);
+  for (int64_t w = blk; w < n_w; w += nblk) {
+    const int u = listed ? piece_unit[w] : (int)(w / per_unit);
     const Unit un = units_of(a)[u];
-    const int piece = (int)(w - (int64_t)u * pieces) * kWave;
+    const int piece = (int)(w - (listed ? (int64_t)un.piece0 : (int64_t)u * per_unit)) * kWave;
     // (uniform over the workgroup) a chunk is credited once, by its first unit
     if (un.first != u || piece >= un.n_slots) continue;
     const int node = un.node;
@@ -1184,7 +1226,7 @@ void launch_decode_kernels(const arbor_geom_t *geom, const DecArgs &a, void *out
   // credit workgroups stride over the 64-slot pieces of the plan's chunks (at
   // most half the chip's wave slots, so that the merge workgroups start beside
   // them); merge workgroups hold kCreditWaves rows each
-  const int cgrid = 256;
+  const int cgrid = kCreditGroups;
   const int64_t mb = (mw + kCreditWaves - 1) / kCreditWaves;
   const int mgrid = (int)(mb < 2048 ? mb : 2048);
   timing_begin(geom, ARBOR_KERNEL_DECODE_CREDIT, stream);
@@ -1204,8 +1246,8 @@ size_t decode_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   const size_t per_leaf = ctx / kMinChunk + MAXD + 1;
   const size_t rows = nl * per_leaf * G;
   size_t b = 16 * 256;
-  b += nl * (MAXD * (4 * (2 + kPlanEnts) + 8) + 12);
-  b += (nl * per_leaf + rows / 16 + nl) * sizeof(Unit) + nl * per_leaf * 4;
+  b += nl * (MAXD * (4 * (3 + kPlanEnts) + 8) + 12);
+  b += (nl * per_leaf + rows / 16 + nl) * sizeof(Unit) + 2 * nl * per_leaf * 4;
   // partial rows over all planes: a chunk size below the largest is taken only
   // while the next larger one gives fewer than kMinUnits units (16 rows at
   // most each, and at most two chunks for one)
@@ -1247,6 +1289,7 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   a.lanc = cv.take<int32_t>(ne);
   a.ldepth = cv.take<int32_t>(n_leaves);
   a.leaf_np = cv.take<int32_t>(n_leaves);
+  a.ent_p0 = cv.take<int32_t>(ne);
   PlanEnt ent{};
   if (!few) {
     int32_t **f[kPlanEnts] = {&ent.up, &ent.kept, &ent.rbase, &ent.loff, &ent.np, &ent.u0, &ent.z0};

@@ -117,3 +117,34 @@ def test_decode_long_chunks_are_as_accurate_as_short_ones(node, d, step):
                 num[x] += float((t[b, l].double() - o).square().sum())
     err = (num / den).sqrt().tolist()
     assert err[0] <= 1.02 * err[1], err
+
+
+def test_decode_credit_of_many_leaves_in_long_chunks():
+    """Row blocks and chunks beyond the credit's workgroups (the plan's list of live 64-slot
+    pieces): 40 leaves, blocks of 40 to 300 slots, 64 layers, two slices of which one listed
+    twice, against the oracle; and an eighth of the layers, whose chunks are shorter."""
+    parent = [-1] + [0] * 5 + [1 + i // 8 for i in range(40)]
+    n_full = [1500] + [128, 300, 40, 65, 260] + [40 + 7 * i for i in range(40)]
+    leaves, G, d = list(range(6, 46)), 4, 64
+    for layers in (64, 8):
+        st = synth.build_state(parent, n_full, layers=layers, kv_heads=8, q_per_kv=G, head_dim=d,
+                               dtype="bf16", seed=layers, shuffle_pages=True, heavy_frac=0.05,
+                               active=leaves, host_store=False)
+        kv = to_gpu(st)
+        q = st["q_dec"].cuda().contiguous()
+        lt = torch.tensor(leaves, dtype=torch.int32, device="cuda")
+        ws = workspace(kv, max_leaves=len(leaves), max_layers=layers, n_slice=3)
+        out = torch.empty((len(leaves), layers, 8 * G, d), device="cuda")
+        A = torch.zeros(kv.num_tokens, device="cuda")
+        rows, stt = torch.zeros(kv.num_nodes, dtype=torch.int64, device="cuda"), status()
+        check_rc(L.arbor_tree_decode_attn_scored(kv, lt, 0, layers, q, out, None, 0.0,
+                                                 [1, layers - 1, 1], 0, A, rows, stt, ws))
+        torch.cuda.synchronize()
+        assert int(stt) == L.OK
+        pick = [1, layers - 1]
+        two = oracle_state(dict(st, k=st["k"][pick], v=st["v"][pick]))
+        Ao, ro = O.decode_credit(two, leaves, 0, q[:, pick].float().cpu().numpy(), G, [0, 1, 0],
+                                 np.zeros(kv.num_tokens, np.float32),
+                                 np.zeros(kv.num_nodes, np.int64), self_window=0)
+        assert np.allclose(A.cpu().numpy(), Ao, rtol=1e-4, atol=1e-30)
+        assert np.array_equal(rows.cpu().numpy(), ro)
