@@ -26,27 +26,29 @@ namespace {
 
 constexpr int MAXD = ARBOR_MAX_DEPTH + 1;
 static_assert(MAXD == kWave, "one wave covers a chain");
-// Slots of a chain node that one work unit takes: the plan picks the largest
-// of kChunks that still gives kMinUnits units (fp32 pools: below), so that a call over few keys
-// (one layer of a model's own loop) is cut finely enough to fill the chip and
-// one over many keys writes and merges few partials.  Measured: one layer of a
-// 341-block tree under 16 leaves takes 35 us at 64 slots, 91 at the former 256
-// (with one launch per class of 16, 32 or 64 rows); 20 layers of the 70B shape
-// 355 us at up to 1,024, 373 at 512, 402 at 256; 32 layers of the 8B shape 122
-// us with at least 4,096 units (two for every wave the chip holds), 131 with
-// 2,048 and 135 with 8,192.
+// Slots of a chain node that one work unit takes: the plan picks the largest of
+// kChunks that is no longer than a wave's even share of the call, 1 / kWaves of the
+// (slot, 16-row block, layer, kv head)s, so that no unit outlasts the others and
+// few partials are written and merged; of four fifths of it where a node is
+// shorter than the chunk, as uneven units fill the waves less well.  Times at
+// this size / at half of it / at twice of it, us: the 8B shape under 4 leaves, 32
+// layers 117 / - / 122, 16 layers 57.4 / 60.4 / -, 8 layers 37.0 / 41.2 / 37.6;
+// the 70B shape under one leaf, 20 layers 117 / 129 / -, under 8 leaves 349 at
+// 1,024, 373 at 512, 402 at 256, and for 4 layers 82 / 96 / -; 16 leaves of a
+// 341-block tree, 8 layers 66.4 / 68.2 / 79.2, one layer 35 at 64, 91 at 256.
+// Taking the largest size that gives 4,096 units instead cut the calls of few
+// rows too finely (the second figures).
 constexpr int kChunks[] = {1024, 512, 256, 128, 64};
 constexpr int kNChunks = 5;
 constexpr int kMinChunk = 64, kMaxChunk = 1024;
-constexpr int kMinUnits = 4096;
+constexpr int kWaves = 2048;      // two for every SIMD, as the registers of d = 128 allow
+constexpr int kWaves64 = 3072;    // bf16 pools of d = 64: three
 constexpr int kPartSlots = 256;   // slots of a unit that share a reference max
-// fp32 pools, whose slots are twice the bytes: units of at most 256 slots (so
+// fp32 pools, whose slots are twice the bytes: units of at most 256 slots, so that
 // none is summed in parts, whose second accumulator would leave two waves per
-// SIMD instead of three), and half as many of them are enough.  16 layers of the
-// 8B shape take 109.7 us with at least 2,048 units of 256 slots, 119 with
-// 4,096 of 128; 8 layers of the 70B shape 306 us, with units of 512 slots in parts 390.
+// SIMD instead of three (8 layers of the 70B shape: 306 us, in parts of longer
+// units 390)
 constexpr int kFirstChunkF32 = 2;
-constexpr int kMinUnitsF32 = 2048;
 static_assert(kChunks[kFirstChunkF32] <= kPartSlots, "no parts");
 constexpr int kPlanLds = 4096;    // trees up to this many nodes are walked from LDS
 constexpr float kLog2e = 1.4426950408889634f;
@@ -130,8 +132,8 @@ struct CreditArgs {
 // leaves' nodes of its depth.  The units are written by all threads, each
 // finding its unit's entry by a binary search.  SMALL / FEW are template
 // arguments, so that every access compiles to an LDS or a global instruction
-// rather than a flat one; BF16, the pool's type, sets the rule of
-// the chunk size.
+// rather than a flat one; WAVES and FIRST are the pool's rule of the
+// chunk size.
 // Bound by latency: 16 leaves of a 341-block tree take 8.2 us; with a
 // comparison against every leaf and each node's thread writing its units
 // 14.8, and 9.7 for the former plan, which scanned all V nodes.
@@ -151,12 +153,13 @@ struct Place {
   int rank, first, nl;
 };
 
-template <bool SMALL, bool FEW, bool BF16>
+template <bool SMALL, bool FEW, int WAVES, int FIRST>
 __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   constexpr bool MASKS = SMALL && FEW;
   constexpr int kEnt = FEW ? kPlanLeaves * MAXD : 1;
   __shared__ int64_t sm[4 * 16];
-  __shared__ int s_cu[kNChunks * 16];
+  __shared__ unsigned s_work;
+  __shared__ int s_least;
   __shared__ int s_err, s_maxd, s_maxnp;
   // the parent links are not needed once the chains are known: u0 takes their place
   static_assert(kPlanLds >= kPlanLeaves * MAXD, "u0 fits");
@@ -166,6 +169,9 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   __shared__ int32_t s_ldep[FEW ? kPlanLeaves : 1];
   const Tree &t = a.t;
   const int V = t.V, G = a.pl.G, nb = a.n_leaves;
+  // (loaded here, not where they are used)
+  const int zS = a.zS, planes = a.Lr * a.pl.Hkv;
+  asm volatile("" : : "s"(zS), "s"(planes));
   const int nt = blockDim.x, tid = threadIdx.x;
   // each thread's first node and leaf are loaded together with the status word
   const int par0 = SMALL && tid < V ? t.parent[tid] : 0;
@@ -180,7 +186,11 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   else
     en = gent;
   int32_t *ldepp = FEW ? s_ldep : a.ldepth;
-  if (tid == 0) s_err = s_maxd = s_maxnp = 0;
+  if (tid == 0) {
+    s_err = s_maxd = s_maxnp = 0;
+    s_work = 0;
+    s_least = INT32_MAX;
+  }
   if constexpr (SMALL)
     for (int i = tid; i < V; i += nt) {
       s_par[i] = i == tid ? par0 : t.parent[i];
@@ -227,9 +237,8 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     constexpr uint64_t k = (1ull << 21) - 1;
     return Place{(int)(m & k), (int)((m >> 21) & k), (int)(m >> 42)};
   };
-  int64_t cu[kNChunks];
-#pragma unroll
-  for (int k = 0; k < kNChunks; ++k) cu[k] = 0;
+  int64_t work = 0;          // slots times row blocks
+  int least = INT32_MAX;     // the shortest node's slots
   for (int e = tid; e < n_e; e += nt) {
     const int b = e / ds, d = e - b * ds;
     const int dl = ldepp[b];
@@ -252,41 +261,33 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     a.lanc[b * MAXD + d] = x;
     en.kept[e] = c;
     if (pc.rank == 0) {
-      const int nbr = (pc.nl * G + 15) / 16;
-#pragma unroll
-      for (int k = 0; k < kNChunks; ++k)
-        cu[k] += (int64_t)((c + kChunks[k] - 1) / kChunks[k]) * nbr;
+      work += (int64_t)c * ((pc.nl * G + 15) / 16);
+      if (c > 0) least = min(least, c);
     }
   }
-  // the chunk size (counts of units, saturated: only their order against
-  // kMinUnits matters)
+  // the chunk size (a thread's work counts up to the largest one's need: the sum
+  // of 1,024 threads fits 32 bits)
   int C = kMinChunk;
   {
-    const int planes = a.Lr * a.pl.Hkv;
-    const int nw = nt >> 6;
+    constexpr int64_t kMost = (int64_t)kMaxChunk * WAVES * 5 / 4;
+    static_assert(kMost <= 1 << 22, "1,024 of them fit");
+    const int64_t all = work * planes;
     if ((tid & ~(kWave - 1)) < n_e) {
-      int v[kNChunks];
-#pragma unroll
-      for (int k = 0; k < kNChunks - 1; ++k)
-        v[k] = wave_sum((int)(cu[k] * planes < kMinUnits ? cu[k] * planes : kMinUnits));
-      if (lane_id() == 0)
-#pragma unroll
-        for (int k = 0; k < kNChunks - 1; ++k) s_cu[k * 16 + (tid >> 6)] = v[k];
-    } else if (lane_id() < kNChunks - 1) {
-      s_cu[lane_id() * 16 + (tid >> 6)] = 0;
+      const unsigned v = wave_sum((unsigned)(all < kMost ? all : kMost));
+      const int lo = wave_allreduce(least, [](int x, int y) { return min(x, y); });
+      if (lane_id() == 0) {
+        atomicAdd(&s_work, v);
+        atomicMin(&s_least, lo);
+      }
     }
     __syncthreads();
-    // lane (k, w) holds wave w's count for size k
-    static_assert((kNChunks - 1) * 16 == kWave, "one row of 16 lanes per chunk size");
-    int s = (lane_id() & 15) < nw ? s_cu[lane_id()] : 0;
-    s += dpp_move<dpp::kQuadXor1>(s);
-    s += dpp_move<dpp::kQuadXor2>(s);
-    s += dpp_move<dpp::kRowHalfMirror>(s);
-    s += dpp_move<dpp::kRowMirror>(s);
-    const uint64_t m = ballot(s >= (BF16 ? kMinUnits : kMinUnitsF32));
+    const unsigned s = (unsigned)__builtin_amdgcn_readfirstlane((int)s_work);
+    const int lo = __builtin_amdgcn_readfirstlane(s_least);
 #pragma unroll
-    for (int k = kNChunks - 2; k >= (BF16 ? 0 : kFirstChunkF32); --k)
-      C = (m >> (16 * k)) & 1 ? kChunks[k] : C;
+    for (int k = kNChunks - 2; k >= FIRST; --k) {
+      const unsigned need = (unsigned)(kChunks[k] * WAVES);
+      C = s >= (lo < kChunks[k] ? need / 4 * 5 : need) ? kChunks[k] : C;
+    }
   }
   const int lc = 31 - __builtin_clz(C);      // chunks of c slots: (c + C - 1) >> lc
   // units, partial rows, leaf-list places and logit slots of every node, in
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
   // leaf-list entries (low half)
   // (in a credit call whose chunks have several 64-slot pieces v[3] counts those,
   // for the list from which the credit's workgroups take them)
-  const bool pieced = a.zS > 0 && C > kWave;
+  const bool pieced = zS > 0 && C > kWave;
   int64_t run[4] = {0, 0, 0, 0};
   for (int base = 0; base < n_e; base += nt) {
     const int e = base + tid;
@@ -358,7 +359,6 @@ __global__ __launch_bounds__(1024) void decode_plan(DecArgs a, PlanEnt gent) {
     // slice-layer logits of every node's rows and slots, in blocks
     // of 64 floats: [slice][kv head][z_total]
     Meta m;
-    const int64_t planes = (int64_t)a.Lr * a.pl.Hkv;
     m.n_units = (int32_t)n_units;
     m.rows = (int32_t)run[1];
     m.chunk = C;
@@ -1072,7 +1072,7 @@ __device__ __forceinline__ void credit_pieces(const DecArgs &a, const Meta &mt,
   const int64_t n_w = listed ? mt.n_pieces : (int64_t)mt.n_units * per_unit;
   constexpr int kLast = kCreditWaves - 1;
   for (int64_t w = blk; w < n_w; w += nblk) {
-    const int u = listed ? piece_unit[w] : (int)(w / per_unit);
+    const int u = listed ? piece_unit[w] : (int)((unsigned)w / (unsigned)per_unit);
     const Unit un = units_of(a)[u];
     const int piece = (int)(w - (listed ? (int64_t)un.piece0 : (int64_t)u * per_unit)) * kWave;
     // (uniform over the workgroup) a chunk is credited once, by its first unit
@@ -1248,12 +1248,14 @@ size_t decode_workspace(const arbor_geom_t *g, const arbor_sizes_t *sz) {
   size_t b = 16 * 256;
   b += nl * (MAXD * (4 * (3 + kPlanEnts) + 8) + 12);
   b += (nl * per_leaf + rows / 16 + nl) * sizeof(Unit) + 2 * nl * per_leaf * 4;
-  // partial rows over all planes: a chunk size below the largest is taken only
-  // while the next larger one gives fewer than kMinUnits units (16 rows at
-  // most each, and at most two chunks for one)
+  // partial rows over all planes.  A chunk size C below the longest is taken while
+  // 2 C is more than an even share, or than four fifths of it, so the whole
+  // chunks hold at most 5/2 kWaves64 units of 16 rows, beside one ragged chunk for
+  // each row of each chain node.
   const int longest = g->dtype == ARBOR_BF16 ? kMaxChunk : kChunks[kFirstChunkF32];
   const size_t least = nl * (ctx / longest + MAXD + 1) * G * planes;
-  const size_t most = std::min(rows * planes, (size_t)kMinUnits * 32);
+  const size_t most =
+      std::min(rows * planes, (size_t)kWaves64 * 40 + nl * (MAXD + 1) * G * planes);
   b += std::max(least, most) * (g->head_dim + 2) * 4;
   // logits of the credited slice layers (scored decode)
   b += nl * G * (ctx + 64 * (MAXD + 1)) * (size_t)(sz->n_slice > 0 ? sz->n_slice : 0) *
@@ -1319,17 +1321,22 @@ int launch_decode(const arbor_geom_t *geom, const arbor_tree_t *tree, const arbo
   // small tree takes a smaller workgroup, whose barriers are cheaper
   const int64_t plan_need = std::max<int64_t>(small ? t.V : 0, (int64_t)n_leaves * 8);
   const int plan_threads = (int)std::min<int64_t>(1024, (plan_need + kWave - 1) / kWave * kWave);
-#define ARBOR_PLAN_LAUNCH(S, F, B) \
-  hipLaunchKernelGGL((decode_plan<S, F, B>), dim3(1), dim3(plan_threads), 0, stream, a, ent)
-  auto plan = [&](auto b) {
-    constexpr bool B = decltype(b)::value;
-    if (small && few) ARBOR_PLAN_LAUNCH(true, true, B);
-    else if (small) ARBOR_PLAN_LAUNCH(true, false, B);
-    else if (few) ARBOR_PLAN_LAUNCH(false, true, B);
-    else ARBOR_PLAN_LAUNCH(false, false, B);
+#define ARBOR_PLAN_LAUNCH(S, F)                                                              \
+  hipLaunchKernelGGL((decode_plan<S, F, decltype(waves)::value, decltype(first)::value>),    \
+                     dim3(1), dim3(plan_threads), 0, stream, a, ent)
+  auto plan = [&](auto waves, auto first) {
+    if (small && few) ARBOR_PLAN_LAUNCH(true, true);
+    else if (small) ARBOR_PLAN_LAUNCH(true, false);
+    else if (few) ARBOR_PLAN_LAUNCH(false, true);
+    else ARBOR_PLAN_LAUNCH(false, false);
   };
-  if (geom->dtype == ARBOR_BF16) plan(std::true_type{});
-  else plan(std::false_type{});
+  using std::integral_constant;
+  if (geom->dtype != ARBOR_BF16)
+    plan(integral_constant<int, kWaves>{}, integral_constant<int, kFirstChunkF32>{});
+  else if (geom->head_dim == 64)
+    plan(integral_constant<int, kWaves64>{}, integral_constant<int, 0>{});
+  else
+    plan(integral_constant<int, kWaves>{}, integral_constant<int, 0>{});
 #undef ARBOR_PLAN_LAUNCH
   const CreditArgs *crp = credit ? &cr : nullptr;
   if (geom->dtype == ARBOR_BF16) {
