@@ -1073,7 +1073,10 @@ __global__ __launch_bounds__(256) void score_tables(ScoreArgs a) {
 // chain or a workspace too small leaves o's table unwritten (the setup
 // reports the error, and no later kernel runs).
 constexpr int kPrepObs = 512;
-constexpr int kFewObs = 32;    // up to this many, four waves reduce a chunk
+// up to this many observers four waves reduce a chunk, beyond it 16 (341 blocks of
+// the dpts shape, whole calls: 8 observers 35.3 us with four waves, 35.9 with 16;
+// 16 35.4 and 35.2; 24 42.2 and 40.3; 32 44.3 and 41.3; 64 67.9 and 61.8)
+constexpr int kFewObs = 16;
 
 // The setup's check of nodes [base, base + blockDim.x).
 __device__ __forceinline__ void check_nodes(const ScoreArgs &a, int base) {
@@ -1197,7 +1200,9 @@ struct FinalArgs {
 // (With a launch of its own for the slab sums, 16 leaves over a 341-block tree
 // took 3.4 + 7.3 us, now 5.4; 85 observers of the 8B shape 4.8 + 6.1, now 8.1;
 // 341 of the 70B shape 23 + 21, now 45.)
-constexpr int kCutChunks = 32;   // a root of more chunks is not cut into parts (below)
+// a root of more chunks is not cut into parts (below): 340 observers, whole calls cut
+// / uncut, 16 chunks 178.7 / 185.2 us, 32 277.1 / 279.8, 48 372.6 / 370.1, 64 482 / 472
+constexpr int kCutChunks = 32;
 template <int W>
 __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2 *__restrict__ cred,
                                                          float *__restrict__ A,

@@ -71,9 +71,10 @@ def test_score_one_observer_of_a_large_tree(sw):
 
 
 @pytest.mark.parametrize("n_root,n_obs", [(1, 33), (15, 300), (16, 34), (17, 257), (64, 63),
-                                          (65, 300), (129, 40), (2048, 33), (2049, 33)])
+                                          (65, 300), (129, 40), (2048, 33), (2049, 33), (65, 16),
+                                          (65, 17), (2049, 17)])
 def test_score_root_parts_of_many_observers(n_root, n_obs):
-    """More than 32 observers: the root's chunks are reduced in parts of 16 slots and
+    """More than 16 observers: the root's chunks are reduced in parts of 16 slots and
     groups of four observers, 256 observers at a time; beyond 2,048 slots uncut."""
     parent, n_full = synth.random_tree(n_obs + 1, 20, n_obs)
     n_full[0] = n_root
