@@ -201,14 +201,12 @@ struct PlanEmit {
   }
 };
 
-// workgroup 0 scans with all kScanWaves waves, the others select and plan SW
-// nodes each, one per wave.  Up to kSpreadNodes nodes SW = 4
-// (a workgroup's other waves exit at once), so that the selections spread over
-// as many CUs as with small workgroups; more nodes fill the chip anyway, and
-// every wave selects: 9,841 nodes take 11.1 us instead of 12.8.
-constexpr int kSpreadNodes = 2048;
+// workgroup 0 scans with all kScanWaves waves, the others select and plan kSelWaves
+// nodes each, one per wave (their other waves exit at once, so that the selections
+// spread over as many CUs as with small workgroups; nodes in all 16 waves of them
+// made no difference: 1,023 nodes 3.2 us either way, 3,280 5.6, 9,841 10.8)
+constexpr int kSelWaves = 4;
 constexpr int kScanWaves = 16;
-template <int SW>
 __global__ __launch_bounds__(kScanWaves * kWave) void select_plan(Tree t, Pool pl, const float *__restrict__ A,
                                                    const int32_t *__restrict__ k, int l_tail,
                                                    int n_sinks, int mode,
@@ -219,13 +217,13 @@ __global__ __launch_bounds__(kScanWaves * kWave) void select_plan(Tree t, Pool p
                                                    int32_t *__restrict__ push_base,
                                                    int32_t *__restrict__ changed,
                                                    int32_t *__restrict__ meta, int32_t *status) {
-  __shared__ SelectLds<SW> lds;
+  __shared__ SelectLds<kSelWaves> lds;
   if (blockIdx.x == 0) {
     scan_nodes(t, pl, k, push_base, changed, meta, status);
     return;
   }
-  if ((int)(threadIdx.x >> 6) >= SW) return;
-  const int i = ((int)blockIdx.x - 1) * SW + (threadIdx.x >> 6);
+  if ((int)(threadIdx.x >> 6) >= kSelWaves) return;
+  const int i = ((int)blockIdx.x - 1) * kSelWaves + (threadIdx.x >> 6);
   if (i >= t.V) return;
   const int64_t tb = t.tok_off[i];
   int first = INT_MAX;
@@ -407,16 +405,11 @@ int launch_select_compact(const arbor_geom_t *geom, arbor_tree_t *tree, arbor_po
   int32_t *changed = cv.take<int32_t>(t.V);
   int32_t *meta = cv.take<int32_t>(4);
   if (!cv.ok) return ARBOR_EWORKSPACE;
-  const int sw = t.V <= kSpreadNodes ? 4 : kScanWaves;
-  const int node_blocks = (t.V + sw - 1) / sw;
+  const int node_blocks = (t.V + kSelWaves - 1) / kSelWaves;
   timing_begin(geom, ARBOR_KERNEL_SELECT, stream);
-#define ARBOR_SELECT_LAUNCH(SW)                                                                 \
-  hipLaunchKernelGGL(select_plan<SW>, dim3(node_blocks + 1), dim3(kScanWaves * kWave), 0, stream, \
-                     t, pl, A, k, params->l_tail, params->n_sinks, params->select_mode, sel_pos,  \
-                     mv_src, mv_dst, first_moved, push_base, changed, meta, status)
-  if (sw == 4) ARBOR_SELECT_LAUNCH(4);
-  else ARBOR_SELECT_LAUNCH(kScanWaves);
-#undef ARBOR_SELECT_LAUNCH
+  hipLaunchKernelGGL(select_plan, dim3(node_blocks + 1), dim3(kScanWaves * kWave), 0, stream, t,
+                     pl, A, k, params->l_tail, params->n_sinks, params->select_mode, sel_pos,
+                     mv_src, mv_dst, first_moved, push_base, changed, meta, status);
   timing_end(geom, ARBOR_KERNEL_SELECT, stream);
   const int64_t planes = (int64_t)t.V * pl.L * pl.Hkv;
   const int move_blocks = (int)((planes + 3) / 4 < 8192 ? (planes + 3) / 4 : 8192);
