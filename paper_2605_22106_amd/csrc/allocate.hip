@@ -229,16 +229,15 @@ __device__ void block_min_sum3(int64_t (&v)[3], int64_t *sm) {
   __syncthreads();
 }
 
-// The rank-th smallest (0-based) of the keys src[0, n), 0 <= rank < n.  Keys
-// are taken relative to the smallest one, and each pass splits the remaining
+// The rank-th smallest (0-based) of the keys src[0, n), 0 <= rank < n, all of them
+// in [kmin, kmax].  Keys are taken relative to kmin, and each pass splits the remaining
 // range [lo, lo + span] into 256 equal power-of-two buckets: the listed prices
 // are spread fairly evenly over their small range, so one pass usually leaves
 // at most 64 candidates, which one wave then ranks directly.  src and dst
-// (room for n keys) may be LDS or global memory; both are overwritten.
+// (room for n keys) are both overwritten.
 // Called by the whole block; contains __syncthreads.
 __device__ uint64_t select_rank(uint64_t *src, uint64_t *dst, int64_t n, int64_t rank,
-                                int64_t *sm, bool known = false, uint64_t kmin = 0,
-                                uint64_t kmax = 0) {
+                                uint64_t kmin, uint64_t kmax) {
   __shared__ unsigned hist4[4 * 256];
   __shared__ int64_t s_wtot[4];
   __shared__ int s_chosen;
@@ -246,24 +245,9 @@ __device__ uint64_t select_rank(uint64_t *src, uint64_t *dst, int64_t n, int64_t
   __shared__ unsigned s_ncand;
   __shared__ uint64_t s_key;
   const int tid = threadIdx.x, lane = lane_id();
-  uint64_t cmin = kmin, cmax = kmax;
-  if (!known) {
-    cmin = ~0ull;
-    cmax = 0ull;
-    for (int64_t e = tid; e < n; e += blockDim.x) {
-      const uint64_t key = src[e];
-      cmin = key < cmin ? key : cmin;
-      cmax = key > cmax ? key : cmax;
-    }
-    // both extremes in one exchange (keys of finite positive doubles < 2^63)
-    int64_t v3[3] = {0, cmin == ~0ull ? INT64_MAX : (int64_t)cmin, INT64_MAX - (int64_t)cmax};
-    block_min_sum3(v3, sm);
-    cmin = (uint64_t)v3[1];
-    cmax = (uint64_t)(INT64_MAX - v3[2]);
-  }
-  if (cmin == cmax) return cmin;
+  if (kmin == kmax) return kmin;
   int64_t ncand = n;
-  uint64_t lo = cmin, span = cmax - cmin;
+  uint64_t lo = kmin, span = kmax - kmin;
   while (ncand > kWave) {
     if (span == 0) return lo;   // every candidate left is lo
     // buckets of 2^shift keys: span >> shift < 256
@@ -861,8 +845,8 @@ __global__ __launch_bounds__(kCutThreads) void alloc_cut(Tree t, int64_t budget,
       });
     }
     __syncthreads();
-    answer = select_rank(s_cand, s_cand + kCandLds, tot[1], E - tot[0], sm, true,
-                         (uint64_t)(ka + 1), (uint64_t)kb);
+    answer = select_rank(s_cand, s_cand + kCandLds, tot[1], E - tot[0], (uint64_t)(ka + 1),
+                         (uint64_t)kb);
     break;
   }
   // the prices below the cut, all of them eligible ones (the cut is)
