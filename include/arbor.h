@@ -92,10 +92,11 @@ typedef enum {
 
 /* (host) A timing request that belongs to one call: when a call launches
  * `kernel`, it records `start` on the launch stream right before that launch
- * and `stop` right after it, so hipEventElapsedTime(start, stop) after the stream has synchronised is the
- * kernel's own duration.  The caller owns the events (created with timing on
- * the device of the call) and the struct; the library keeps no reference
- * after the call returns.  Calls that do not launch `kernel` record nothing. */
+ * and `stop` right after it, so hipEventElapsedTime(start, stop) after the
+ * stream has synchronised is the kernel's own duration.  The caller owns the
+ * events (created with timing on the device of the call) and the struct; the
+ * library keeps no reference after the call returns.  Calls that do not launch
+ * `kernel` record nothing. */
 typedef struct {
   int32_t kernel;           /* arbor_kernel_t                                     */
   hipEvent_t start;
@@ -391,11 +392,11 @@ typedef struct {
   int64_t *rows_seen;           /* device, int64 [V], in/out                         */
 } arbor_decode_credit_t;
 
-/* The attention units keep the logits of the distinct slice layers (fp32, a
- * multiple of 64 per unit row and kv head) in the workspace; the launch that
- * merges the partials also turns them into the credited weights, its credit
- * workgroups forming each row's log-sum-exp from the chain's partials
- * themselves.  The workspace must be sized with arbor_sizes_t.n_slice >=
+/* The attention units keep the products of query and key of the distinct slice
+ * layers (fp32, a multiple of 64 per unit row and kv head) in the workspace;
+ * the launch that merges the partials also turns them into the credited
+ * weights, its credit workgroups forming each row's max and sum from the
+ * chain's partials themselves.  The workspace must be sized with arbor_sizes_t.n_slice >=
  * n_slice.
  * Errors: those of arbor_tree_decode_attn; EINVAL for a slice layer outside
  * [layer_begin, layer_end), n_slice outside 1..8, self_window not 0 or 1, or A /

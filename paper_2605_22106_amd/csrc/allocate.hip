@@ -1157,7 +1157,8 @@ __global__ __launch_bounds__(AT) void allocate_kernel(Tree t, const int32_t *__r
     return;
   }
 
-  pressure_drain(p, V, nd.path, [&](int i) { return nd.F[i]; }, nd.w, nd.n_kept, sum_red, sum_F - b_off, k_out, status, sm);
+  pressure_drain(p, V, nd.path, [&](int i) { return nd.F[i]; }, nd.w, nd.n_kept, sum_red,
+                 sum_F - b_off, k_out, status, sm);
 }
 
 }  // namespace
@@ -1235,11 +1236,11 @@ int launch_allocate(const arbor_tree_t *tree, const int32_t *active, int32_t n_a
   }
 #undef ARBOR_NODES_ARGS
   if (t.V <= kCutThreads * kRegNodes)
-    hipLaunchKernelGGL(alloc_cut<true>, dim3(1), dim3(kCutThreads), 0, stream, t, (int64_t)budget_tokens, p,
-                       k_out, on_path_out, status, ws, n_wg);
+    hipLaunchKernelGGL(alloc_cut<true>, dim3(1), dim3(kCutThreads), 0, stream, t,
+                       (int64_t)budget_tokens, p, k_out, on_path_out, status, ws, n_wg);
   else
-    hipLaunchKernelGGL(alloc_cut<false>, dim3(1), dim3(kCutThreads), 0, stream, t, (int64_t)budget_tokens,
-                       p, k_out, on_path_out, status, ws, n_wg);
+    hipLaunchKernelGGL(alloc_cut<false>, dim3(1), dim3(kCutThreads), 0, stream, t,
+                       (int64_t)budget_tokens, p, k_out, on_path_out, status, ws, n_wg);
   return hip_ok(hipGetLastError());
 }
 

@@ -1068,10 +1068,11 @@ __global__ __launch_bounds__(256) void score_tables(ScoreArgs a) {
 // Setup and tables in one launch (up to kPrepObs observers): workgroup 0 runs
 // the setup; workgroup 1 + o builds observer o's table without waiting for
 // it.  It walks every observer's chain itself (one thread per observer, the
-// setup's checks) for the sums that place the tables after the partials, and the prefix of the sub-page counts that places o's table:
-// the same integers the setup computes, so the offsets agree.  A malformed
-// chain or a workspace too small leaves o's table unwritten (the setup
-// reports the error, and no later kernel runs).
+// setup's checks) for the sums that place the tables after the partials, and
+// the prefix of the sub-page counts that places o's table: the same integers
+// the setup computes, so the offsets agree.  A malformed chain or a workspace
+// too small leaves o's table unwritten (the setup or, for one observer over a
+// large tree, the reduction reports the error).
 constexpr int kPrepObs = 512;
 // up to this many observers four waves reduce a chunk, beyond it 16 (341 blocks of
 // the dpts shape, whole calls: 8 observers 35.3 us with four waves, 35.9 with 16;
@@ -1294,7 +1295,8 @@ __global__ __launch_bounds__(W *kWave) void score_reduce(ScoreArgs a, const int2
         const int at = before + rank_below(bm, lane);
         hbase[at] = (ob == 0 ? pb0 : a.pbase[o]) + ctxoff;
         hlen[at] = ob == 0 ? len0 : a.ctxlen[o];
-        if (chk == 0 && part == 0) rows_add += (int64_t)a.S * pl.Hkv * pl.G * min(a.W, t.n_full[jo]);
+        if (chk == 0 && part == 0)
+          rows_add += (int64_t)a.S * pl.Hkv * pl.G * min(a.W, t.n_full[jo]);
       }
       __syncthreads();
       if (live) {

@@ -711,61 +711,61 @@ __global__ __launch_bounds__(PT) void uncert_topk_merge(const float4 *__restrict
     __syncthreads();
     if (tid < top_k) add(key_float(s_key[tid]));
   } else {
-  __syncthreads();
-  static_assert(KMAX == PT, "one candidate slot per thread");
-  // thread t looks at candidate t of every chunk (loads of eight chunks in
-  // flight; unconditional, since slot t always lies in the buffer)
-  auto each_cand = [&](auto &&f) __attribute__((always_inline)) {
-    for (int c0 = 0; c0 < n_chunk; c0 += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = cr[(int64_t)min(c0 + u, n_chunk - 1) * KMAX + tid];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t key = ordered_key(v[u]);
-        if (c0 + u < n_chunk && tid < s_cn[c0 + u] && key >= lb) f(key);
-      }
-    }
-  };
-  int n_f = 0;
-  if (n_chunk <= PT) {
-    int mine = 0;
-    each_cand([&](uint32_t) __attribute__((always_inline)) { ++mine; });
-    int64_t t;
-    int o = (int)block_exclusive_scan<int64_t>(mine, s_scan, &t);
-    n_f = (int)t;
-    if (n_f <= MMAX) {
-      each_cand([&](uint32_t key) __attribute__((always_inline)) { s_key[o++] = key; });
-      __syncthreads();
-    }
-  }
-  if (n_chunk <= PT && n_f <= MMAX) {
-    // the top K of the row among the candidates at or above lb: the K-th
-    // largest, the values above it, and `need` copies of it
-    auto visit_lds = [&](auto &&f) __attribute__((always_inline)) {
-      for (int i = tid; i < n_f; i += PT) f(s_key[i]);
-    };
-    need = top_k;
-    tau = block_select(visit_lds, need, hist, s_pick, s_scan);
-    visit_lds([&](uint32_t key) __attribute__((always_inline)) {
-      if (key > tau) add(key_float(key));
-    });
-  } else {
-    auto visit_v = [&](auto &&f) __attribute__((always_inline)) {
-      for (int q = tid; q < n_chunk * KMAX; q += PT) {
-        const int c = q / KMAX, j = q % KMAX;
-        if (j < (cn[c] & (kSorted - 1))) f(cr[q]);
+    __syncthreads();
+    static_assert(KMAX == PT, "one candidate slot per thread");
+    // thread t looks at candidate t of every chunk (loads of eight chunks in
+    // flight; unconditional, since slot t always lies in the buffer)
+    auto each_cand = [&](auto &&f) __attribute__((always_inline)) {
+      for (int c0 = 0; c0 < n_chunk; c0 += 8) {
+        float v[8];
+  #pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = cr[(int64_t)min(c0 + u, n_chunk - 1) * KMAX + tid];
+  #pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t key = ordered_key(v[u]);
+          if (c0 + u < n_chunk && tid < s_cn[c0 + u] && key >= lb) f(key);
+        }
       }
     };
-    auto visit = [&](auto &&f) __attribute__((always_inline)) {
-      visit_v([&](float x) __attribute__((always_inline)) { f(ordered_key(x)); });
-    };
-    need = top_k;
-    tau = block_select(visit, need, hist, s_pick, s_scan);
-    visit_v([&](float x) __attribute__((always_inline)) {
-      if (ordered_key(x) > tau) add(x);
-    });
-  }
+    int n_f = 0;
+    if (n_chunk <= PT) {
+      int mine = 0;
+      each_cand([&](uint32_t) __attribute__((always_inline)) { ++mine; });
+      int64_t t;
+      int o = (int)block_exclusive_scan<int64_t>(mine, s_scan, &t);
+      n_f = (int)t;
+      if (n_f <= MMAX) {
+        each_cand([&](uint32_t key) __attribute__((always_inline)) { s_key[o++] = key; });
+        __syncthreads();
+      }
+    }
+    if (n_chunk <= PT && n_f <= MMAX) {
+      // the top K of the row among the candidates at or above lb: the K-th
+      // largest, the values above it, and `need` copies of it
+      auto visit_lds = [&](auto &&f) __attribute__((always_inline)) {
+        for (int i = tid; i < n_f; i += PT) f(s_key[i]);
+      };
+      need = top_k;
+      tau = block_select(visit_lds, need, hist, s_pick, s_scan);
+      visit_lds([&](uint32_t key) __attribute__((always_inline)) {
+        if (key > tau) add(key_float(key));
+      });
+    } else {
+      auto visit_v = [&](auto &&f) __attribute__((always_inline)) {
+        for (int q = tid; q < n_chunk * KMAX; q += PT) {
+          const int c = q / KMAX, j = q % KMAX;
+          if (j < (cn[c] & (kSorted - 1))) f(cr[q]);
+        }
+      };
+      auto visit = [&](auto &&f) __attribute__((always_inline)) {
+        visit_v([&](float x) __attribute__((always_inline)) { f(ordered_key(x)); });
+      };
+      need = top_k;
+      tau = block_select(visit, need, hist, s_pick, s_scan);
+      visit_v([&](float x) __attribute__((always_inline)) {
+        if (ordered_key(x) > tau) add(x);
+      });
+    }
   }
   st = block_sum_f(st, s_f);
   tt = block_sum_f(tt, s_f);
