@@ -430,7 +430,7 @@ constexpr int MMAX = 1024;  // candidates selected in LDS by the merge workgroup
 // RES: the chunk has at most PVEC vectors per thread, which stay in registers
 // for every pass over them.
 constexpr int PVEC = 8;
-template <class T, bool RES>
+template <bool RES, class T>
 __global__ __launch_bounds__(PT) void uncert_topk_part(const T *__restrict__ logits, int64_t vocab,
                                                        int n_chunk, int top_k,
                                                        float4 *__restrict__ part,
@@ -829,7 +829,7 @@ int launch_uncertainty(const void *logits, int32_t dtype, int32_t n_rows, int64_
     const int64_t nvec = vocab / (bf ? 8 : 4);
     const bool res = (nvec + ch - 1) / ch <= (int64_t)PVEC * PT;
 #define ARBOR_TOPK_PART(T, R)                                                                   \
-  hipLaunchKernelGGL((uncert_topk_part<T, R>), dim3(ch, n_rows), dim3(PT), 0, stream,            \
+  hipLaunchKernelGGL((uncert_topk_part<R, T>), dim3(ch, n_rows), dim3(PT), 0, stream,            \
                      static_cast<const T *>(logits), vocab, ch, top_k, part, cand, cand_n,       \
                      status)
     if (bf && res) ARBOR_TOPK_PART(__bf16, true);
