@@ -150,3 +150,65 @@ def test_allocate_refuses_a_small_workspace(nodes):
         assert lib.arbor_allocate(ctypes.byref(t), any_ptr, 1, 100, any_ptr, ctypes.byref(p),
                                   any_ptr, any_ptr, any_ptr, any_ptr, ws, size,
                                   None) == L.EWORKSPACE
+
+
+def _decode_need(parent, n, leaves, L_, H, G, D, dtype, n_slice):
+    """Bytes that the tree decode's plan takes of the workspace: the carved arrays, then
+    units, lists, partials and kept products (chunk sizes by the waves' even share)."""
+    maxd, up256 = 64, lambda x: (x + 255) // 256 * 256
+    below = {}
+    for leaf in leaves:
+        x = leaf
+        while x >= 0:
+            below[x] = below.get(x, 0) + 1
+            x = parent[x]
+    blocks = lambda x: (below[x] * G + 15) // 16
+    planes, bf = L_ * H, dtype == L.BF16
+    waves = 3072 if bf and D == 64 else 2048
+    work = planes * sum(n[x] * blocks(x) for x in below)
+    least = min((n[x] for x in below if n[x]), default=1 << 30)
+    C = 64
+    for c in ([1024, 512, 256, 128] if bf else [256, 128]):
+        if 4 * work >= c * waves * (5 if least < c else 4):
+            C = c
+            break
+    chunks = lambda x: -(-n[x] // C)
+    units = sum(chunks(x) * blocks(x) for x in below)
+    rows = sum(chunks(x) * below[x] * G for x in below)
+    chain = lambda x: [] if x < 0 else [x] + chain(parent[x])
+    max_np = max(sum(chunks(x) for x in chain(leaf)) for leaf in leaves)
+    nb, pieces = len(leaves), sum(-(-n[x] // 64) for x in below)
+    floats = 12 * units + nb * max_np + pieces + 8 + rows * planes * (2 + D)
+    floats += n_slice * H * 64 * sum(below[x] * G * -(-n[x] // 64) for x in below)
+    carve = up256(64) + 3 * up256(4 * nb * maxd) + 2 * up256(4 * nb)
+    if nb > 64:
+        carve += 7 * up256(4 * nb * maxd) + up256(8 * nb * maxd)
+    return carve + 4 * floats + 256
+
+
+@pytest.mark.parametrize("dtype,D", [(L.BF16, 128), (L.BF16, 64), (L.F32, 128)])
+def test_the_workspace_covers_the_decode_plan(dtype, D):
+    """Trees from one leaf to wide frontiers, short and long blocks, one layer to 80."""
+    lib, rng = L.load(), random.Random(D + dtype)
+    for _ in range(1500):
+        V = rng.choice([1, 2, 5, 30, 200])
+        parent = [-1] + [rng.randint(max(0, i - rng.choice([1, 4, V])), i - 1) for i in range(1, V)]
+        depth = [0] * V
+        for i in range(1, V):
+            if depth[parent[i]] >= 62:
+                parent[i] = 0
+            depth[i] = depth[parent[i]] + 1
+        top = rng.choice([1, 40, 300, 3000])
+        n = [rng.randint(0, top) for _ in range(V)]
+        n[0] = rng.choice([0, 64, 5000, 70000])
+        leaves = [rng.randrange(V) for _ in range(rng.choice([1, 3, 16, 64, 65, 150]))]
+        L_, H, G, S = rng.choice([1, 4, 32, 80]), rng.choice([1, 4, 8]), rng.choice([1, 4, 8]), \
+            rng.choice([0, 1, 2])
+        total = [0] * V
+        for i in range(V):
+            total[i] = n[i] + (total[parent[i]] if i else 0)
+        g = L.Geom(L_, H, G, D, 16, dtype, 1 << 20)
+        sz = L.Sizes(V, sum(n), max(total[x] for x in leaves), 0, 1, S, len(leaves), L_)
+        size = lib.arbor_workspace_size(ctypes.byref(g), ctypes.byref(sz))
+        need = _decode_need(parent, n, leaves, L_, H, G, D, dtype, S)
+        assert need <= size, (V, len(leaves), L_, H, G, S, need, size)
